@@ -1,0 +1,266 @@
+"""The library's work as its callers meet it, one case per kind of call and size (`listed`), and a generator
+of further cases over the same ranges (`draw`).
+
+A case is a dict of plain values; `kind` says which public entry points a pass goes through:
+
+  project   bda_kv_project, or bda_kv_project_packed where `packed`: keys and values of a layer in one launch
+  train     bda_kv_project and bda_kv_project_backward with both gradients: a layer's training step
+  lowrank   bda_lowrank_linear: a compressed linear layer
+  prepare   bda_prepare_device_ex: a layer's weights converted at load time, window search and companions included
+
+Values: latent rows are RMS-normalised Gaussians (they come out of a norm), upstream gradients and linear
+inputs Gaussians, weights Gaussians of standard deviation 0.02.  The coefficients C of the run-time calls are
+Gaussians with a scale per head (log-normal around 0.5), the size that blocks of windows picked by their
+residual have.
+"""
+import math
+
+import torch
+
+import paper_2510_01718_amd as bda
+
+DTYPES = {"f32": (bda.BDA_F32, torch.float32, 4), "f16": (bda.BDA_F16, torch.float16, 2), "bf16": (bda.BDA_BF16, torch.bfloat16, 2)}
+MODES = {"first": bda.BASIS_FIRST, "last": bda.BASIS_LAST, "residual_min": bda.BASIS_RESIDUAL_MIN, "offset_search": bda.BASIS_OFFSET_SEARCH}
+
+
+def _project(name, T, d_c, d_h, Hk, Hv, dtype, off_k=0, off_v=0, out="same", packed=False):
+    return {"name": name, "kind": "project", "T": T, "d_c": d_c, "d_h": d_h, "Hk": Hk, "Hv": Hv, "off_k": off_k, "off_v": off_v,
+            "dtype": dtype, "out": out, "packed": packed}
+
+
+def _train(name, T, d_c, d_h, Hk, Hv, dtype, off_k=0, off_v=0, grad="same"):
+    return {"name": name, "kind": "train", "T": T, "d_c": d_c, "d_h": d_h, "Hk": Hk, "Hv": Hv, "off_k": off_k, "off_v": off_v,
+            "dtype": dtype, "grad": grad}
+
+
+def _lowrank(name, T, d_in, r, d_out, dtype, last=False):
+    return {"name": name, "kind": "lowrank", "T": T, "d_in": d_in, "r": r, "d_out": d_out, "last": last, "dtype": dtype}
+
+
+def _prepare(name, d_c, d_h, H, d_side, side, mode, w_dtype, c_dtype):
+    return {"name": name, "kind": "prepare", "d_c": d_c, "d_h": d_h, "H": H, "d_side": d_side, "side": side, "mode": mode,
+            "w_dtype": w_dtype, "c_dtype": c_dtype}
+
+
+def listed():
+    return [
+        # one sequence generating a token: a stream over 3 MB of weights and mostly latency
+        _project("decode_1_token", 1, 512, 128, 16, 16, "f16"),
+        # a serving batch generating, 128 + 128 heads, weights repacked at load time
+        _project("decode_32_tokens_wide", 32, 512, 128, 128, 128, "bf16", 0, 384, packed=True),
+        # a prompt of odd length, or a chunk of a long one beside decoding sequences
+        _project("prefill_777", 777, 512, 128, 16, 16, "f16", 0, 384),
+        # a whole prompt
+        _project("prefill_4096", 4096, 512, 128, 16, 16, "f16"),
+        # a long prompt at 128 + 128 heads: the largest forward there is
+        _project("prefill_8192_wide", 8192, 512, 128, 128, 128, "bf16"),
+        # head and latent widths off the usual powers of two, windows where a search put them, float32 results
+        _project("prefill_odd_heads", 3001, 384, 96, 12, 12, "bf16", 208, 48, out="f32"),
+        # a small translation-sized model trained in float32
+        _train("train_float32", 4096, 512, 64, 8, 8, "f32"),
+        # a training step at one prompt's worth of tokens, gradients kept in float32
+        _train("train_4096", 4096, 512, 128, 16, 16, "f16", 0, 384, grad="f32"),
+        # the same at 128 + 128 heads and 8192 tokens
+        _train("train_8192_wide", 8192, 512, 128, 128, 128, "bf16", 0, 384),
+        # a pruned feed-forward layer of rank 1024 over a long prompt
+        _lowrank("lowrank_8192", 8192, 4096, 1024, 11008, "f16"),
+        # loading a layer with the full window search: keys with the query weight, values with the output weight
+        _prepare("prepare_search", 512, 128, 16, 2048, "qo", "offset_search", "f32", "f16"),
+        # loading a 128-head layer from a bf16 checkpoint, the better of the two end windows
+        _prepare("prepare_wide", 512, 128, 128, 1536, "q", "residual_min", "bf16", "bf16"),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return max(lo, min(hi, int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))))
+
+
+def _window(rng, d_c, d_h):
+    last = d_c - d_h
+    return rng.choice([0, last, 16 * rng.randint(0, last // 16)])
+
+
+def _heads(rng, n_max, d_h):
+    """Heads of the key and value groups: both alike as in a layer, or different ones."""
+    most = max(2, n_max // d_h)
+    Hk = _log_int(rng, 1, most // 2)
+    return Hk, Hk if rng.random() < 0.6 else max(1, min(most - Hk, _log_int(rng, 1, most // 2)))
+
+
+def draw(rng):
+    kind = rng.choice(["project", "project", "project", "project", "train", "train", "train", "lowrank", "prepare", "prepare"])
+    if kind in ("project", "train"):
+        dtype = rng.choice(["f16", "bf16", "f16", "bf16", "f32"])
+        if rng.random() < 0.6:                                    # the widths of the configurations
+            d_c, d_h = (512, 128) if dtype != "f32" else (512, 64)
+        else:
+            d_h = rng.choice([32, 64, 96, 128, 192, 256]) if dtype != "f32" else rng.choice([16, 32, 64, 80, 128])
+            d_c = d_h + 32 * rng.randint(2, 20)
+        if dtype == "f32":                                        # at most the listed float32 case's products
+            n_max, t_max = 4096, 8192
+            most = 4096 * 448 * 1024
+        else:
+            n_max, t_max = 32768, 8192
+            most = 8192 * 384 * 32768
+        Hk, Hv = _heads(rng, n_max, d_h)
+        N = (Hk + Hv) * d_h
+        T = _log_int(rng, 1, t_max) if kind == "project" else _log_int(rng, 128, t_max)
+        T = max(1, min(T, most // ((d_c - d_h) * N)))
+        off_k, off_v = _window(rng, d_c, d_h), _window(rng, d_c, d_h)
+        if kind == "project":
+            c = _project("", T, d_c, d_h, Hk, Hv, dtype, off_k, off_v, "f32" if rng.random() < 0.2 else "same",
+                         packed=dtype != "f32" and T <= 64 and rng.random() < 0.4)
+        else:
+            c = _train("", T, d_c, d_h, Hk, Hv, dtype, off_k, off_v, "f32" if rng.random() < 0.4 else "same")
+    elif kind == "lowrank":
+        d_in, r = 256 * rng.randint(4, 16), 64 * rng.randint(4, 16)
+        d_out = r + 8 * _log_int(rng, 64, 1248)
+        c = _lowrank("", _log_int(rng, 16, 8192), d_in, r, d_out, rng.choice(["f16", "bf16"]), rng.random() < 0.3)
+    else:
+        d_h = rng.choice([32, 64, 64, 96, 128, 128, 128])
+        d_c = d_h + rng.choice([128, 192, 256, 384])
+        mode = rng.choice(["first", "last", "residual_min", "residual_min", "offset_search", "offset_search"])
+        H = _log_int(rng, 2, 16 if mode == "offset_search" else 128)
+        d_side = _log_int(rng, 128, 2048 if H <= 16 else 1536)
+        c = _prepare("", d_c, d_h, H, d_side, rng.choice(["none", "q", "o", "qo" if H <= 16 else "q"]), mode,
+                     rng.choice(["f32", "f16", "bf16"]), rng.choice(["f16", "bf16"]))
+    del c["name"]
+    return c
+
+
+def _randn(gen, rows, cols, dtype, std=1.0):
+    t = torch.randn((rows, cols), generator=gen, device="cuda")
+    return (t if std == 1.0 else t.mul_(std)).to(dtype)
+
+
+def _latent(gen, T, d_c, dtype):
+    c = torch.randn((T, d_c), generator=gen, device="cuda")
+    return c.mul_(torch.rsqrt(c.square().mean(dim=1, keepdim=True) + 1e-6)).to(dtype)
+
+
+def _coefficients(gen, K, heads, d_h, dtype):
+    C = torch.randn((K, heads, d_h), generator=gen, device="cuda")
+    scale = torch.randn((heads, 1), generator=gen, device="cuda").mul_(0.5).exp_().mul_(0.5)
+    return C.mul_(scale).to(dtype).reshape(K, heads * d_h)
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    stream = int(torch.cuda.current_stream().cuda_stream)
+    s = {"case": case, "stream": stream}
+    kind = case["kind"]
+    if kind in ("project", "train"):
+        T, d_c, d_h, H = case["T"], case["d_c"], case["d_h"], [case["Hk"], case["Hv"]]
+        N, K = sum(H) * d_h, d_c - d_h
+        code, dt, _ = DTYPES[case["dtype"]]
+        s.update(H=H, off=[case["off_k"], case["off_v"]], N=N, code=code, c=_latent(gen, T, d_c, dt), C=_coefficients(gen, K, sum(H), d_h, dt))
+        if kind == "project":
+            s["out_code"], out_dt, _ = DTYPES[case["dtype" if case["out"] == "same" else "out"]]
+            if case["packed"]:
+                s["packed"] = torch.empty_like(s["C"])
+                bda.bda_pack_weights(s["C"], N, d_c, d_h, H, code, s["packed"], stream)
+        else:
+            s["grad_code"], grad_dt, _ = DTYPES[case["dtype" if case["grad"] == "same" else "grad"]]
+            out_dt = dt
+            s["d_out"] = _randn(gen, T, N, dt)
+            s["grad_c"] = torch.empty((T, d_c), dtype=grad_dt, device="cuda")
+            s["grad_C"] = torch.empty((K, N), dtype=grad_dt, device="cuda")
+        s["out"] = torch.empty((T, N), dtype=out_dt, device="cuda")
+    elif kind == "lowrank":
+        T, d_in, r, d_out = case["T"], case["d_in"], case["r"], case["d_out"]
+        s["code"], dt, _ = DTYPES[case["dtype"]]
+        s.update(x=_randn(gen, T, d_in, dt), U=_randn(gen, d_in, r, dt, 0.0128), C=_randn(gen, r, d_out - r, dt, 0.5),
+                 off=d_out - r if case["last"] else 0, out=torch.empty((T, d_out), dtype=dt, device="cuda"))
+    else:
+        d_c, d_h, H, d_side = case["d_c"], case["d_h"], case["H"], case["d_side"]
+        N, K = H * d_h, d_c - d_h
+        s["w_code"], w_dt, _ = DTYPES[case["w_dtype"]]
+        s["c_code"], c_dt, _ = DTYPES[case["c_dtype"]]
+        mode = MODES[case["mode"]]
+        nb = bda.bda_prepare_device_workspace_bytes(d_c, H, d_h, mode, True)
+        s.update(N=N, mode=mode, ws_bytes=nb, ws=torch.empty(max(nb, 16), dtype=torch.uint8, device="cuda"), jobs=[])
+        for side in ("none",) if case["side"] == "none" else tuple(case["side"]):
+            job = {"W": _randn(gen, d_c, N, w_dt, 0.02), "C": torch.empty((K, N), dtype=c_dt, device="cuda"),
+                   "off": torch.zeros(1, dtype=torch.int32, device="cuda"), "resid": torch.zeros(3, dtype=torch.float64, device="cuda"),
+                   "flag": torch.zeros(1, dtype=torch.int32, device="cuda"), "side": None, "side_out": None, "ld_side": 0, "kind": bda.SIDE_NONE}
+            if side != "none":
+                shape = (d_side, N) if side == "q" else (N, d_side)
+                job.update(side=_randn(gen, *shape, w_dt, 0.02), side_out=torch.empty(shape, dtype=c_dt, device="cuda"), ld_side=shape[1],
+                           kind=bda.SIDE_Q if side == "q" else bda.SIDE_O)
+            s["jobs"].append(job)
+    return s
+
+
+def run(s):
+    case = s["case"]
+    kind = case["kind"]
+    if kind == "project":
+        T, d_c, d_h, N = case["T"], case["d_c"], case["d_h"], s["N"]
+        if case["packed"]:
+            bda.bda_kv_project_packed(s["c"], d_c, T, d_c, d_h, s["H"], s["off"], s["packed"], s["out"], N, s["code"], s["out_code"], s["stream"])
+        else:
+            bda.bda_kv_project(s["c"], d_c, T, d_c, d_h, s["H"], s["off"], s["C"], N, s["out"], N, s["code"], s["out_code"], s["stream"])
+        return s["out"]
+    if kind == "train":
+        T, d_c, d_h, N = case["T"], case["d_c"], case["d_h"], s["N"]
+        bda.bda_kv_project(s["c"], d_c, T, d_c, d_h, s["H"], s["off"], s["C"], N, s["out"], N, s["code"], s["code"], s["stream"])
+        bda.bda_kv_project_backward(s["c"], d_c, s["d_out"], N, s["C"], N, T, d_c, d_h, s["H"], s["off"], s["grad_c"], d_c,
+                                    s["grad_C"], N, s["code"], s["grad_code"], s["stream"])
+        return s["out"], s["grad_c"], s["grad_C"]
+    if kind == "lowrank":
+        bda.bda_lowrank_linear(s["x"], case["d_in"], case["T"], case["d_in"], case["r"], case["d_out"], s["off"], s["U"], s["C"], s["out"],
+                               case["d_out"], s["code"], s["stream"])
+        return s["out"]
+    outs = []
+    for j in s["jobs"]:
+        bda.bda_prepare_device_ex(j["W"], s["N"], s["w_code"], case["d_c"], case["H"], case["d_h"], j["C"], s["N"], s["c_code"], side=j["side"],
+                                  ld_side=j["ld_side"], d_side=case["d_side"] if j["kind"] else 0, side_kind=j["kind"], side_out=j["side_out"],
+                                  ld_side_out=j["ld_side"], mode=s["mode"], basis_offset_out=j["off"], resid_out=j["resid"],
+                                  singular_head=j["flag"], workspace=s["ws"], workspace_bytes=s["ws_bytes"], stream=s["stream"])
+        outs += [j["C"], j["off"], j["resid"], j["flag"]] + ([j["side_out"]] if j["kind"] else [])
+    return outs
+
+
+def work(case):
+    kind = case["kind"]
+    if kind in ("project", "train"):
+        T, d_c, K, N = case["T"], case["d_c"], case["d_c"] - case["d_h"], (case["Hk"] + case["Hv"]) * case["d_h"]
+        es = DTYPES[case["dtype"]][2]
+        flops = 2.0 * T * K * N
+        if kind == "project":
+            out = es if case["out"] == "same" else DTYPES[case["out"]][2]
+            return {"bytes": es * (T * d_c + K * N) + out * T * N, "flops": flops}
+        gs = es if case["grad"] == "same" else DTYPES[case["grad"]][2]
+        return {"bytes": es * (T * d_c + K * N + 2 * T * N) + gs * (T * d_c + K * N), "flops": 3 * flops}
+    if kind == "lowrank":
+        T, d_in, r, d_out = case["T"], case["d_in"], case["r"], case["d_out"]
+        return {"bytes": 2 * (T * d_in + d_in * r + r * (d_out - r) + T * d_out), "flops": 2.0 * T * r * (d_in + d_out - r)}
+    # per head: an inverse and the rows outside the window for every candidate, the companion's product with all of W once (every
+    # window's companion block is a part of it) and the stored form's product for every candidate
+    d_c, n, H, d_side = case["d_c"], case["d_h"], case["H"], case["d_side"]
+    K, N, ws, cs = d_c - n, H * n, DTYPES[case["w_dtype"]][2], DTYPES[case["c_dtype"]][2]
+    cands = {"first": 1, "last": 1, "residual_min": 2, "offset_search": (K + 15) // 16 + 1}[case["mode"]]
+    nbytes = flops = 0.0
+    for side in ("none",) if case["side"] == "none" else tuple(case["side"]):
+        nbytes += ws * d_c * N + cs * K * N
+        flops += H * cands * (2.0 * n ** 3 + 2.0 * K * n * n)
+        if side == "none":
+            flops += H * cands * 2.0 * K * n * n
+        else:
+            nbytes += (ws + cs) * d_side * N
+            flops += H * 2.0 * d_side * d_c * n + H * cands * 2.0 * d_side * K * n
+    return {"bytes": nbytes, "flops": flops}
+
+
+def tolerance(case):
+    """About four times the distance from the same path in float64, rounded once to the stored types (float32 sums in another order
+    move a result of 16 bits by its last place now and then, and the linear layer's stored h as well)."""
+    stored = case["c_dtype"] if case["kind"] == "prepare" else case["dtype"]
+    if case["kind"] == "project" and case["out"] == "f32" and case["dtype"] != "f32":
+        return {"rel": 1.5e-6, "max": 1.2e-5, "differ": 0.0}
+    if stored == "f32":
+        return {"rel": 6e-6, "max": 5e-5, "differ": 0.0}
+    if case["kind"] == "lowrank":
+        return {"rel": 2.4e-4 if stored == "f16" else 7e-4, "max": 4e-3 if stored == "f16" else 3.2e-2, "differ": 0.0}
+    return {"rel": 6e-5 if stored == "f16" else 2.2e-4, "max": 4e-3 if stored == "f16" else 3.2e-2, "differ": 0.0}
