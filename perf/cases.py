@@ -264,3 +264,75 @@ def tolerance(case):
     if case["kind"] == "lowrank":
         return {"rel": 2.4e-4 if stored == "f16" else 7e-4, "max": 4e-3 if stored == "f16" else 3.2e-2, "differ": 0.0}
     return {"rel": 6e-5 if stored == "f16" else 2.2e-4, "max": 4e-3 if stored == "f16" else 3.2e-2, "differ": 0.0}
+
+
+def _outside(M, off, n):
+    """Columns of M outside the window [off, off + n), ascending."""
+    return torch.cat([M[:, :off], M[:, off + n:]], dim=1)
+
+
+def _exact_prepare(case, job):
+    """C, window, residuals, flag (and companion) of one job: every candidate window in float64, the residual on C and the companion
+    as stored."""
+    d_c, n, H = case["d_c"], case["d_h"], case["H"]
+    K, last = d_c - n, d_c - n
+    stored = DTYPES[case["c_dtype"]][1]
+    W = job["W"].double().reshape(d_c, H, n).permute(1, 0, 2)                     # head, latent dimension, head column
+    kind = job["kind"]
+    side = None
+    if kind == bda.SIDE_Q:
+        side = job["side"].double().reshape(-1, H, n).permute(1, 0, 2)            # head, row of W_q, head column
+    elif kind == bda.SIDE_O:
+        side = job["side"].double().reshape(H, n, -1).transpose(1, 2)             # head, column of W_o, head column
+    offs = {"first": [0], "last": [last], "residual_min": [0, last], "offset_search": sorted(set(range(0, last + 1, 16)) | {last})}[case["mode"]]
+    best, means = None, {}
+    for off in offs:
+        A = W[:, off:off + n]
+        rest = torch.cat([W[:, :off], W[:, off + n:]], dim=1)
+        C = torch.linalg.solve(A.cpu().transpose(1, 2), rest.cpu().transpose(1, 2)).transpose(1, 2).to(W.device)
+        Chat, B, total = C.to(stored).double(), [], 0.0
+        for h in range(H):
+            if side is None:
+                total += float(torch.linalg.norm(rest[h] - Chat[h] @ A[h]))
+                continue
+            B.append(side[h] @ A[h].T)                                            # d_side x n for either companion
+            Bhat = B[h].to(stored).double()
+            total += math.hypot(float(torch.linalg.norm(side[h] @ A[h].T - Bhat)), float(torch.linalg.norm(side[h] @ rest[h].T - Bhat @ Chat[h].T)))
+        means[off] = total / H
+        if best is None or means[off] < means[best[0]]:
+            best = (off, C, B)
+    off, C, B = best
+    resid = torch.tensor([means.get(0, math.nan), means.get(last, math.nan), means[off]], dtype=torch.float64)
+    out = [C.permute(1, 0, 2).reshape(K, H * n), torch.tensor([off], dtype=torch.int32), resid, torch.zeros(1, dtype=torch.int32)]
+    if side is not None:
+        B = torch.stack(B)
+        out.append(B.permute(1, 0, 2).reshape(-1, H * n) if kind == bda.SIDE_Q else B.transpose(1, 2).reshape(H * n, -1))
+    return out
+
+
+def exact(case, seed):
+    s = prepare(case, seed)
+    kind = case["kind"]
+    if kind == "prepare":
+        return [t for job in s["jobs"] for t in _exact_prepare(case, job)]
+    if kind == "lowrank":
+        h = s["x"].double() @ s["U"].double()
+        return torch.cat([h @ s["C"].double(), h] if case["last"] else [h, h @ s["C"].double()], dim=1)
+    n, c = case["d_h"], s["c"].double()
+    out = torch.empty((case["T"], s["N"]), dtype=torch.float64, device=c.device)
+    grad_c, grad_C = torch.zeros_like(c), torch.empty(s["C"].shape, dtype=torch.float64, device=c.device)
+    col = 0
+    for H, off in zip(s["H"], s["off"]):
+        cols = slice(col, col + H * n)
+        col += H * n
+        C = s["C"][:, cols].double()
+        out[:, cols] = _outside(c, off, n) @ C
+        out[:, cols] += c[:, off:off + n].repeat(1, H)
+        if kind == "train":
+            g = s["d_out"][:, cols].double()
+            grad_C[:, cols] = _outside(c, off, n).T @ g
+            rest = g @ C.T
+            grad_c[:, :off] += rest[:, :off]
+            grad_c[:, off + n:] += rest[:, off:]
+            grad_c[:, off:off + n] += g.reshape(-1, H, n).sum(dim=1)
+    return out if kind == "project" else (out, grad_c, grad_C)
