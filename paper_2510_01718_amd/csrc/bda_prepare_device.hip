@@ -1,13 +1,13 @@
 // GPU preparation of one projection (Algorithm "BD Attention Preparation (QK)", Appendix "BD for VO in
 // MHA", Algorithm "BD Decomposition (Row)" for the window choice, Appendix "Residual-Min with Offset
 // Search" for the candidate windows).  Float64 throughout, four kernels:
-//   prepare_kernel   C_h = W_h[Bbar,:] W_h[B,:]^{-1}, one workgroup per head (several when there are few heads:
-//                    each inverts for itself and takes a share of the rows): the d_h x d_h basis block
-//                    is inverted in place by Gauss-Jordan elimination with partial (row) pivoting (in
-//                    LDS up to d_h = 128, in the caller's workspace up to 256; the row interchanges are
-//                    undone as column interchanges at the end), then the d_c - d_h rows outside the
-//                    window are multiplied by the inverse, 16 rows at a time staged through LDS, and
-//                    stored rounded to the requested type;
+//   invert_kernel    C_h = W_h[Bbar,:] W_h[B,:]^{-1} for d_h <= 128, one workgroup per head (several when
+//                    there are few heads: each inverts for itself and takes a share of the rows): the
+//                    basis block is inverted in registers by Gauss-Jordan elimination with partial (row)
+//                    pivoting, then the d_c - d_h rows outside the window are multiplied by the inverse on
+//                    the matrix cores and stored rounded to the requested type;
+//   prepare_wide_kernel   the same for d_h up to 256 with the block in the caller's workspace (the row
+//                    interchanges are undone as column interchanges at the end);
 //   side_kernel      the companion block: W_q^h W_h[B,:]^T or W_h[B,:] W_o^h, rounded the same way;
 //   residual_kernel  the Frobenius reconstruction error of the stored form of one head - what was just
 //                    written to C and to the companion output, read back - as partial sums of squares
@@ -23,6 +23,7 @@
 
 #include <cstdint>
 #include <mutex>
+#include <type_traits>
 
 #include "bda_internal.h"
 
@@ -94,26 +95,241 @@ struct PrepArgs {
     int d_c, H, d_h, off, d_side, side_kind;
     int h0;                      // first head of this launch (batches when the block lives in the workspace)
     int cand, n_parts;
+    int w_type, c_type;          // element types of W / side and of C / side_out
 };
 
 __device__ __forceinline__ int window_start(const PrepArgs& a) { return a.off_ptr ? *a.off_ptr : a.off; }
 
-// BIG: the basis block lives in global memory (a.mat, one block per workgroup) instead of LDS.
-template <typename WT, typename CT, bool BIG>
-__global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const PrepArgs a)
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// v_mfma_f64_16x16x4: lane (c = lane % 16, g = lane / 16) holds A[c][g] and B[g][c] and receives
+// D[4 r + g][c] in element r.
+__device__ __forceinline__ f64x4 mfma_f64(double a, double b, f64x4 acc) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0); }
+
+// Calls f(T{}) with the C++ type of a bda_dtype (one uniform branch around a whole loop, where a kernel
+// instantiated per type would only multiply the code).
+template <typename F>
+__device__ __forceinline__ void with_type(int type, F&& f)
+{
+    if (type == BDA_F32) f(float{});
+    else if (type == BDA_F16) f(_Float16{});
+    else if (type == BDA_BF16) f(__bf16{});
+    else f(double{});
+}
+
+// Largest of a 32-bit value over the 64 lanes, in every lane.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
+{
+    auto step = [&](auto ctrl) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xf, 0xf, true);
+        v = o > v ? o : v;
+    };
+    step(std::integral_constant<int, 0x111>{});      // row_shr 1, 2, 4, 8: lane 15 of a row of 16 holds the row's largest
+    step(std::integral_constant<int, 0x112>{});
+    step(std::integral_constant<int, 0x114>{});
+    step(std::integral_constant<int, 0x118>{});
+    uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)v, 15);
+#pragma unroll
+    for (int l = 31; l < 64; l += 16) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+        m = o > m ? o : m;
+    }
+    return m;
+}
+
+// Inverse of the basis block and C_h = W_h[Bbar,:] A^{-1}, head widths up to 32 NB (NB = 1 .. 4).  512
+// threads = 16 rows x 32 columns of threads; a thread keeps rows ty + 16 u and columns tx + 32 v of the
+// block in registers through the whole elimination.  A step moves one column and one row (2 KiB) through
+// LDS and waits twice: the owners of column k write it, every wave finds the pivot for itself, the owners
+// of the pivot row write that, every thread updates its 8 NB^2 elements.  Rows are never interchanged: a
+// row that has been a pivot is left out of the later searches, and the permutation is applied where the
+// inverse is written to LDS for the product.  The column loop is unrolled over v and the pivot row's u is
+// a uniform switch, so every register index is a constant.
+// The pivot is the largest of the column to 13 bits of its mantissa (the key carries the row number in its
+// low bits): growth is bounded as with the exact largest, up to a factor 1 + 2^-13.
+// The product runs on v_mfma_f64_16x16x4: a wave takes 16 rows of W_h[Bbar,:] straight from memory into
+// registers (they are its A operand) against the inverse in LDS, whose pitch of 16 mod 32 doubles lets the
+// two k rows that one half of a wave reads fall into different halves of the banks.
+// Bound: the elimination's serial chain (128 steps), then the double-precision matrix rate.  A version that
+// kept the block in LDS and rewrote all of it in every step, with the product in vector FMAs, took 0.62 ms
+// for 16 heads of 128 and 0.88 ms for 128; this one about 0.15 ms (a layer's two 25-window searches with
+// companions: 52.1 -> 27.5 ms).
+constexpr int kInvertThreads = 512;
+template <int NB>
+constexpr int invert_lds_bytes() { return 32 * NB * (32 * NB + 16) * (int)sizeof(double); }
+
+template <int NB>
+__global__ __launch_bounds__(kInvertThreads) void invert_kernel(const PrepArgs a)
+{
+    constexpr int NP = 32 * NB, NU = 2 * NB, NV = NB, LD = NP + 16;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    double* const inv = (double*)smem_raw;
+    __shared__ double s_col[2][NP];
+    __shared__ double s_row[NP];
+    __shared__ double s_red[kInvertThreads / 64];
+    __shared__ int s_piv[NP], s_pos[NP];
+    const int n = a.d_h, t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int h = blockIdx.x;
+    const int off = window_start(a);
+    if (off < 0) return;                       // no usable window was found: nothing to prepare
+    const int64_t col0 = (int64_t)h * n;
+    const int tx = t & 31, ty = t >> 5;
+
+    double m[NU][NV];
+    double part = 0.0;
+    with_type(a.w_type, [&](auto tag) {
+        typedef decltype(tag) WT;
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const int i = ty + 16 * u, j = tx + 32 * v;
+                m[u][v] = (i < n && j < n) ? load_as_double<WT>(a.W, (int64_t)(off + i) * a.ldw + col0 + j) : 0.0;
+            }
+    });
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) part = fma(m[u][v], m[u][v], part);
+    for (int s = 32; s >= 1; s >>= 1) part += __shfl_xor(part, s, 64);
+    if (lane == 0) s_red[wave] = part;
+    __syncthreads();
+    double scale = 0.0;
+    for (int w = 0; w < kInvertThreads / 64; ++w) scale += s_red[w];
+    const double tiny = sqrt(scale) * n * 2.220446049250313e-16;
+
+    uint64_t used_lo = 0, used_hi = 0;         // rows that have been pivots (uniform)
+    bool singular = false;
+#pragma unroll
+    for (int kv = 0; kv < NV; ++kv) {
+        for (int kk = 0; kk < 32 && 32 * kv + kk < n; ++kk) {
+            const int k = 32 * kv + kk;
+            double* const col = s_col[k & 1];
+            if (tx == kk) {
+#pragma unroll
+                for (int u = 0; u < NU; ++u) col[ty + 16 * u] = m[u][kv];
+            }
+            __syncthreads();
+            uint32_t key = 0;
+            if (lane < n && !((used_lo >> lane) & 1)) {
+                const uint64_t b = __builtin_bit_cast(uint64_t, col[lane]);
+                key = ((uint32_t)(b >> 32) & 0x7fffff80u) | (uint32_t)(127 - lane);
+            }
+            if constexpr (NP > 64) {
+                if (lane + 64 < n && !((used_hi >> lane) & 1)) {
+                    const uint64_t b = __builtin_bit_cast(uint64_t, col[lane + 64]);
+                    const uint32_t key2 = ((uint32_t)(b >> 32) & 0x7fffff80u) | (uint32_t)(63 - lane);
+                    key = key2 > key ? key2 : key;
+                }
+            }
+            const int p = 127 - (int)(wave_max_u32(key) & 127u);       // uniform: the pivot row (< n: some row is unused)
+            const double pv = col[p];
+            if (!(fabs(pv) > tiny)) { singular = true; break; }
+            const int pu = p >> 4, pt = p & 15;
+            if (ty == pt) {
+#pragma unroll
+                for (int u = 0; u < NU; ++u)
+                    if (u == pu) {
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) s_row[tx + 32 * v] = m[u][v];
+                    }
+            }
+            if (t == 0) { s_piv[k] = p; s_pos[p] = k; }
+            if (p < 64) used_lo |= (uint64_t)1 << p; else used_hi |= (uint64_t)1 << (p - 64);
+            const double ip = 1.0 / pv;
+            double f[NU];
+#pragma unroll
+            for (int u = 0; u < NU; ++u) f[u] = col[ty + 16 * u];
+            __syncthreads();
+            double r[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) r[v] = s_row[tx + 32 * v] * ip;
+            if (tx == kk) r[kv] = ip;          // column k of the block is replaced by the inverse's
+#pragma unroll
+            for (int u = 0; u < NU; ++u)
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    const double cur = (v == kv && tx == kk) ? 0.0 : m[u][v];
+                    m[u][v] = fma(-f[u], r[v], cur);
+                }
+            if (ty == pt) {
+#pragma unroll
+                for (int u = 0; u < NU; ++u)
+                    if (u == pu) {
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) m[u][v] = r[v];
+                    }
+            }
+        }
+        if (singular) break;
+    }
+    if (singular) {
+        if (t == 0) {
+            if (a.status) atomicMax(a.status, h + 1);
+            if (a.cand_singular) a.cand_singular[a.cand] = 1;    // (every writer stores the same value)
+        }
+        return;
+    }
+    __syncthreads();                           // s_piv and s_pos are complete
+    // storage row p_k of the result is row k of (P A)^{-1}, and A^{-1} = (P A)^{-1} P
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int i = ty + 16 * u, j = tx + 32 * v;
+            const bool in = i < n && j < n;
+            inv[(i < n ? s_pos[i] : i) * LD + (j < n ? s_piv[j] : j)] = in ? m[u][v] : 0.0;
+        }
+    __syncthreads();
+
+    // gridDim.y workgroups per head each invert the block for themselves (the same operations in the same
+    // order, so the same inverse bit for bit) and share out the row tiles of the product.
+    const int K = a.d_c - n, c = lane & 15, g = lane >> 4;
+    for (int rt = (int)blockIdx.y + (int)gridDim.y * wave; rt * 16 < K; rt += (int)gridDim.y * (kInvertThreads / 64)) {
+        const int ra = rt * 16 + c;            // this lane's row of the A operand
+        const int src = ra < off ? ra : ra + n;
+        double av[8 * NB];
+        with_type(a.w_type, [&](auto tag) {
+            typedef decltype(tag) WT;
+#pragma unroll
+            for (int ks = 0; ks < 8 * NB; ++ks) {
+                const int k = 4 * ks + g;
+                av[ks] = (ra < K && k < n) ? load_as_double<WT>(a.W, (int64_t)src * a.ldw + col0 + k) : 0.0;
+            }
+        });
+#pragma unroll 1
+        for (int jt = 0; jt < NU; jt += 2) {
+            f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+            for (int ks = 0; ks < 8 * NB; ++ks) {
+                const double* const b = inv + (4 * ks + g) * LD + jt * 16 + c;
+                acc[0] = mfma_f64(av[ks], b[0], acc[0]);
+                acc[1] = mfma_f64(av[ks], b[16], acc[1]);
+            }
+            with_type(a.c_type, [&](auto tag) {
+                typedef decltype(tag) CT;
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int row = rt * 16 + 4 * r + g, j = (jt + q) * 16 + c;
+                        if (row < K && j < n) store_rounded<CT>(a.C, (int64_t)row * a.ldC + col0 + j, acc[q][r]);
+                    }
+            });
+        }
+    }
+}
+
+// Head widths above 128: the basis block lives in the workspace (a.mat, one block per workgroup).
+template <typename WT, typename CT>
+__global__ __launch_bounds__(kPrepThreads) void prepare_wide_kernel(const PrepArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const int n = a.d_h;
-    const int ld = BIG ? n : n + 1;            // LDS: odd stride in doubles, a column walk touches all banks
-    double* R;                                 // kPrepRows x n staging, also scratch for the reductions
-    double* A;                                 // n x ld: the basis block, then its inverse
-    if constexpr (BIG) {
-        R = (double*)smem_raw;
-        A = a.mat + (size_t)blockIdx.x * n * n;
-    } else {
-        A = (double*)smem_raw;
-        R = A + (size_t)n * ld;
-    }
+    const int ld = n;
+    double* const R = (double*)smem_raw;       // kPrepRows x n staging, also scratch for the reductions
+    double* const A = a.mat + (size_t)blockIdx.x * n * n;   // the basis block, then its inverse
     __shared__ int piv[kPrepMaxDh];
     __shared__ int s_pivot_row;
     __shared__ double s_pivot_val;
@@ -146,11 +362,7 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const PrepArgs a)
     __syncthreads();
 
     // ---- Gauss-Jordan inversion in place, partial pivoting ----------------------------------------
-    // thread -> (row, segment of the columns): two threads per row up to 128 rows, one per row beyond
-    const int rows_per_pass = n <= 128 ? 128 : 256;
-    const int row = t % rows_per_pass, seg = t / rows_per_pass, n_seg = kPrepThreads / rows_per_pass;
-    const int jn = (n + n_seg - 1) / n_seg;
-    const int j_lo = seg * jn, j_hi = (j_lo + jn < n) ? j_lo + jn : n;
+    const int row = t;
     for (int k = 0; k < n; ++k) {
         // pivot: the largest |A[i][k]|, i >= k (first such row on ties)
         if (t < 64) {
@@ -191,7 +403,7 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const PrepArgs a)
         __syncthreads();
         if (row < n && row != k) {
 #pragma unroll 8
-            for (int j = j_lo; j < j_hi; ++j) {
+            for (int j = 0; j < n; ++j) {
                 const double cur = (j == k) ? 0.0 : A[row * ld + j];
                 A[row * ld + j] = cur - f * A[k * ld + j];
             }
@@ -220,12 +432,8 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const PrepArgs a)
     __syncthreads();
 
     // ---- C_h = W_h[Bbar,:] A^{-1} ------------------------------------------------------------------
-    // With few heads a launch leaves most compute units idle, and the inversion above is one workgroup's
-    // latency whatever else runs: gridDim.y workgroups per head each invert the block for themselves (the
-    // same operations in the same order, so the same inverse bit for bit) and share out the row blocks of
-    // the product, which is a third of the kernel's time when one workgroup does all of them.
     const int K = a.d_c - n;
-    for (int r0 = (int)blockIdx.y * kPrepRows; r0 < K; r0 += (int)gridDim.y * kPrepRows) {
+    for (int r0 = 0; r0 < K; r0 += kPrepRows) {
         for (int e = t; e < kPrepRows * n; e += kPrepThreads) {
             const int i = e / n, c = e % n;
             const int r = r0 + i;
@@ -233,37 +441,20 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const PrepArgs a)
             R[i * n + c] = r < K ? load_as_double<WT>(a.W, (int64_t)src * a.ldw + col0 + c) : 0.0;
         }
         __syncthreads();
-        // thread -> (output column, subset of the staged rows): rows rg, rg + n_rg, ...
-        const int cols_per_pass = n <= 128 ? 128 : 256;
-        const int j = t % cols_per_pass, rg = t / cols_per_pass, n_rg = kPrepThreads / cols_per_pass;
-        if (j < n) {
+        if (t < n) {
             double acc[kPrepRows];
 #pragma unroll
             for (int m = 0; m < kPrepRows; ++m) acc[m] = 0.0;
-            if (n_rg == 2) {
 #pragma unroll 4
-                for (int k = 0; k < n; ++k) {
-                    const double b = A[k * ld + j];
+            for (int k = 0; k < n; ++k) {
+                const double b = A[k * ld + t];
 #pragma unroll
-                    for (int m = 0; m < kPrepRows / 2; ++m) acc[m] = fma(R[(2 * m + rg) * n + k], b, acc[m]);
-                }
+                for (int m = 0; m < kPrepRows; ++m) acc[m] = fma(R[m * n + k], b, acc[m]);
+            }
 #pragma unroll
-                for (int m = 0; m < kPrepRows / 2; ++m) {
-                    const int r = r0 + 2 * m + rg;
-                    if (r < K) store_rounded<CT>(a.C, (int64_t)r * a.ldC + col0 + j, acc[m]);
-                }
-            } else {
-#pragma unroll 4
-                for (int k = 0; k < n; ++k) {
-                    const double b = A[k * ld + j];
-#pragma unroll
-                    for (int m = 0; m < kPrepRows; ++m) acc[m] = fma(R[m * n + k], b, acc[m]);
-                }
-#pragma unroll
-                for (int m = 0; m < kPrepRows; ++m) {
-                    const int r = r0 + m;
-                    if (r < K) store_rounded<CT>(a.C, (int64_t)r * a.ldC + col0 + j, acc[m]);
-                }
+            for (int m = 0; m < kPrepRows; ++m) {
+                const int r = r0 + m;
+                if (r < K) store_rounded<CT>(a.C, (int64_t)r * a.ldC + col0 + t, acc[m]);
             }
         }
         __syncthreads();
@@ -522,29 +713,41 @@ int check_launch(const char* what)
     return err == hipSuccess ? BDA_OK : fail(BDA_EHIP, "bda_prepare_device: %s: %s", what, hipGetErrorString(err));
 }
 
+template <int NB>
+int launch_invert(const PrepArgs& a, hipStream_t st)
+{
+    static LdsLimitState once;
+    int dev = 0;
+    hipError_t err = hipGetDevice(&dev);
+    if (err != hipSuccess) return fail(BDA_EHIP, "bda_prepare_device: hipGetDevice: %s", hipGetErrorString(err));
+    constexpr int lds = invert_lds_bytes<NB>();
+    const bool tracked = dev >= 0 && dev < LdsLimitState::kMaxDevices;
+    if (!tracked || !once.done[dev].load(std::memory_order_acquire)) {
+        err = hipFuncSetAttribute((const void*)invert_kernel<NB>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (err != hipSuccess) return fail(BDA_EHIP, "bda_prepare_device: LDS size %d: %s", lds, hipGetErrorString(err));
+        if (tracked) once.done[dev].store(true, std::memory_order_release);
+    }
+    // workgroups per head: up to 64 per launch, at most one per row tile
+    const int row_tiles = (a.d_c - a.d_h + 15) / 16;
+    int per_head = 64 / a.H;
+    per_head = per_head < 1 ? 1 : per_head > row_tiles ? row_tiles : per_head;
+    hipLaunchKernelGGL(invert_kernel<NB>, dim3(a.H, per_head), dim3(kInvertThreads), lds, st, a);
+    return check_launch("prepare kernel");
+}
+
 template <typename WT, typename CT>
 int launch_prepare(PrepArgs a, int batch, hipStream_t st)
 {
     const int n = a.d_h;
-    const bool big = n > kPrepLdsDh;
-    const size_t stage = (size_t)(kPrepRows * n > kPrepThreads ? kPrepRows * n : kPrepThreads);
-    const size_t lds = ((big ? 0 : (size_t)n * (n + 1)) + stage) * sizeof(double);
-    const void* kern = big ? (const void*)prepare_kernel<WT, CT, true> : (const void*)prepare_kernel<WT, CT, false>;
-    hipError_t err = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (err != hipSuccess) return fail(BDA_EHIP, "bda_prepare_device: LDS size %zu: %s", lds, hipGetErrorString(err));
-    const int per_launch = big ? batch : a.H;
-    // workgroups per head (the block in LDS only: a block in the workspace belongs to one workgroup): up to
-    // 64 per launch, at most one per row block.  More shorten a lone call a little further (16 heads x 16:
-    // 52.6 ms for a layer's offset searches against 54.8) but fill every compute unit with redundant
-    // inversions, and then calls on other streams no longer run beside this one (measured).
-    const int row_blocks = (a.d_c - n + kPrepRows - 1) / kPrepRows;
-    int per_head = big ? 1 : 64 / a.H;
-    per_head = per_head < 1 ? 1 : per_head > row_blocks ? (row_blocks < 1 ? 1 : row_blocks) : per_head;
-    for (int h0 = 0; h0 < a.H; h0 += per_launch) {
+    if (n <= 32) return launch_invert<1>(a, st);
+    if (n <= 64) return launch_invert<2>(a, st);
+    if (n <= 96) return launch_invert<3>(a, st);
+    if (n <= kPrepLdsDh) return launch_invert<4>(a, st);
+    const size_t lds = (size_t)kPrepRows * n * sizeof(double);
+    for (int h0 = 0; h0 < a.H; h0 += batch) {
         a.h0 = h0;
-        const int heads = a.H - h0 < per_launch ? a.H - h0 : per_launch;
-        if (big) hipLaunchKernelGGL((prepare_kernel<WT, CT, true>), dim3(heads), dim3(kPrepThreads), lds, st, a);
-        else hipLaunchKernelGGL((prepare_kernel<WT, CT, false>), dim3(heads, per_head), dim3(kPrepThreads), lds, st, a);
+        const int heads = a.H - h0 < batch ? a.H - h0 : batch;
+        hipLaunchKernelGGL((prepare_wide_kernel<WT, CT>), dim3(heads), dim3(kPrepThreads), lds, st, a);
         if (int rc = check_launch("prepare kernel")) return rc;
     }
     return BDA_OK;
@@ -610,6 +813,7 @@ int run_prepare(const PrepCall& c, const Plan& p, unsigned char* ws, hipStream_t
     a.ldw = c.ldw; a.ld_side = c.ld_side; a.ldC = c.ldC; a.ld_side_out = c.ld_side_out;
     a.d_c = c.d_c; a.H = c.H; a.d_h = c.d_h; a.d_side = c.d_side; a.side_kind = c.side_kind;
     a.n_parts = p.n_parts;
+    a.w_type = c.w_dtype; a.c_type = c.c_dtype;
     const bool multi = p.n_cand > 1;
     int side_parts = 1;                      // workgroups per head of the companion kernel: its 64 x 64 tiles, at most 64
     if (c.side_kind != BDA_SIDE_NONE) {

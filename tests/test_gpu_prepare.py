@@ -183,3 +183,16 @@ def test_prepare_device_ex_calls_overlapping_on_several_streams():
         assert int(b["flag"].item()) == 0 and int(b["off"].item()) == ref["off"], j
         assert np.array_equal(_host(b["C"], wl.F16), ref["C"]) and np.array_equal(_host(b["side_out"], wl.F16), ref["side"]), j
         assert np.array_equal(b["resid"].cpu().numpy(), ref["resid"]), j
+
+
+@pytest.mark.parametrize("d_c,H,d_h,d_side", [(9, 2, 1, 3), (50, 1, 31, 33), (66, 3, 33, 5), (97, 70, 64, 7), (130, 2, 65, 40),
+                                              (200, 2, 97, 16), (145, 2, 127, 31), (131, 3, 128, 65)])
+def test_prepare_device_ex_head_widths_at_the_edges_of_the_register_tiles(d_c, H, d_h, d_side):
+    """Head widths around the multiples of 32 that the inversion's register tiles are made for, row counts outside the
+    window that are no multiple of 16, more heads than workgroups share; zero pivots, so rows have to be taken out of order."""
+    W, Wq, Wo = _weights(d_c, H, d_h, d_side, seed=40 + d_h, weak_first=False)
+    last = d_c - d_h
+    if d_h > 2:
+        W[last, :d_h // 2] = 0.0                      # the last window's first pivot is zero, and no row is its own pivot
+    side, kind = (Wq, oracle.SIDE_Q) if d_h % 2 else (Wo, oracle.SIDE_O)
+    _check_against_oracle(W, d_c, H, d_h, wl.F16, side, kind, oracle.LAST)
