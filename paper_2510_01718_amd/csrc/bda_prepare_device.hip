@@ -1,6 +1,6 @@
 // GPU preparation of one projection (Algorithm "BD Attention Preparation (QK)", Appendix "BD for VO in
 // MHA", Algorithm "BD Decomposition (Row)" for the window choice, Appendix "Residual-Min with Offset
-// Search" for the candidate windows).  Float64 throughout, four kernels:
+// Search" for the candidate windows).  Float64 throughout:
 //   invert_kernel    C_h = W_h[Bbar,:] W_h[B,:]^{-1} for d_h <= 128, one workgroup per head (several when
 //                    there are few heads: each inverts for itself and takes a share of the rows): the
 //                    basis block is inverted in registers by Gauss-Jordan elimination with partial (row)
@@ -8,19 +8,22 @@
 //                    the matrix cores and stored rounded to the requested type;
 //   prepare_wide_kernel   the same for d_h up to 256 with the block in the caller's workspace (the row
 //                    interchanges are undone as column interchanges at the end);
-//   side_kernel      the companion block: W_q^h W_h[B,:]^T or W_h[B,:] W_o^h, rounded the same way;
-//   residual_kernel  the Frobenius reconstruction error of the stored form of one head - what was just
-//                    written to C and to the companion output, read back - as partial sums of squares
-//                    (a fixed number of parts per head, each summed in a fixed order);
+//   strip_kernel     with a companion and d_c up to 512: the companion block, W_q^h W_h[B,:]^T or W_h[B,:] W_o^h,
+//                    rounded the same way, and the Frobenius reconstruction errors of the stored form of one
+//                    head for all candidate windows of the launch, as partial sums of squares (a fixed number
+//                    of parts per head, each summed in a fixed order);
+//   side_kernel, residual_kernel   the same in two steps, one window per launch: wider latents, and errors
+//                    without a companion;
 //   select_kernel    per candidate window the mean over heads of the residuals, the smallest mean
 //                    (earlier candidate on ties, NaN as +inf), the chosen window start.
-// A search runs prepare / side / residual once per candidate window into the caller's outputs, selects,
-// and runs prepare / side once more for the chosen window, whose start it reads from device memory:
-// nothing comes back to the host in between.
+// A search prepares and measures its candidate windows, as many per launch as the caller's outputs can hold
+// stored C's (see Slot), selects, and prepares the chosen window once more, whose start it reads from device
+// memory: nothing comes back to the host in between.
 // The host routine bda_prepare solves with an orthogonal factorisation instead of forming the inverse;
 // the two agree to a small multiple of cond(W_h[B,:]) * 2^-53.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <mutex>
 #include <type_traits>
@@ -92,13 +95,36 @@ struct PrepArgs {
     double* partials;            // workspace: [candidate][head][part] sums of squares, or NULL
     double* mat;                 // workspace: one d_h x d_h block per workgroup of a batch (d_h > 128), or NULL
     int64_t ldw, ld_side, ldC, ld_side_out;
-    int d_c, H, d_h, off, d_side, side_kind;
+    int d_c, H, d_h, d_side, side_kind;
+    int off, off_step, off_last; // candidate window i starts at min(off + i off_step, off_last)
     int h0;                      // first head of this launch (batches when the block lives in the workspace)
-    int cand, n_parts;
+    int cand, n_cand, n_parts;   // first candidate window of this launch and their number
     int w_type, c_type;          // element types of W / side and of C / side_out
+    int write_side, measure;     // strip_kernel: store the companion block / sum the reconstruction errors
 };
 
-__device__ __forceinline__ int window_start(const PrepArgs& a) { return a.off_ptr ? *a.off_ptr : a.off; }
+// Start of window `z` of this launch, or -1.
+__device__ __forceinline__ int window_start(const PrepArgs& a, int z = 0)
+{
+    if (a.off_ptr) return *a.off_ptr;
+    const int o = a.off + (a.cand + z) * a.off_step;
+    return o < a.off_last ? o : a.off_last;
+}
+
+// Where window `z` of a launch keeps its stored C: element (kk, i) of head h at p[o + kk sk + i si + h sh].
+// The first has C itself.  During a search the companion output is free until the chosen window is
+// prepared, and holds the others: K = d_c - d_h of its rows each (Q), or K of its columns, transposed (O).
+struct Slot {
+    void* p;
+    int64_t o, sk, si, sh;
+};
+__device__ __forceinline__ Slot slot_of(const PrepArgs& a, int z)
+{
+    if (z == 0) return {a.C, 0, a.ldC, 1, a.d_h};
+    const int64_t first = (int64_t)(z - 1) * (a.d_c - a.d_h);
+    if (a.side_kind == BDA_SIDE_Q) return {a.side_out, first * a.ld_side_out, a.ld_side_out, 1, a.d_h};
+    return {a.side_out, first, 1, a.ld_side_out, a.d_h * a.ld_side_out};
+}
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
@@ -170,10 +196,11 @@ __global__ __launch_bounds__(kInvertThreads) void invert_kernel(const PrepArgs a
     __shared__ int s_piv[NP], s_pos[NP];
     const int n = a.d_h, t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int h = blockIdx.x;
-    const int off = window_start(a);
+    const int h = blockIdx.x, z = blockIdx.z;
+    const int off = window_start(a, z);
     if (off < 0) return;                       // no usable window was found: nothing to prepare
     const int64_t col0 = (int64_t)h * n;
+    const Slot slot = slot_of(a, z);
     const int tx = t & 31, ty = t >> 5;
 
     double m[NU][NV];
@@ -267,7 +294,7 @@ __global__ __launch_bounds__(kInvertThreads) void invert_kernel(const PrepArgs a
     if (singular) {
         if (t == 0) {
             if (a.status) atomicMax(a.status, h + 1);
-            if (a.cand_singular) a.cand_singular[a.cand] = 1;    // (every writer stores the same value)
+            if (a.cand_singular) a.cand_singular[a.cand + z] = 1;    // (every writer stores the same value)
         }
         return;
     }
@@ -314,7 +341,7 @@ __global__ __launch_bounds__(kInvertThreads) void invert_kernel(const PrepArgs a
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const int row = rt * 16 + 4 * r + g, j = (jt + q) * 16 + c;
-                        if (row < K && j < n) store_rounded<CT>(a.C, (int64_t)row * a.ldC + col0 + j, acc[q][r]);
+                        if (row < K && j < n) store_rounded<CT>(slot.p, slot.o + row * slot.sk + j * slot.si + h * slot.sh, acc[q][r]);
                     }
             });
         }
@@ -647,6 +674,222 @@ __global__ __launch_bounds__(kPrepThreads) void residual_kernel(const PrepArgs a
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Companion block and reconstruction error of the stored form with a companion, d_c up to 512.
+//
+// With S the companion seen as d_side x d_h (W_q^h, or W_o^h transposed) both kinds need P = S W_h^T
+// (d_side x d_c): the companion block of ANY window is columns [off, off + d_h) of P, rounded, and the
+// error matrix is P - [Phat at the window, Phat_window Chat^T outside it].  A workgroup takes 32 rows of P
+// at a time and keeps them while it goes through all candidate windows of the launch: the exact values in
+// the matrix cores' result layout in registers (they are the initial accumulators), the rounded ones in
+// LDS (any window's columns of them are the row operand).  What a window costs is then only its own product
+// 32 x (d_c - d_h) x d_h, whose column operand - the rows of the stored Chat - comes from the L2.
+//
+// 8 waves; wave w owns the 16-column tiles w, w + 8, ... of P, both 16-row tiles of each.  Contraction in
+// blocks of 32: lane group g takes elements 8 g .. 8 g + 7 of a block (one wide load), element s of each
+// group in step s - the same order for both operands, so it is only the order of the sum that changes.
+// Each lane adds its squares in a fixed order, the lanes of a wave, the waves and (in select_kernel) the
+// parts of a head likewise: the result does not depend on scheduling or on how windows are batched.
+// Bound: the double-precision matrix rate.  Against a companion kernel and an error kernel that formed all
+// three products per window in vector FMAs fed from LDS (0.05 + 0.35 ms per window for 16 heads of 128,
+// d_c 512, d_side 2048): a 25-window search of keys and values 27.5 -> 8.2 ms, two windows for 128 heads 5.4 -> 2.2 ms.
+// ---------------------------------------------------------------------------------------------
+constexpr int kStripThreads = 512, kStripRows = 32, kStripMaxDc = 512, kStripTiles = kStripMaxDc / 128;
+
+template <typename T> __device__ __forceinline__ T rounded(double v)
+{
+    T r;
+    store_rounded<T>(&r, 0, v);
+    return r;
+}
+template <typename T> __device__ __forceinline__ double widened(T v) { return load_as_double<T>(&v, 0); }
+
+template <typename T>
+struct Eight {
+    T e[8];
+};
+
+// Eight elements si apart; those from `valid` on are zero.  `vec` (uniform): contiguous, 16-byte aligned, valid
+// either <= 0 or >= 8.
+template <typename T>
+__device__ __forceinline__ Eight<T> fetch8(const T* p, int64_t si, int valid, bool vec)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int Q = (int)sizeof(T) / 2;      // 16-byte pieces
+    u32x4 w[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) w[q] = (u32x4){0, 0, 0, 0};
+    if (vec) {
+        if (valid >= 8) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q) w[q] = ((const u32x4*)p)[q];
+        }
+        return __builtin_bit_cast(Eight<T>, w);
+    }
+    Eight<T> r = __builtin_bit_cast(Eight<T>, w);
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+        if (s < valid) r.e[s] = p[s * si];
+    return r;
+}
+
+__host__ __device__ inline int strip_pitch(int d_c) { return (d_c + 15) / 16 * 16 + 2; }
+inline int strip_lds_bytes(int d_c, int n)
+{
+    const int a = strip_pitch(d_c), b = (n + 31) / 32 * 32 + 2;
+    return kStripRows * (a > b ? a : b) * (int)sizeof(double);
+}
+
+template <typename WT, typename CT>
+__global__ __launch_bounds__(kStripThreads) void strip_kernel(const PrepArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    double* const ph = (double*)smem_raw;      // first the strip of S, then the rounded strip of P
+    __shared__ double s_sum[kStripThreads / 64][kMaxCandidates];
+    const int n = a.d_h, d_c = a.d_c, t = threadIdx.x, lane = t & 63, c = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int h = blockIdx.x;
+    const int off0 = window_start(a);
+    if (off0 < 0) return;
+    const int64_t col0 = (int64_t)h * n;
+    const bool q_side = a.side_kind == BDA_SIDE_Q;
+    const int n_blk = (n + 31) >> 5, npk = n_blk * 32, lds_s = npk + 2, lds_p = strip_pitch(d_c);
+    const int z_lo = a.measure ? (int)((int64_t)a.n_cand * blockIdx.z / gridDim.z) : 0;
+    const int z_hi = a.measure ? (int)((int64_t)a.n_cand * (blockIdx.z + 1) / gridDim.z) : 0;
+    const WT* const W = (const WT*)a.W;
+    const WT* const S = (const WT*)a.side;
+    CT* const side_out = (CT*)a.side_out;
+    const bool w_vec = n % 8 == 0 && (uintptr_t)W % 16 == 0 && (a.ldw * (int64_t)sizeof(WT)) % 16 == 0;
+    for (int z = lane; z < z_hi - z_lo; z += 64) s_sum[wave][z] = 0.0;
+
+    const int n_strips = (a.d_side + kStripRows - 1) / kStripRows;
+    for (int strip = blockIdx.y; strip < n_strips; strip += gridDim.y) {
+        const int s0 = strip * kStripRows;
+        __syncthreads();                       // the strip before is no longer read
+        if (q_side) {
+            for (int e = t; e < kStripRows * npk; e += kStripThreads) {
+                const int r = e / npk, k = e % npk;
+                ph[r * lds_s + k] = (k < n && s0 + r < a.d_side) ? widened<WT>(S[(int64_t)(s0 + r) * a.ld_side + col0 + k]) : 0.0;
+            }
+        } else {
+            for (int e = t; e < kStripRows * npk; e += kStripThreads) {
+                const int r = e % kStripRows, k = e / kStripRows;
+                ph[r * lds_s + k] = (k < n && s0 + r < a.d_side) ? widened<WT>(S[(col0 + k) * a.ld_side + s0 + r]) : 0.0;
+            }
+        }
+        __syncthreads();
+
+        // ---- P: rows s0 .. s0 + 31, this wave's column tiles (without a measurement only those the window meets) ----
+        f64x4 P[kStripTiles][2];
+        bool live[kStripTiles];
+#pragma unroll
+        for (int j = 0; j < kStripTiles; ++j) {
+            P[j][0] = P[j][1] = (f64x4){0.0, 0.0, 0.0, 0.0};
+            const int l0 = (wave + 8 * j) * 16;
+            live[j] = l0 < d_c && (a.measure || (l0 + 16 > off0 && l0 < off0 + n));
+        }
+        for (int b = 0; b < n_blk; ++b) {
+            const int k0 = 32 * b + 8 * g;
+            Eight<WT> w[kStripTiles];
+#pragma unroll
+            for (int j = 0; j < kStripTiles; ++j) {
+                const int l = (wave + 8 * j) * 16 + c;
+                w[j] = fetch8<WT>(W + (int64_t)l * a.ldw + col0 + k0, 1, live[j] && l < d_c ? n - k0 : 0, w_vec);
+            }
+            double av[2][8];
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                for (int s = 0; s < 8; ++s) av[rt][s] = ph[(16 * rt + c) * lds_s + k0 + s];
+#pragma unroll
+            for (int j = 0; j < kStripTiles; ++j)
+                if (live[j]) {
+#pragma unroll
+                    for (int s = 0; s < 8; ++s) {
+                        const double bv = widened<WT>(w[j].e[s]);
+                        P[j][0] = mfma_f64(av[0][s], bv, P[j][0]);
+                        P[j][1] = mfma_f64(av[1][s], bv, P[j][1]);
+                    }
+                }
+        }
+        __syncthreads();                       // the strip of S is no longer read
+#pragma unroll
+        for (int j = 0; j < kStripTiles; ++j) {
+            const int l = (wave + 8 * j) * 16 + c;
+            if (live[j] && l < d_c) {
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) ph[(16 * rt + 4 * r + g) * lds_p + l] = widened<CT>(rounded<CT>(P[j][rt][r]));
+            }
+        }
+        __syncthreads();
+
+        if (a.write_side) {
+            for (int e = t; e < kStripRows * n; e += kStripThreads) {
+                const int r = q_side ? e / n : e % kStripRows, i = q_side ? e % n : e / kStripRows;
+                if (s0 + r < a.d_side) {
+                    const CT v = rounded<CT>(ph[r * lds_p + off0 + i]);
+                    if (q_side) side_out[(int64_t)(s0 + r) * a.ld_side_out + col0 + i] = v;
+                    else side_out[(col0 + i) * a.ld_side_out + s0 + r] = v;
+                }
+            }
+        }
+
+        for (int z = z_lo; z < z_hi; ++z) {
+            const int off = window_start(a, z);
+            const Slot slot = slot_of(a, z);
+            const CT* const chat = (const CT*)slot.p + slot.o + h * slot.sh;
+            const bool c_vec = n % 8 == 0 && slot.si == 1 && (uintptr_t)chat % 16 == 0 && (slot.sk * (int64_t)sizeof(CT)) % 16 == 0;
+            double r2 = 0.0;
+#pragma unroll
+            for (int j = 0; j < kStripTiles; ++j) {
+                const int l0 = (wave + 8 * j) * 16, l = l0 + c;
+                if (l0 >= d_c) continue;
+                const bool in_window = l >= off && l < off + n;
+                f64x4 acc[2] = {-P[j][0], -P[j][1]};
+                if (l0 < off || l0 + 16 > off + n) {
+                    const CT* const row = chat + (int64_t)(l < off ? l : l - n) * slot.sk;
+                    const int cols = l < d_c && !in_window ? n : 0;     // (a lane inside the window adds nothing)
+                    Eight<CT> next = fetch8<CT>(row + (8 * g) * slot.si, slot.si, cols - 8 * g, c_vec);
+                    for (int b = 0; b < n_blk; ++b) {
+                        const int k0 = 32 * b + 8 * g;
+                        const Eight<CT> cur = next;
+                        if (b + 1 < n_blk) next = fetch8<CT>(row + (k0 + 32) * slot.si, slot.si, cols - k0 - 32, c_vec);
+                        double av[2][8];
+#pragma unroll
+                        for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                            for (int s = 0; s < 8; ++s) av[rt][s] = k0 + s < n ? ph[(16 * rt + c) * lds_p + off + k0 + s] : 0.0;
+#pragma unroll
+                        for (int s = 0; s < 8; ++s) {
+                            const double bv = widened<CT>(cur.e[s]);
+                            acc[0] = mfma_f64(av[0][s], bv, acc[0]);
+                            acc[1] = mfma_f64(av[1][s], bv, acc[1]);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        double d = acc[rt][r];
+                        if (in_window) d += ph[(16 * rt + 4 * r + g) * lds_p + l];
+                        r2 = fma(d, d, r2);
+                    }
+            }
+            for (int s = 32; s >= 1; s >>= 1) r2 += __shfl_xor(r2, s, 64);
+            if (lane == 0) s_sum[wave][z - z_lo] += r2;
+        }
+    }
+    __syncthreads();
+    for (int z = z_lo + t; z < z_hi; z += kStripThreads) {
+        double sum = 0.0;
+        for (int w = 0; w < kStripThreads / 64; ++w) sum += s_sum[w][z - z_lo];
+        a.partials[((size_t)(a.cand + z) * a.H + h) * a.n_parts + blockIdx.y] = sum;
+    }
+}
+
 struct SelectArgs {
     double* partials;           // (a head's first part is overwritten with the root of its sum)
     const int* cand_singular;
@@ -713,25 +956,31 @@ int check_launch(const char* what)
     return err == hipSuccess ? BDA_OK : fail(BDA_EHIP, "bda_prepare_device: %s: %s", what, hipGetErrorString(err));
 }
 
+// Raises a kernel's dynamic LDS limit on the current device (once per device; tried again after a failure).
+int raise_lds(const void* kernel, int bytes, LdsLimitState& state)
+{
+    int dev = 0;
+    hipError_t err = hipGetDevice(&dev);
+    if (err != hipSuccess) return fail(BDA_EHIP, "bda_prepare_device: hipGetDevice: %s", hipGetErrorString(err));
+    const bool tracked = dev >= 0 && dev < LdsLimitState::kMaxDevices;
+    if (tracked && state.done[dev].load(std::memory_order_acquire)) return BDA_OK;
+    err = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (err != hipSuccess) return fail(BDA_EHIP, "bda_prepare_device: LDS size %d: %s", bytes, hipGetErrorString(err));
+    if (tracked) state.done[dev].store(true, std::memory_order_release);
+    return BDA_OK;
+}
+
 template <int NB>
 int launch_invert(const PrepArgs& a, hipStream_t st)
 {
     static LdsLimitState once;
-    int dev = 0;
-    hipError_t err = hipGetDevice(&dev);
-    if (err != hipSuccess) return fail(BDA_EHIP, "bda_prepare_device: hipGetDevice: %s", hipGetErrorString(err));
     constexpr int lds = invert_lds_bytes<NB>();
-    const bool tracked = dev >= 0 && dev < LdsLimitState::kMaxDevices;
-    if (!tracked || !once.done[dev].load(std::memory_order_acquire)) {
-        err = hipFuncSetAttribute((const void*)invert_kernel<NB>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (err != hipSuccess) return fail(BDA_EHIP, "bda_prepare_device: LDS size %d: %s", lds, hipGetErrorString(err));
-        if (tracked) once.done[dev].store(true, std::memory_order_release);
-    }
-    // workgroups per head: up to 64 per launch, at most one per row tile
+    if (int rc = raise_lds((const void*)invert_kernel<NB>, lds, once)) return rc;
+    // workgroups per head and window: up to 64 per launch, at most one per row tile
     const int row_tiles = (a.d_c - a.d_h + 15) / 16;
-    int per_head = 64 / a.H;
+    int per_head = 64 / (a.H * a.n_cand);
     per_head = per_head < 1 ? 1 : per_head > row_tiles ? row_tiles : per_head;
-    hipLaunchKernelGGL(invert_kernel<NB>, dim3(a.H, per_head), dim3(kInvertThreads), lds, st, a);
+    hipLaunchKernelGGL(invert_kernel<NB>, dim3(a.H, per_head, a.n_cand), dim3(kInvertThreads), lds, st, a);
     return check_launch("prepare kernel");
 }
 
@@ -751,6 +1000,31 @@ int launch_prepare(PrepArgs a, int batch, hipStream_t st)
         if (int rc = check_launch("prepare kernel")) return rc;
     }
     return BDA_OK;
+}
+
+// Companion block and (a.measure) reconstruction errors of the windows of this launch.
+template <typename WT, typename CT>
+int launch_companion(PrepArgs a, hipStream_t st)
+{
+    const int64_t n_strips = ((int64_t)a.d_side + kStripRows - 1) / kStripRows;
+    if (a.d_c <= kStripMaxDc) {
+        static LdsLimitState once;
+        const int lds = strip_lds_bytes(a.d_c, a.d_h);
+        if (int rc = raise_lds((const void*)strip_kernel<WT, CT>, strip_lds_bytes(kStripMaxDc, kPrepMaxDh), once)) return rc;
+        // a part of a head's error sum is a workgroup; where those leave the chip idle they also share out the windows
+        const int64_t parts = a.measure ? a.n_parts : std::max<int64_t>(1, std::min<int64_t>(n_strips, 2048 / a.H));
+        const int64_t busy = a.H * std::min(n_strips, parts);
+        const int split = a.measure ? (int)std::max<int64_t>(1, std::min<int64_t>(512 / busy, a.n_cand)) : 1;
+        hipLaunchKernelGGL((strip_kernel<WT, CT>), dim3(a.H, (unsigned)parts, split), dim3(kStripThreads), lds, st, a);
+        return check_launch("companion kernel");
+    }
+    // wider latents: their strips do not fit the LDS; one window per launch, the companion block first
+    const int64_t tiles = (((int64_t)a.d_side + 63) / 64) * ((a.d_h + 63) / 64);   // 64 x 64 tiles of the companion block, at most 64 workgroups a head
+    hipLaunchKernelGGL((side_kernel<WT, CT>), dim3(a.H, (unsigned)std::min<int64_t>(tiles, 64)), dim3(kPrepThreads), 0, st, a);
+    if (int rc = check_launch("companion kernel")) return rc;
+    if (!a.measure) return BDA_OK;
+    hipLaunchKernelGGL((residual_kernel<WT, CT>), dim3(a.H, a.n_parts), dim3(kPrepThreads), 0, st, a);
+    return check_launch("residual kernel");
 }
 
 // What a call needs beyond its inputs and outputs, and where it lies in the workspace.
@@ -814,27 +1088,27 @@ int run_prepare(const PrepCall& c, const Plan& p, unsigned char* ws, hipStream_t
     a.d_c = c.d_c; a.H = c.H; a.d_h = c.d_h; a.d_side = c.d_side; a.side_kind = c.side_kind;
     a.n_parts = p.n_parts;
     a.w_type = c.w_dtype; a.c_type = c.c_dtype;
-    const bool multi = p.n_cand > 1;
-    int side_parts = 1;                      // workgroups per head of the companion kernel: its 64 x 64 tiles, at most 64
-    if (c.side_kind != BDA_SIDE_NONE) {
-        const int64_t tiles = (int64_t)((c.d_side + 63) / 64) * ((c.d_h + 63) / 64);
-        side_parts = (int)(tiles < 64 ? tiles : 64);
-    }
+    const bool multi = p.n_cand > 1, companion = c.side_kind != BDA_SIDE_NONE;
     if (ws) {
         hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(kMaxCandidates), 0, st, flags, kMaxCandidates, 0);
         if (int rc = check_launch("fill kernel")) return rc;
     }
-    for (int ci = 0; ci < p.n_cand; ++ci) {
-        a.off = p.offs[ci];
-        a.off_ptr = nullptr;
+    a.off = p.offs[0];
+    a.off_step = multi ? p.offs[1] - p.offs[0] : 0;
+    a.off_last = p.offs[p.n_cand - 1];
+    a.status = multi ? nullptr : c.singular_head;          // during a search a singular window is just a bad candidate
+    a.measure = p.want_resid;
+    // Candidate windows that one launch prepares and measures: as many stored C's as the outputs have room for
+    // until the chosen window is known.
+    const int slots = multi && companion && !p.big && c.d_c <= kStripMaxDc ? 1 + c.d_side / (c.d_c - c.d_h) : 1;
+    for (int ci = 0; ci < p.n_cand; ci += slots) {
         a.cand = ci;
-        a.status = multi ? nullptr : c.singular_head;      // during a search a singular window is just a bad candidate
+        a.n_cand = std::min(slots, p.n_cand - ci);
+        a.write_side = !multi;
         if (int rc = launch_prepare<WT, CT>(a, p.batch, st)) return rc;
-        if (c.side_kind != BDA_SIDE_NONE) {
-            hipLaunchKernelGGL((side_kernel<WT, CT>), dim3(c.H, side_parts), dim3(kPrepThreads), 0, st, a);
-            if (int rc = check_launch("companion kernel")) return rc;
-        }
-        if (p.want_resid) {
+        if (companion) {
+            if (int rc = launch_companion<WT, CT>(a, st)) return rc;
+        } else if (p.want_resid) {
             hipLaunchKernelGGL((residual_kernel<WT, CT>), dim3(c.H, p.n_parts), dim3(kPrepThreads), 0, st, a);
             if (int rc = check_launch("residual kernel")) return rc;
         }
@@ -852,16 +1126,15 @@ int run_prepare(const PrepCall& c, const Plan& p, unsigned char* ws, hipStream_t
     }
     if (multi) {
         // the chosen window once more, into the outputs for good (its start is read on the device)
-        a.off = -1;
         a.off_ptr = c.basis_offset_out;
         a.cand = 0;
+        a.n_cand = 1;
         a.cand_singular = nullptr;
         a.status = c.singular_head;
+        a.measure = 0;
+        a.write_side = 1;
         if (int rc = launch_prepare<WT, CT>(a, p.batch, st)) return rc;
-        if (c.side_kind != BDA_SIDE_NONE) {
-            hipLaunchKernelGGL((side_kernel<WT, CT>), dim3(c.H, side_parts), dim3(kPrepThreads), 0, st, a);
-            if (int rc = check_launch("companion kernel")) return rc;
-        }
+        if (companion) return launch_companion<WT, CT>(a, st);
     }
     return BDA_OK;
 }

@@ -196,3 +196,17 @@ def test_prepare_device_ex_head_widths_at_the_edges_of_the_register_tiles(d_c, H
         W[last, :d_h // 2] = 0.0                      # the last window's first pivot is zero, and no row is its own pivot
     side, kind = (Wq, oracle.SIDE_Q) if d_h % 2 else (Wo, oracle.SIDE_O)
     _check_against_oracle(W, d_c, H, d_h, wl.F16, side, kind, oracle.LAST)
+
+
+@pytest.mark.parametrize("d_c,H,d_h,d_side,side_kind,store,mode", [
+    (80, 2, 33, 30, oracle.SIDE_Q, wl.F16, oracle.OFFSET_SEARCH),      # one window per launch, columns read one by one
+    (80, 2, 33, 150, oracle.SIDE_O, wl.BF16, oracle.OFFSET_SEARCH),    # four per launch, the last with one; last window off the grid of 16
+    (512, 1, 128, 1000, oracle.SIDE_Q, wl.F32, oracle.RESIDUAL_MIN),   # largest strip, rows that end inside one
+    (496, 3, 96, 405, oracle.SIDE_O, wl.F16, oracle.OFFSET_SEARCH),    # second window of a launch fills the companion output to its edge
+    (513, 1, 96, 70, oracle.SIDE_Q, wl.F16, oracle.RESIDUAL_MIN),      # just past the strips
+    (64, 40, 16, 33, oracle.SIDE_Q, wl.BF16, oracle.RESIDUAL_MIN)])
+def test_prepare_device_ex_windows_prepared_together(d_c, H, d_h, d_side, side_kind, store, mode):
+    """Several candidate windows in one launch, their stored C's in the companion output meanwhile: strips, column
+    tiles and windows that end on and off the kernels' tile sizes."""
+    W, Wq, Wo = _weights(d_c, H, d_h, d_side, seed=60 + d_c + d_side)
+    _check_against_oracle(W, d_c, H, d_h, store, Wq if side_kind == oracle.SIDE_Q else Wo, side_kind, mode)
