@@ -100,6 +100,8 @@ struct PrepArgs {
     int h0;                      // first head of this launch (batches when the block lives in the workspace)
     int cand, n_cand, n_parts;   // first candidate window of this launch and their number
     int w_type, c_type;          // element types of W / side and of C / side_out
+    int per_row;                 // O: pieces of d_h columns in a row of the companion output (see Slot)
+    uint32_t per_row_magic;
     int write_side, measure;     // strip_kernel: store the companion block / sum the reconstruction errors
 };
 
@@ -111,19 +113,28 @@ __device__ __forceinline__ int window_start(const PrepArgs& a, int z = 0)
     return o < a.off_last ? o : a.off_last;
 }
 
-// Where window `z` of a launch keeps its stored C: element (kk, i) of head h at p[o + kk sk + i si + h sh].
-// The first has C itself.  During a search the companion output is free until the chosen window is
-// prepared, and holds the others: K = d_c - d_h of its rows each (Q), or K of its columns, transposed (O).
+// Where window `z` of a launch keeps its stored C: row kk of head h, d_h contiguous elements, begins at element
+// slot_row() of the array.  The first window has C itself.  During a search the companion output is free until
+// the chosen window is prepared, and holds the others: d_c - d_h of its rows each (Q: the layout of C), or as
+// many pieces of d_h columns of the head's own d_h rows, a.per_row of them in a row (O).
 struct Slot {
     void* p;
-    int64_t o, sk, si, sh;
+    int64_t ld;
+    int first, per_row;          // pieces before this window's; 0: rows of C's layout
+    uint32_t magic;              // ceil(2^32 / per_row)
 };
 __device__ __forceinline__ Slot slot_of(const PrepArgs& a, int z)
 {
-    if (z == 0) return {a.C, 0, a.ldC, 1, a.d_h};
-    const int64_t first = (int64_t)(z - 1) * (a.d_c - a.d_h);
-    if (a.side_kind == BDA_SIDE_Q) return {a.side_out, first * a.ld_side_out, a.ld_side_out, 1, a.d_h};
-    return {a.side_out, first, 1, a.ld_side_out, a.d_h * a.ld_side_out};
+    const int first = (z - 1) * (a.d_c - a.d_h);
+    if (z == 0) return {a.C, a.ldC, 0, 0, 0};
+    return {a.side_out, a.ld_side_out, first, a.per_row, a.per_row_magic};
+}
+__device__ __forceinline__ int64_t slot_row(const Slot& s, int kk, int h, int n)
+{
+    const int q = s.first + kk;
+    if (!s.per_row) return q * s.ld + (int64_t)h * n;
+    const int row = s.per_row == 1 ? q : (int)__umulhi((uint32_t)q, s.magic);
+    return ((int64_t)h * n + row) * s.ld + (q - row * s.per_row) * n;
 }
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -176,18 +187,19 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
 // The product runs on v_mfma_f64_16x16x4: a wave takes 16 rows of W_h[Bbar,:] straight from memory into
 // registers (they are its A operand) against the inverse in LDS, whose pitch of 16 mod 32 doubles lets the
 // two k rows that one half of a wave reads fall into different halves of the banks.
+// (256 threads: 0.21 ms against 0.17 in a search's launches.)
 // Bound: the elimination's serial chain (128 steps), then the double-precision matrix rate.  A version that
 // kept the block in LDS and rewrote all of it in every step, with the product in vector FMAs, took 0.62 ms
 // for 16 heads of 128 and 0.88 ms for 128; this one about 0.15 ms (a layer's two 25-window searches with
 // companions: 52.1 -> 27.5 ms).
-constexpr int kInvertThreads = 512;
+constexpr int kInvertThreads = 512, kInvertRows = kInvertThreads / 32;
 template <int NB>
 constexpr int invert_lds_bytes() { return 32 * NB * (32 * NB + 16) * (int)sizeof(double); }
 
 template <int NB>
 __global__ __launch_bounds__(kInvertThreads) void invert_kernel(const PrepArgs a)
 {
-    constexpr int NP = 32 * NB, NU = 2 * NB, NV = NB, LD = NP + 16;
+    constexpr int NP = 32 * NB, NU = NP / kInvertRows, NV = NB, LD = NP + 16;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     double* const inv = (double*)smem_raw;
     __shared__ double s_col[2][NP];
@@ -211,7 +223,7 @@ __global__ __launch_bounds__(kInvertThreads) void invert_kernel(const PrepArgs a
         for (int u = 0; u < NU; ++u)
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
-                const int i = ty + 16 * u, j = tx + 32 * v;
+                const int i = ty + kInvertRows * u, j = tx + 32 * v;
                 m[u][v] = (i < n && j < n) ? load_as_double<WT>(a.W, (int64_t)(off + i) * a.ldw + col0 + j) : 0.0;
             }
     });
@@ -235,25 +247,27 @@ __global__ __launch_bounds__(kInvertThreads) void invert_kernel(const PrepArgs a
             double* const col = s_col[k & 1];
             if (tx == kk) {
 #pragma unroll
-                for (int u = 0; u < NU; ++u) col[ty + 16 * u] = m[u][kv];
+                for (int u = 0; u < NU; ++u) col[ty + kInvertRows * u] = m[u][kv];
             }
             __syncthreads();
             uint32_t key = 0;
-            if (lane < n && !((used_lo >> lane) & 1)) {
-                const uint64_t b = __builtin_bit_cast(uint64_t, col[lane]);
-                key = ((uint32_t)(b >> 32) & 0x7fffff80u) | (uint32_t)(127 - lane);
-            }
+            const uint64_t lo = __builtin_bit_cast(uint64_t, col[NP > 32 ? lane : lane & 31]);
+            const uint64_t hi = NP > 64 ? __builtin_bit_cast(uint64_t, col[NP > 96 ? lane + 64 : 64 + (lane & 31)]) : lo;
+            if (lane < n && !((used_lo >> lane) & 1)) key = ((uint32_t)(lo >> 32) & 0x7fffff80u) | (uint32_t)(127 - lane);
             if constexpr (NP > 64) {
                 if (lane + 64 < n && !((used_hi >> lane) & 1)) {
-                    const uint64_t b = __builtin_bit_cast(uint64_t, col[lane + 64]);
-                    const uint32_t key2 = ((uint32_t)(b >> 32) & 0x7fffff80u) | (uint32_t)(63 - lane);
+                    const uint32_t key2 = ((uint32_t)(hi >> 32) & 0x7fffff80u) | (uint32_t)(63 - lane);
                     key = key2 > key ? key2 : key;
                 }
             }
             const int p = 127 - (int)(wave_max_u32(key) & 127u);       // uniform: the pivot row (< n: some row is unused)
-            const double pv = col[p];
+            // (the pivot itself is in a lane's registers already)
+            const uint64_t pb = p < 64 ? lo : hi;
+            const uint32_t pb_lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)pb, p & 63);
+            const uint32_t pb_hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(pb >> 32), p & 63);
+            const double pv = __builtin_bit_cast(double, (uint64_t)pb_hi << 32 | pb_lo);
             if (!(fabs(pv) > tiny)) { singular = true; break; }
-            const int pu = p >> 4, pt = p & 15;
+            const int pu = p / kInvertRows, pt = p % kInvertRows;
             if (ty == pt) {
 #pragma unroll
                 for (int u = 0; u < NU; ++u)
@@ -267,7 +281,7 @@ __global__ __launch_bounds__(kInvertThreads) void invert_kernel(const PrepArgs a
             const double ip = 1.0 / pv;
             double f[NU];
 #pragma unroll
-            for (int u = 0; u < NU; ++u) f[u] = col[ty + 16 * u];
+            for (int u = 0; u < NU; ++u) f[u] = col[ty + kInvertRows * u];
             __syncthreads();
             double r[NV];
 #pragma unroll
@@ -304,7 +318,7 @@ __global__ __launch_bounds__(kInvertThreads) void invert_kernel(const PrepArgs a
     for (int u = 0; u < NU; ++u)
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-            const int i = ty + 16 * u, j = tx + 32 * v;
+            const int i = ty + kInvertRows * u, j = tx + 32 * v;
             const bool in = i < n && j < n;
             inv[(i < n ? s_pos[i] : i) * LD + (j < n ? s_piv[j] : j)] = in ? m[u][v] : 0.0;
         }
@@ -326,7 +340,7 @@ __global__ __launch_bounds__(kInvertThreads) void invert_kernel(const PrepArgs a
             }
         });
 #pragma unroll 1
-        for (int jt = 0; jt < NU; jt += 2) {
+        for (int jt = 0; jt < 2 * NB; jt += 2) {
             f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
 #pragma unroll
             for (int ks = 0; ks < 8 * NB; ++ks) {
@@ -341,7 +355,7 @@ __global__ __launch_bounds__(kInvertThreads) void invert_kernel(const PrepArgs a
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const int row = rt * 16 + 4 * r + g, j = (jt + q) * 16 + c;
-                        if (row < K && j < n) store_rounded<CT>(slot.p, slot.o + row * slot.sk + j * slot.si + h * slot.sh, acc[q][r]);
+                        if (row < K && j < n) store_rounded<CT>(slot.p, slot_row(slot, row, h, n) + j, acc[q][r]);
                     }
             });
         }
@@ -692,7 +706,8 @@ __global__ __launch_bounds__(kPrepThreads) void residual_kernel(const PrepArgs a
 // parts of a head likewise: the result does not depend on scheduling or on how windows are batched.
 // Bound: the double-precision matrix rate.  Against a companion kernel and an error kernel that formed all
 // three products per window in vector FMAs fed from LDS (0.05 + 0.35 ms per window for 16 heads of 128,
-// d_c 512, d_side 2048): a 25-window search of keys and values 27.5 -> 8.2 ms, two windows for 128 heads 5.4 -> 2.2 ms.
+// d_c 512, d_side 2048): a 25-window search of keys and values 27.5 -> 8.2 ms, two windows for 128 heads 5.4 -> 2.2 ms; with a block's row operand read once for all tiles, the column operands
+// fetched a block ahead and contiguous for W_o too, 7.0 ms (46 TFLOP/s while a window is measured).
 // ---------------------------------------------------------------------------------------------
 constexpr int kStripThreads = 512, kStripRows = 32, kStripMaxDc = 512, kStripTiles = kStripMaxDc / 128;
 
@@ -709,10 +724,9 @@ struct Eight {
     T e[8];
 };
 
-// Eight elements si apart; those from `valid` on are zero.  `vec` (uniform): contiguous, 16-byte aligned, valid
-// either <= 0 or >= 8.
+// Eight elements; those from `valid` on are zero.  `vec` (uniform): 16-byte aligned, valid either <= 0 or >= 8.
 template <typename T>
-__device__ __forceinline__ Eight<T> fetch8(const T* p, int64_t si, int valid, bool vec)
+__device__ __forceinline__ Eight<T> fetch8(const T* p, int valid, bool vec)
 {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     constexpr int Q = (int)sizeof(T) / 2;      // 16-byte pieces
@@ -729,7 +743,7 @@ __device__ __forceinline__ Eight<T> fetch8(const T* p, int64_t si, int valid, bo
     Eight<T> r = __builtin_bit_cast(Eight<T>, w);
 #pragma unroll
     for (int s = 0; s < 8; ++s)
-        if (s < valid) r.e[s] = p[s * si];
+        if (s < valid) r.e[s] = p[s];
     return r;
 }
 
@@ -767,15 +781,15 @@ __global__ __launch_bounds__(kStripThreads) void strip_kernel(const PrepArgs a)
         const int s0 = strip * kStripRows;
         __syncthreads();                       // the strip before is no longer read
         if (q_side) {
-            for (int e = t; e < kStripRows * npk; e += kStripThreads) {
-                const int r = e / npk, k = e % npk;
-                ph[r * lds_s + k] = (k < n && s0 + r < a.d_side) ? widened<WT>(S[(int64_t)(s0 + r) * a.ld_side + col0 + k]) : 0.0;
-            }
+            for (int k = lane; k < npk; k += 64)
+#pragma unroll
+                for (int r = wave; r < kStripRows; r += 8)
+                    ph[r * lds_s + k] = (k < n && s0 + r < a.d_side) ? widened<WT>(S[(int64_t)(s0 + r) * a.ld_side + col0 + k]) : 0.0;
         } else {
-            for (int e = t; e < kStripRows * npk; e += kStripThreads) {
-                const int r = e % kStripRows, k = e / kStripRows;
+            const int r = t % kStripRows;
+#pragma unroll 4
+            for (int k = t / kStripRows; k < npk; k += kStripThreads / kStripRows)
                 ph[r * lds_s + k] = (k < n && s0 + r < a.d_side) ? widened<WT>(S[(col0 + k) * a.ld_side + s0 + r]) : 0.0;
-            }
         }
         __syncthreads();
 
@@ -788,14 +802,23 @@ __global__ __launch_bounds__(kStripThreads) void strip_kernel(const PrepArgs a)
             const int l0 = (wave + 8 * j) * 16;
             live[j] = l0 < d_c && (a.measure || (l0 + 16 > off0 && l0 < off0 + n));
         }
-        for (int b = 0; b < n_blk; ++b) {
-            const int k0 = 32 * b + 8 * g;
-            Eight<WT> w[kStripTiles];
+        Eight<WT> w[kStripTiles];
+        auto fetch_w = [&](int b) {
 #pragma unroll
             for (int j = 0; j < kStripTiles; ++j) {
-                const int l = (wave + 8 * j) * 16 + c;
-                w[j] = fetch8<WT>(W + (int64_t)l * a.ldw + col0 + k0, 1, live[j] && l < d_c ? n - k0 : 0, w_vec);
+                const int l = (wave + 8 * j) * 16 + c, k0 = 32 * b + 8 * g;
+                w[j] = fetch8<WT>(W + (int64_t)l * a.ldw + col0 + k0, live[j] && l < d_c ? n - k0 : 0, w_vec);
             }
+        };
+        constexpr bool kAheadW = sizeof(WT) <= 4, kAheadC = sizeof(CT) <= 2;   // (as far as the registers go)
+        if (kAheadW) fetch_w(0);
+        for (int b = 0; b < n_blk; ++b) {
+            const int k0 = 32 * b + 8 * g;
+            if (!kAheadW) fetch_w(b);
+            Eight<WT> now[kStripTiles];
+#pragma unroll
+            for (int j = 0; j < kStripTiles; ++j) now[j] = w[j];
+            if (kAheadW && b + 1 < n_blk) fetch_w(b + 1);
             double av[2][8];
 #pragma unroll
             for (int rt = 0; rt < 2; ++rt)
@@ -806,7 +829,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_kernel(const PrepArgs a)
                 if (live[j]) {
 #pragma unroll
                     for (int s = 0; s < 8; ++s) {
-                        const double bv = widened<WT>(w[j].e[s]);
+                        const double bv = widened<WT>(now[j].e[s]);
                         P[j][0] = mfma_f64(av[0][s], bv, P[j][0]);
                         P[j][1] = mfma_f64(av[1][s], bv, P[j][1]);
                     }
@@ -836,44 +859,67 @@ __global__ __launch_bounds__(kStripThreads) void strip_kernel(const PrepArgs a)
             }
         }
 
-        for (int z = z_lo; z < z_hi; ++z) {
-            const int off = window_start(a, z);
+        // ---- the windows: blocks of the contraction outside, this wave's tiles inside, so that a block's row operand is
+        // read once for all of them; the column operands are fetched one block ahead, across windows ----
+        Eight<CT> ct[kStripTiles];
+        auto fetch_c = [&](int z, int b) {
+            const int off = window_start(a, z), k0 = 32 * b + 8 * g;
             const Slot slot = slot_of(a, z);
-            const CT* const chat = (const CT*)slot.p + slot.o + h * slot.sh;
-            const bool c_vec = n % 8 == 0 && slot.si == 1 && (uintptr_t)chat % 16 == 0 && (slot.sk * (int64_t)sizeof(CT)) % 16 == 0;
-            double r2 = 0.0;
+            const bool c_vec = n % 8 == 0 && (uintptr_t)slot.p % 16 == 0 && (slot.ld * (int64_t)sizeof(CT)) % 16 == 0;
 #pragma unroll
             for (int j = 0; j < kStripTiles; ++j) {
-                const int l0 = (wave + 8 * j) * 16, l = l0 + c;
-                if (l0 >= d_c) continue;
-                const bool in_window = l >= off && l < off + n;
-                f64x4 acc[2] = {-P[j][0], -P[j][1]};
-                if (l0 < off || l0 + 16 > off + n) {
-                    const CT* const row = chat + (int64_t)(l < off ? l : l - n) * slot.sk;
-                    const int cols = l < d_c && !in_window ? n : 0;     // (a lane inside the window adds nothing)
-                    Eight<CT> next = fetch8<CT>(row + (8 * g) * slot.si, slot.si, cols - 8 * g, c_vec);
-                    for (int b = 0; b < n_blk; ++b) {
-                        const int k0 = 32 * b + 8 * g;
-                        const Eight<CT> cur = next;
-                        if (b + 1 < n_blk) next = fetch8<CT>(row + (k0 + 32) * slot.si, slot.si, cols - k0 - 32, c_vec);
-                        double av[2][8];
+                const int l = (wave + 8 * j) * 16 + c;
+                const bool outside = l < d_c && (l < off || l >= off + n);      // (a lane inside the window adds nothing)
+                ct[j] = fetch8<CT>((const CT*)slot.p + slot_row(slot, l < off ? l : l - n, h, n) + k0, outside ? n - k0 : 0, c_vec);
+            }
+        };
+        if (kAheadC && z_lo < z_hi) fetch_c(z_lo, 0);
+        for (int z = z_lo; z < z_hi; ++z) {
+            const int off = window_start(a, z);
+            f64x4 acc[kStripTiles][2];
 #pragma unroll
-                        for (int rt = 0; rt < 2; ++rt)
+            for (int j = 0; j < kStripTiles; ++j) { acc[j][0] = -P[j][0]; acc[j][1] = -P[j][1]; }
+            for (int b = 0; b < n_blk; ++b) {
+                const int k0 = 32 * b + 8 * g;
+                if (!kAheadC) fetch_c(z, b);
+                Eight<CT> now[kStripTiles];
 #pragma unroll
-                            for (int s = 0; s < 8; ++s) av[rt][s] = k0 + s < n ? ph[(16 * rt + c) * lds_p + off + k0 + s] : 0.0;
+                for (int j = 0; j < kStripTiles; ++j) now[j] = ct[j];
+                if (kAheadC) {
+                    if (b + 1 < n_blk) fetch_c(z, b + 1);
+                    else if (z + 1 < z_hi) fetch_c(z + 1, 0);
+                }
 #pragma unroll
-                        for (int s = 0; s < 8; ++s) {
-                            const double bv = widened<CT>(cur.e[s]);
-                            acc[0] = mfma_f64(av[0][s], bv, acc[0]);
-                            acc[1] = mfma_f64(av[1][s], bv, acc[1]);
+                for (int half = 0; half < 8; half += 4) {
+                    double av[2][4];
+#pragma unroll
+                    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) av[rt][s] = k0 + half + s < n ? ph[(16 * rt + c) * lds_p + off + k0 + half + s] : 0.0;
+#pragma unroll
+                    for (int j = 0; j < kStripTiles; ++j) {
+                        const int l0 = (wave + 8 * j) * 16;
+                        if (l0 < d_c && (l0 < off || l0 + 16 > off + n)) {
+#pragma unroll
+                            for (int s = 0; s < 4; ++s) {
+                                const double bv = widened<CT>(now[j].e[half + s]);
+                                acc[j][0] = mfma_f64(av[0][s], bv, acc[j][0]);
+                                acc[j][1] = mfma_f64(av[1][s], bv, acc[j][1]);
+                            }
                         }
                     }
                 }
+            }
+            double r2 = 0.0;
+#pragma unroll
+            for (int j = 0; j < kStripTiles; ++j) {
+                const int l = (wave + 8 * j) * 16 + c;
+                const bool in_window = l >= off && l < off + n;
 #pragma unroll
                 for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        double d = acc[rt][r];
+                        double d = acc[j][rt][r];
                         if (in_window) d += ph[(16 * rt + 4 * r + g) * lds_p + l];
                         r2 = fma(d, d, r2);
                     }
@@ -976,9 +1022,9 @@ int launch_invert(const PrepArgs& a, hipStream_t st)
     static LdsLimitState once;
     constexpr int lds = invert_lds_bytes<NB>();
     if (int rc = raise_lds((const void*)invert_kernel<NB>, lds, once)) return rc;
-    // workgroups per head and window: up to 64 per launch, at most one per row tile
+    // workgroups per head and window: up to one per compute unit, at most one per row tile
     const int row_tiles = (a.d_c - a.d_h + 15) / 16;
-    int per_head = 64 / (a.H * a.n_cand);
+    int per_head = 256 / (a.H * a.n_cand);
     per_head = per_head < 1 ? 1 : per_head > row_tiles ? row_tiles : per_head;
     hipLaunchKernelGGL(invert_kernel<NB>, dim3(a.H, per_head, a.n_cand), dim3(kInvertThreads), lds, st, a);
     return check_launch("prepare kernel");
@@ -1100,7 +1146,17 @@ int run_prepare(const PrepCall& c, const Plan& p, unsigned char* ws, hipStream_t
     a.measure = p.want_resid;
     // Candidate windows that one launch prepares and measures: as many stored C's as the outputs have room for
     // until the chosen window is known.
-    const int slots = multi && companion && !p.big && c.d_c <= kStripMaxDc ? 1 + c.d_side / (c.d_c - c.d_h) : 1;
+    int slots = 1;
+    if (multi && companion && !p.big && c.d_c <= kStripMaxDc) {
+        const int K = c.d_c - c.d_h;
+        if (c.side_kind == BDA_SIDE_O) {
+            a.per_row = std::min(c.d_side / c.d_h, 1024);
+            a.per_row_magic = a.per_row > 1 ? (uint32_t)((((uint64_t)1 << 32) + a.per_row - 1) / a.per_row) : 0;
+            slots += c.d_h * a.per_row / K;
+        } else {
+            slots += c.d_side / K;
+        }
+    }
     for (int ci = 0; ci < p.n_cand; ci += slots) {
         a.cand = ci;
         a.n_cand = std::min(slots, p.n_cand - ci);
