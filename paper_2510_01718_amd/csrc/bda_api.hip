@@ -9,6 +9,7 @@
 #include "bda_gemm_stream.hpp"
 #include "bda_gemm_plain.hpp"
 #include "bda_gemm_duo.hpp"
+#include "bda_gemm_f32.hpp"
 #include "bda_internal.h"
 
 namespace bda {
@@ -251,13 +252,29 @@ int launch_decode(GemmArgs& a, hipStream_t st)
     return launch_decode_blocks<X, OutT, 4, false>(a, st);
 }
 
-template <typename InT, typename OutT>
-int launch_general(GemmArgs& a, int64_t N_total, hipStream_t st)
+int run_general(GemmArgs& a, int G, const int64_t* group_cols, int dtype, int out_dtype, hipStream_t st)
 {
-    if (plan_only(a, BDA_KERNEL_GENERAL, 64, 64, a.n_tiles * a.m_tiles, 256, 2 * 16 * 65 * 4, 1)) return BDA_OK;
-    hipLaunchKernelGGL((gemm_general_kernel<InT, OutT>), dim3(a.n_tiles, a.m_tiles), dim3(256), 0, st, a, N_total);
-    hipError_t err = hipGetLastError();
-    return err == hipSuccess ? BDA_OK : fail(BDA_EHIP, "kernel launch: %s", hipGetErrorString(err));
+    GeneralArgs p{};
+    p.tok = a.A; p.wgt = a.B; p.out = a.D;
+    p.ld_tok = a.lda; p.ld_wgt = a.ldb; p.ld_out = a.ldd;
+    p.rows = a.M; p.len = a.K;
+    p.d_c = a.K + a.a_skip; p.d_h = a.d_h; p.skip = a.a_skip; p.ident = a.ident;
+    p.n_groups = G;
+    for (int g = 0; g < G; ++g) {
+        p.col_start[g + 1] = p.col_start[g] + group_cols[g];
+        p.off[g] = a.a_off[g];
+    }
+    return launch_general<Product::Forward>(p, group_cols, G, dtype, out_dtype, [&](auto kern, int threads, int lds, LdsLimitState& once, int tile) {
+        a.m_tiles = p.m_tiles;
+        a.n_tiles = p.n_tiles;
+        a.sm = a.sn = 1;
+        a.lin_slots = 0;
+        if (plan_only(a, BDA_KERNEL_GENERAL, kGeneralBT[tile], kGeneralBN[tile], a.n_tiles * a.m_tiles, threads, lds, 1)) return (int)BDA_OK;
+        if (int rc = set_max_lds(kern, lds, once)) return rc;
+        hipLaunchKernelGGL(kern, general_grid(p), dim3(threads), lds, st, p);
+        hipError_t err = hipGetLastError();
+        return err == hipSuccess ? (int)BDA_OK : fail(BDA_EHIP, "kernel launch: %s", hipGetErrorString(err));
+    });
 }
 
 // Fills the per-group tile tables for column tiles of width bn and token tiles of height bt.
@@ -460,15 +477,7 @@ int run_gemm(GemmArgs& a, int G, const int64_t* group_cols, int dtype, int out_d
 #undef BDA_LAUNCH
         return fail(BDA_EDTYPE, "unsupported dtype/out_dtype pair %d/%d", dtype, out_dtype);
     }
-    build_tiles(a, G, group_cols, 64, 64);
-    a.sm = a.sn = 1;
-    if (a.m_tiles > 65535) return fail(BDA_EINVAL, "general kernel: T too large (%lld)", (long long)a.M);
-    if (dtype == BDA_F32 && out_dtype == BDA_F32) return launch_general<float, float>(a, N_total, st);
-    if (dtype == BDA_F16 && out_dtype == BDA_F16) return launch_general<RawF16, RawF16>(a, N_total, st);
-    if (dtype == BDA_F16 && out_dtype == BDA_F32) return launch_general<RawF16, float>(a, N_total, st);
-    if (dtype == BDA_BF16 && out_dtype == BDA_BF16) return launch_general<RawBF16, RawBF16>(a, N_total, st);
-    if (dtype == BDA_BF16 && out_dtype == BDA_F32) return launch_general<RawBF16, float>(a, N_total, st);
-    return fail(BDA_EDTYPE, "unsupported dtype/out_dtype pair %d/%d", dtype, out_dtype);
+    return run_general(a, G, group_cols, dtype, out_dtype, st);
 }
 
 int check_dtypes(const char* fn, int dtype, int out_dtype)

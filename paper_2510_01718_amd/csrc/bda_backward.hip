@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include "bda_bwd_kernels.hpp"
+#include "bda_gemm_f32.hpp"
 #include "bda_internal.h"
 
 namespace bda {
@@ -76,24 +77,14 @@ int launch_fast(BwdArgs& a, int64_t rows, const int64_t* group_cols, int G, int 
     return fail(BDA_EDTYPE, "unsupported dtype/grad_dtype pair %d/%d", dtype, out_dtype);
 }
 
-template <typename InT, typename OutT, bool WEIGHT>
-int launch_general_typed(const BwdArgs& a, hipStream_t st)
+template <Product P>
+int run_general(GeneralArgs& p, const int64_t* out_cols, int G, int dtype, int out_dtype, hipStream_t st)
 {
-    if constexpr (WEIGHT) hipLaunchKernelGGL((bwd_weight_general_kernel<InT, OutT>), dim3(a.n_tiles, a.m_tiles), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((bwd_latent_general_kernel<InT, OutT>), dim3(a.n_tiles, a.m_tiles), dim3(256), 0, st, a);
-    return launched();
-}
-
-template <bool WEIGHT>
-int launch_general(const BwdArgs& a, int dtype, int out_dtype, hipStream_t st)
-{
-    if (a.m_tiles > 65535) return fail(BDA_EINVAL, "general kernel: too many row tiles (%d)", a.m_tiles);
-    if (dtype == BDA_F32 && out_dtype == BDA_F32) return launch_general_typed<float, float, WEIGHT>(a, st);
-    if (dtype == BDA_F16 && out_dtype == BDA_F16) return launch_general_typed<RawF16, RawF16, WEIGHT>(a, st);
-    if (dtype == BDA_F16 && out_dtype == BDA_F32) return launch_general_typed<RawF16, float, WEIGHT>(a, st);
-    if (dtype == BDA_BF16 && out_dtype == BDA_BF16) return launch_general_typed<RawBF16, RawBF16, WEIGHT>(a, st);
-    if (dtype == BDA_BF16 && out_dtype == BDA_F32) return launch_general_typed<RawBF16, float, WEIGHT>(a, st);
-    return fail(BDA_EDTYPE, "unsupported dtype/grad_dtype pair %d/%d", dtype, out_dtype);
+    return launch_general<P>(p, out_cols, G, dtype, out_dtype, [&](auto kern, int threads, int lds, LdsLimitState& once, int) {
+        if (int rc = allow_lds(kern, lds, once)) return rc;
+        hipLaunchKernelGGL(kern, general_grid(p), dim3(threads), lds, st, p);
+        return launched();
+    });
 }
 
 }  // namespace
@@ -160,6 +151,12 @@ extern "C" int bda_kv_project_backward(const void* c, int64_t ldc, const void* d
         a.a_off[g] = basis_offset[g];
     }
     hipStream_t st = (hipStream_t)stream;
+    GeneralArgs p{};
+    p.d_c = d_c; p.d_h = d_h; p.n_groups = G;
+    for (int g = 0; g < G; ++g) {
+        p.col_start[g + 1] = a.col_start[g + 1];
+        p.off[g] = basis_offset[g];
+    }
 
     const int64_t max_ld = (int64_t)1 << 21;   // 32-bit buffer offsets inside one tile
     bool fast = (dtype == BDA_F16 || dtype == BDA_BF16) && aligned(d_out, 16) && ld_dout % 8 == 0 && ld_dout < max_ld &&
@@ -171,13 +168,14 @@ extern "C" int bda_kv_project_backward(const void* c, int64_t ldc, const void* d
         const bool f = fast && aligned(C, 16) && aligned(grad_c, gsz == 4 ? 16 : 8) && ldC % 8 == 0 && ld_gc % 8 == 0 &&
                        ld_gc < max_ld && (int64_t)K * ldC * 2 < ((int64_t)1 << 31);
         int rc;
+        const int64_t latent_cols[1] = {d_c};
         if (f) {
-            const int64_t latent_cols[1] = {d_c};
             rc = launch_fast<false>(a, T, latent_cols, 1, dtype, grad_dtype, st);
         } else {
-            a.n_tiles = (d_c + 63) / 64;
-            a.m_tiles = (int)((T + 63) / 64);
-            rc = launch_general<false>(a, dtype, grad_dtype, st);
+            p.tok = d_out; p.wgt = C; p.out = grad_c;
+            p.ld_tok = ld_dout; p.ld_wgt = ldC; p.ld_out = ld_gc;
+            p.rows = T; p.len = N;
+            rc = run_general<Product::Latent>(p, latent_cols, 1, dtype, grad_dtype, st);
         }
         if (rc) return rc;
     }
@@ -186,11 +184,10 @@ extern "C" int bda_kv_project_backward(const void* c, int64_t ldc, const void* d
         const bool f = fast && (T == 0 || aligned(c, 16)) && aligned(grad_C, gsz == 4 ? 16 : 8) && ldc % 8 == 0 &&
                        ldc < max_ld && ld_gC % 8 == 0 && ld_gC < max_ld;
         if (f) return launch_fast<true>(a, K, cols, G, dtype, grad_dtype, st);
-        a.tile_start[0] = 0;
-        for (int g = 0; g < G; ++g) a.tile_start[g + 1] = a.tile_start[g] + (int)((cols[g] + 63) / 64);
-        a.n_tiles = a.tile_start[G];
-        a.m_tiles = (K + 63) / 64;
-        return launch_general<true>(a, dtype, grad_dtype, st);
+        p.tok = c; p.wgt = d_out; p.out = grad_C;
+        p.ld_tok = ldc; p.ld_wgt = ld_dout; p.ld_out = ld_gC;
+        p.rows = K; p.len = T; p.skip = d_h;
+        return run_general<Product::Weight>(p, cols, G, dtype, grad_dtype, st);
     }
     return BDA_OK;
 }

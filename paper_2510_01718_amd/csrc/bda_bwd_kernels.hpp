@@ -572,132 +572,4 @@ __global__ __launch_bounds__(512) void bwd_weight_kernel(const BwdArgs p)
     if (half == 0) bwd_epilogue<X, OutT, TT, TN>(acc, rD, p.ldo, cols_left, wt, wn, l31, lhi);
 }
 
-// ---------------------------------------------------------------------------------------------
-// General kernels: any element type, shape or alignment.  64 x 64 output tile per workgroup of 256
-// threads (4 x 4 outputs each), contraction in steps of 16, scalar guarded loads, float32 FMAs.
-// ---------------------------------------------------------------------------------------------
-template <typename InT, typename OutT>
-__global__ __launch_bounds__(256) void bwd_latent_general_kernel(const BwdArgs p)
-{
-    __shared__ float Gs[16][64 + 1];
-    __shared__ float Ws[16][64 + 1];
-    const InT* __restrict__ Gg = (const InT*)p.g;
-    const InT* __restrict__ Cg = (const InT*)p.C;
-    OutT* __restrict__ Dg = (OutT*)p.out;
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
-    const int l0 = blockIdx.x * 64;
-    const int64_t t0 = (int64_t)blockIdx.y * 64;
-    const int64_t N = p.col_start[p.n_groups];
-
-    float acc[4][4] = {};
-    for (int64_t n0 = 0; n0 < N; n0 += 16) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int idx = tid + 256 * e;
-            {
-                const int kk = idx & 15, r = idx >> 4;
-                const int64_t n = n0 + kk, t = t0 + r;
-                Gs[kk][r] = (n < N && t < p.T) ? load_as_f32(Gg + t * p.ldg + n) : 0.0f;
-            }
-            {
-                const int kk = idx & 15, r = idx >> 4;     // r: latent column of the tile
-                const int64_t n = n0 + kk;
-                const int l = l0 + r;
-                float v = 0.0f;
-                if (n < N && l < p.d_c) {
-                    int g = 0;
-                    while (g + 1 < p.n_groups && n >= p.col_start[g + 1]) ++g;
-                    const int off = p.a_off[g];
-                    if (l >= off && l < off + p.d_h) v = (l - off == (int)((n - p.col_start[g]) % p.d_h)) ? 1.0f : 0.0f;
-                    else v = load_as_f32(Cg + (int64_t)(l < off ? l : l - p.d_h) * p.ldC + n);
-                }
-                Ws[kk][r] = v;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = Gs[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Ws[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t t = t0 + ty * 4 + i;
-            const int l = l0 + tx * 4 + j;
-            if (t < p.T && l < p.d_c) store_from_f32(Dg + t * p.ldo + l, acc[i][j]);
-        }
-}
-
-template <typename InT, typename OutT>
-__global__ __launch_bounds__(256) void bwd_weight_general_kernel(const BwdArgs p)
-{
-    __shared__ float As[16][64 + 1];
-    __shared__ float Bs[16][64 + 1];
-    const InT* __restrict__ Cg = (const InT*)p.c;
-    const InT* __restrict__ Gg = (const InT*)p.g;
-    OutT* __restrict__ Dg = (OutT*)p.out;
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
-    // column tiles are laid out per group so that a tile never straddles two basis windows
-    const int nt = blockIdx.x;
-    int g = 0;
-    while (g + 1 < p.n_groups && nt >= p.tile_start[g + 1]) ++g;
-    const int64_t n0 = p.col_start[g] + (int64_t)(nt - p.tile_start[g]) * 64;
-    const int64_t n_end = p.col_start[g + 1];
-    const int i0 = blockIdx.y * 64;
-    const int a_off = p.a_off[g];
-
-    float acc[4][4] = {};
-    for (int64_t t0 = 0; t0 < p.T; t0 += 16) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int idx = tid + 256 * e;
-            const int r = idx & 63, kk = idx >> 6;
-            const int64_t t = t0 + kk;
-            {
-                const int i = i0 + r;
-                As[kk][r] = (t < p.T && i < p.K) ? load_as_f32(Cg + t * p.ldc + (i < a_off ? i : i + p.d_h)) : 0.0f;
-            }
-            {
-                const int64_t n = n0 + r;
-                Bs[kk][r] = (t < p.T && n < n_end) ? load_as_f32(Gg + t * p.ldg + n) : 0.0f;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = i0 + ty * 4 + i;
-            const int64_t n = n0 + tx * 4 + j;
-            if (r < p.K && n < n_end) store_from_f32(Dg + (int64_t)r * p.ldo + n, acc[i][j]);
-        }
-}
-
 }  // namespace bda

@@ -383,8 +383,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const GemmArgs p)
     }
 }
 
-// General kernel: any element type, any shape or alignment.  64 x 64 output tile per workgroup of
-// 256 threads (4 x 4 outputs each), BK = 16, scalar guarded loads, float32 FMA accumulation.
+// Elements of any type as float32 and back, for the general kernels.
 template <typename InT>
 __device__ __forceinline__ float load_as_f32(const InT* p);
 template <>
@@ -404,82 +403,5 @@ template <>
 __device__ __forceinline__ void store_from_f32<RawF16>(RawF16* p, float v) { p->b = F16::from_f32(v); }
 template <>
 __device__ __forceinline__ void store_from_f32<RawBF16>(RawBF16* p, float v) { p->b = BF16::from_f32(v); }
-
-template <typename InT, typename OutT>
-__global__ __launch_bounds__(256) void gemm_general_kernel(const GemmArgs p, int64_t N_total)
-{
-    __shared__ float As[16][64 + 1];
-    __shared__ float Bs[16][64 + 1];
-    const InT* __restrict__ Ag = (const InT*)p.A;
-    const InT* __restrict__ Bg = (const InT*)p.B;
-    OutT* __restrict__ Dg = (OutT*)p.D;
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
-    // column tiles are laid out per group so that a tile never straddles two basis windows
-    const int nt = blockIdx.x;
-    int g = 0;
-    while (g + 1 < p.n_groups && nt >= p.tile_start[g + 1]) ++g;
-    const int64_t n0 = p.col_start[g] + (int64_t)(nt - p.tile_start[g]) * 64;
-    const int64_t n_end = p.col_start[g + 1];
-    const int64_t t0 = (int64_t)blockIdx.y * 64;
-    const int a_off = p.a_off[g];
-    (void)N_total;
-
-    float acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t t = t0 + ty * 4 + i, n = n0 + tx * 4 + j;
-            float v = 0.0f;
-            if (p.ident && t < p.M && n < n_end)
-                v = load_as_f32(Ag + t * p.lda + a_off + (int)((n - p.col_start[g]) % p.d_h));
-            acc[i][j] = v;
-        }
-    for (int k0 = 0; k0 < p.K; k0 += 16) {
-        // 64 x 16 slice of A and 16 x 64 slice of B, four elements per thread each
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int idx = tid + 256 * e;
-            {
-                const int kk = idx & 15, r = idx >> 4;
-                const int k = k0 + kk;
-                const int64_t t = t0 + r;
-                float v = 0.0f;
-                if (k < p.K && t < p.M) v = load_as_f32(Ag + t * p.lda + (k < a_off ? k : k + p.a_skip));
-                As[kk][r] = v;
-            }
-            {
-                const int c = idx & 63, kk = idx >> 6;
-                const int k = k0 + kk;
-                const int64_t n = n0 + c;
-                float v = 0.0f;
-                if (k < p.K && n < n_end) v = load_as_f32(Bg + (int64_t)k * p.ldb + n);
-                Bs[kk][c] = v;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t t = t0 + ty * 4 + i, n = n0 + tx * 4 + j;
-            if (t < p.M && n < n_end) store_from_f32(Dg + t * p.ldd + n, acc[i][j]);
-        }
-}
 
 }  // namespace bda

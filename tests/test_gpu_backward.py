@@ -97,6 +97,34 @@ def test_backward_general_kernels(dtype):
         _check(33, 64, 16, [2], [8], dtype, grad_dtype=wl.F32)
 
 
+# The general kernel's tiles (128 x 128 .. 32 x 32), each product's remainders in rows, columns and contraction,
+# windows that differ between groups, and sizes at which 16-byte pieces do not apply (odd head width or pitch).
+GENERAL_SHAPES = [
+    (1, 96, 32, [1, 2], [0, 64], 0),            # one token: 32 x 32 tiles, contractions below and above one chunk
+    (31, 512, 64, [8, 8], [0, 448], 0),
+    (33, 132, 20, [3, 2], [4, 112], 0),         # d_h not a multiple of 32 or 16
+    (700, 512, 64, [8, 8], [448, 128], 4),
+    (1030, 160, 80, [13, 4], [16, 0], 0),       # 64 x 32 and 64 x 64 tiles, cut
+    (2050, 288, 96, [12, 11], [0, 192], 0),
+    (4100, 256, 128, [7, 6], [128, 32], 0),     # 128 x 128 tiles, cut
+    (130, 97, 33, [2, 1], [5, 31], 0),          # element by element
+    (900, 128, 64, [9, 9], [0, 64], 1),
+]
+
+
+@pytest.mark.parametrize("T,d_c,d_h,H,offs,pad", GENERAL_SHAPES)
+def test_float32_general_kernel_tiles(T, d_c, d_h, H, offs, pad):
+    """Forward and both gradients.  A float32 sum of n products is off by at most n 2^-24 of the sum of their
+    magnitudes, and by about sqrt(n) 2^-24 of the result's own size: 4e-6 at the longest contraction here."""
+    _check(T, d_c, d_h, H, offs, wl.F32, pad=pad)
+    (c_s, c64), _, (C_s, C64) = _inputs(5, T, d_c, d_h, H, wl.F32)
+    N = sum(H) * d_h
+    got, raw = gh.kv_project(c_s, C_s, d_c, d_h, H, offs, wl.F32, ldc=d_c + pad, ldC=N + pad, ld_out=N + pad, fill=7.5, extra_rows=1)
+    assert_parity(got, oracle.kv_project(c64, C64, d_h, H, offs), d_h, wl.F32, wl.F32, f"forward T={T} d_c={d_c} d_h={d_h}")
+    raw = raw.cpu().numpy()
+    assert np.all(raw[T:] == 7.5) and np.all(raw[:, N:] == 7.5)
+
+
 def test_backward_tile_shapes_chosen_by_size():
     # many 64 x 64 tiles (two per compute unit): 65 x 8 for the latent gradient ...
     _check(4100, 512, 128, [1, 1], [0, 384], wl.F16)
