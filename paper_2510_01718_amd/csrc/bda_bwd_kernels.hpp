@@ -77,6 +77,16 @@ __device__ __forceinline__ u32x4 shifted_identity_frag(int d, int l31, int lhi)
     return f;
 }
 
+// Descriptor from values that are the same in every lane, in scalar registers for certain: where the compiler
+// keeps one of them in a vector register it reads it back lane by lane around every load.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const char* base, uint32_t bytes)
+{
+    const uint64_t b = (uint64_t)base;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), 0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
+}
+
 // Tiles are dealt to the dies in contiguous runs (workgroup b runs on die b % 8), so that tiles
 // that are neighbours in the run order -- they share one operand -- meet in the same L2.
 __device__ __forceinline__ int bwd_tile_of_block(int total)
@@ -133,24 +143,25 @@ struct BwdLds {
     static_assert(4 * TT * TN * 16 * 64 * 4 <= BYTES, "accumulator exchange must fit the staging memory");
 };
 
-// One staged chunk: 4 k-steps of TT x TN MFMAs; `extra(ks, ft)` may add MFMAs that reuse the column
-// operand's fragments.
-template <typename X, int TT, int TN, typename Extra>
-__device__ __forceinline__ void bwd_mma_chunk(const unsigned char* tok_s, const unsigned char* wgt_s,
-                                              f32x16 (&acc)[TN][TT], Extra&& extra)
+// One staged chunk: 4 k-steps of TT x TN MFMAs.  read(ks, fw, ft) fetches the fragments of a step from LDS; they
+// are requested a step (one tile per wave: two steps) before their MFMAs, so that the reads' latency runs beside
+// the MFMAs instead of between them.
+template <typename X, int TT, int TN, typename Read>
+__device__ __forceinline__ void bwd_mma_chunk(f32x16 (&acc)[TN][TT], Read&& read)
 {
+    constexpr int AHEAD = TT * TN == 1 ? 2 : 1, SETS = AHEAD + 1;
+    u32x4 fw[SETS][TN], ft[SETS][TT];
+#pragma unroll
+    for (int ks = 0; ks < AHEAD; ++ks) read(ks, fw[ks], ft[ks]);
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-        u32x4 fw[TN], ft[TT];
-#pragma unroll
-        for (int ni = 0; ni < TN; ++ni) fw[ni] = *(const u32x4*)(wgt_s + ni * 32 * kRowBytes + ks * 32);
-#pragma unroll
-        for (int ti = 0; ti < TT; ++ti) ft[ti] = *(const u32x4*)(tok_s + ti * 32 * kRowBytes + ks * 32);
+        if (ks + AHEAD < 4) read(ks + AHEAD, fw[(ks + AHEAD) % SETS], ft[(ks + AHEAD) % SETS]);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int ni = 0; ni < TN; ++ni)
 #pragma unroll
-            for (int ti = 0; ti < TT; ++ti) acc[ni][ti] = X::mfma(fw[ni], ft[ti], acc[ni][ti]);
-        extra(ks, ft);
+            for (int ti = 0; ti < TT; ++ti) acc[ni][ti] = X::mfma(fw[ks % SETS][ni], ft[ks % SETS][ti], acc[ni][ti]);
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -332,22 +343,38 @@ __global__ __launch_bounds__(512) void bwd_latent_kernel(const BwdArgs p)
         load_chunk(set, ld);
         advance(ld);
         if (cur.valid) {
-            const int off = cur.off, jc = cur.jc;
-            bwd_mma_chunk<X, TT, TN>(lds + tok_rd + LS * L::TOK_STAGE, lds + wgt_rd + LS * L::WGT_STAGE, acc,
-                                     [&](int ks, const u32x4 (&ft)[TT]) {
-                // window rows of Wfull: output columns nc + 16 ks + k' feed latent column off + jk + k'
-                int jk = jc + 16 * ks;
-                if (jk >= p.d_h) jk -= p.d_h;
+            const unsigned char* const tok_s = lds + tok_rd + LS * L::TOK_STAGE;
+            const unsigned char* const wgt_s = lds + wgt_rd + LS * L::WGT_STAGE;
+            const int off = cur.off;
+            // (a wave whose columns all lie in the window has no rows of C: the staged zeros are not multiplied.
+            // With d_h = 128 those waves had half again as many MFMAs as the others and set the launch's time.)
+            if (!(off <= colm0 && colm0 + 32 * TN <= off + p.d_h))
+                bwd_mma_chunk<X, TT, TN>(acc, [&](int ks, u32x4 (&fw)[TN], u32x4 (&ft)[TT]) {
 #pragma unroll
-                for (int ni = 0; ni < TN; ++ni) {
-                    const int d = off + jk - (colm0 + 32 * ni);
-                    if (d > -16 && d < 32) {   // uniform over the wave
-                        const u32x4 f = shifted_identity_frag<X>(d, l31, lhi);
+                    for (int ni = 0; ni < TN; ++ni) fw[ni] = *(const u32x4*)(wgt_s + ni * 32 * kRowBytes + ks * 32);
 #pragma unroll
-                        for (int ti = 0; ti < TT; ++ti) acc[ni][ti] = X::mfma(f, ft[ti], acc[ni][ti]);
+                    for (int ti = 0; ti < TT; ++ti) ft[ti] = *(const u32x4*)(tok_s + ti * 32 * kRowBytes + ks * 32);
+                });
+            // window rows of Wfull: output columns nc + 16 ks + k' feed latent column off + jk + k'.  After the
+            // chunk's other MFMAs, with the G fragments read again: most waves and chunks have none of them, and
+            // the steps above stay free of branches.
+            if (off < colm0 + 32 * TN && off + p.d_h > colm0) {
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) {
+                    int jk = cur.jc + 16 * ks;
+                    if (jk >= p.d_h) jk -= p.d_h;
+#pragma unroll
+                    for (int ni = 0; ni < TN; ++ni) {
+                        const int d = off + jk - (colm0 + 32 * ni);
+                        if (d > -16 && d < 32) {   // uniform over the wave
+                            const u32x4 f = shifted_identity_frag<X>(d, l31, lhi);
+#pragma unroll
+                            for (int ti = 0; ti < TT; ++ti)
+                                acc[ni][ti] = X::mfma(f, *(const u32x4*)(tok_s + ti * 32 * kRowBytes + ks * 32), acc[ni][ti]);
+                        }
                     }
                 }
-            });
+            }
         }
         advance(cur);
         store_chunk(std::integral_constant<int, (S + 1) % D>{}, std::integral_constant<int, 1 - LS>{});
@@ -479,10 +506,8 @@ __global__ __launch_bounds__(512) void bwd_weight_kernel(const BwdArgs p)
     auto load_chunk = [&](auto set) {
         constexpr int S = decltype(set)::value;
         const bool full = ld_chunk < n_full, last = ld_chunk == n_full;
-        const __amdgpu_buffer_rsrc_t rA = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<char*>(c_ptr), 0, (int)(full ? c_full : last ? c_tail : 0u), 0x00020000);
-        const __amdgpu_buffer_rsrc_t rB = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<char*>(g_ptr), 0, (int)(full ? g_full : last ? g_tail : 0u), 0x00020000);
+        const __amdgpu_buffer_rsrc_t rA = uniform_rsrc(c_ptr, full ? c_full : last ? c_tail : 0u);
+        const __amdgpu_buffer_rsrc_t rB = uniform_rsrc(g_ptr, full ? g_full : last ? g_tail : 0u);
 #pragma unroll
         for (int i = 0; i < TOK_LOADS; ++i) tok_reg[S][i] = __builtin_amdgcn_raw_buffer_load_b128(rA, tok_v[i], 0, 0);
 #pragma unroll
@@ -540,20 +565,14 @@ __global__ __launch_bounds__(512) void bwd_weight_kernel(const BwdArgs p)
         constexpr int S = decltype(set)::value, LS = decltype(stage)::value;
         load_chunk(set);
         if (2 * it + half < n_chunks) {
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                u32x4 fw[TN], ft[TT];
+            bwd_mma_chunk<X, TT, TN>(acc, [&](int ks, u32x4 (&fw)[TN], u32x4 (&ft)[TT]) {
 #pragma unroll
                 for (int ni = 0; ni < TN; ++ni)
                     fw[ni] = frag(a_wgt[ni] + LS * L::WGT_STAGE + 16 * ks * L::WGT_PITCH, L::WGT_PITCH);
 #pragma unroll
                 for (int ti = 0; ti < TT; ++ti)
                     ft[ti] = frag(a_tok[ti] + LS * L::TOK_STAGE + 16 * ks * L::TOK_PITCH, L::TOK_PITCH);
-#pragma unroll
-                for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-                    for (int ti = 0; ti < TT; ++ti) acc[ni][ti] = X::mfma(fw[ni], ft[ti], acc[ni][ti]);
-            }
+            });
         }
         store_chunk(std::integral_constant<int, (S + 1) % D>{}, std::integral_constant<int, 1 - LS>{});
         __syncthreads();
