@@ -191,8 +191,8 @@ int bda_prepare_device(const void* W, int64_t ldw, bda_dtype w_dtype, int d_c, i
  * Products are accumulated in float32 (fp16/bf16 inputs use MFMA), the identity slice is added in
  * float32, and each output is rounded once (nearest even) when stored.  The MFMA path needs 16-byte
  * aligned pointers, ld's and basis offsets that are multiples of 8 elements, d_c a multiple of 8
- * and d_h a multiple of 32; anything else (and BDA_F32 inputs) runs a slower general kernel on the float32 matrix instructions with
- * the same result contract.
+ * and d_h a multiple of 32; anything else (and BDA_F32 inputs) runs a slower general kernel
+ * on the float32 matrix instructions with the same result contract.
  * Errors: BDA_EINVAL, BDA_EDTYPE, BDA_EHIP.
  */
 int bda_kv_project(const void* c, int64_t ldc, int64_t T, int d_c, int d_h,
@@ -238,8 +238,8 @@ int bda_lowrank_linear(const void* x, int64_t ldx, int64_t T, int d_in, int r, i
  * Each gradient is one launch on `stream`; products are accumulated in float32 (fp16/bf16 inputs use
  * MFMA; the head sum on the window is part of the same accumulation) and rounded once when stored.
  * The MFMA path needs 16-byte aligned pointers, ld's, d_c and basis offsets that are multiples of 8
- * and d_h a multiple of 32; anything else (and BDA_F32 inputs) runs slower general kernels on the float32 matrix instructions with
- * the same result contract.  Gradients must not overlap the inputs or each other.
+ * and d_h a multiple of 32; anything else (and BDA_F32 inputs) runs a slower general
+ * kernel on the float32 matrix instructions with the same result contract.  Gradients must not overlap the inputs or each other.
  * Errors: BDA_EINVAL, BDA_EDTYPE, BDA_EHIP.
  */
 int bda_kv_project_backward(const void* c, int64_t ldc, const void* d_out, int64_t ld_dout,
@@ -318,7 +318,7 @@ int bda_kv_project_backward_ex(const void* c, int64_t ldc, const void* d_out, in
 typedef enum {
     BDA_KERNEL_NONE = 0,    /* nothing to launch (T = 0) */
     BDA_KERNEL_GENERAL = 1, /* any type / shape / alignment: 128 x 128 to 32 x 32 tiles, float32 MFMA */
-    BDA_KERNEL_MFMA = 2,    /* register-staged MFMA kernel, 128 x 128 or 256 x 256 tiles */
+    BDA_KERNEL_MFMA = 2,    /* register-staged MFMA kernels, 64 x 64, 128 x 128 or 256 x 256 tiles */
     BDA_KERNEL_STREAM = 3,  /* streaming MFMA kernel (LDS DMA ring), general variant */
     BDA_KERNEL_LEAN = 4,    /* streaming MFMA kernel, lean variant (256-, 128- or 64-token tiles) */
     BDA_KERNEL_DECODE = 5,  /* few tokens (token tiles of up to 128): weight-streaming kernels; tile_columns tells 32-, 64- and 128-column slices apart */

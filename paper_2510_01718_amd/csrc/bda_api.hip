@@ -10,6 +10,7 @@
 #include "bda_gemm_plain.hpp"
 #include "bda_gemm_duo.hpp"
 #include "bda_gemm_f32.hpp"
+#include "bda_gemm_mid.hpp"
 #include "bda_internal.h"
 
 namespace bda {
@@ -58,6 +59,23 @@ int launch_mfma(GemmArgs& a, hipStream_t st)
     }
     if (int rc = set_max_lds(kern, lds, once)) return rc;
     hipLaunchKernelGGL(kern, dim3(kNumXcd * a.sm * a.sn), dim3(256), lds, st, a);
+    hipError_t err = hipGetLastError();
+    return err == hipSuccess ? BDA_OK : fail(BDA_EHIP, "kernel launch: %s", hipGetErrorString(err));
+}
+
+template <typename X, typename OutT, int TT, int TN>
+int launch_mid(GemmArgs& a, hipStream_t st)
+{
+    static LdsLimitState once;
+    using L = MidLds<TT, TN>;
+    auto kern = gemm_mid_kernel<X, OutT, TT, TN>;
+    const int total = a.m_tiles * a.n_tiles, grid = kNumXcd * ((total + kNumXcd - 1) / kNumXcd);
+    a.lin_slots = 0;
+    a.sm = a.sn = 1;
+    constexpr int per_cu = 160 * 1024 / L::BYTES;
+    if (plan_only(a, BDA_KERNEL_MFMA, L::BT, L::BN, grid, 512, L::BYTES, (total + 256 * per_cu - 1) / (256 * per_cu))) return BDA_OK;
+    if (int rc = set_max_lds(kern, L::BYTES, once)) return rc;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(512), L::BYTES, st, a);
     hipError_t err = hipGetLastError();
     return err == hipSuccess ? BDA_OK : fail(BDA_EHIP, "kernel launch: %s", hipGetErrorString(err));
 }
@@ -341,6 +359,30 @@ bool lean_kernel_applies(const GemmArgs& a, int G, const int64_t* group_cols)
     return ok && a.K / 64 + id_stages >= 3;
 }
 
+// Tile of gemm_mid_kernel (64 or 128 square) for a launch that the lean kernel does not take, or 0.  Below 96 tiles of
+// 256 x 256 the alternative is the register-staged kernel, slower at every size measured (us, bf16; 64 x 64 tiles
+// against it): T = 1500, K = 288, N = 2304 14.5 / 22.7; T = 1500, K = 608, N = 2176 17.5 / 35.9; T = 300, K = 320,
+// N = 5760 8.5 / 20.7; T = 3001, K = 384, N = 256 6.4 / 23.4.  From 96 up it is the streaming kernel, whose round of
+// tiles takes about 10 + 0.025 K us however few tiles are in it (K = 160 14, 288 17, 416 21, 608 25); the 64 x 64
+// tiles take about 5 us and at most 0.0075 + 1.4e-5 K us each (T = 3001, N = 2304, K = 288: 23 / 32, two rounds; T = 3001,
+// N = 4096, K = 416: 40 / 23.5, one round; T = 1024, N = 9000, K = 4096: 184 / 118).  Launches of at most 128 columns keep the 128 x 128 tiles that their
+// launch plan has always reported (T = 3001, K = 384, N = 256: 11.7).
+int mid_tile(const GemmArgs& a, int G, const int64_t* group_cols, bool big)
+{
+    int64_t N = 0, nt64 = 0;
+    for (int g = 0; g < G; ++g) { N += group_cols[g]; nt64 += (group_cols[g] + 63) / 64; }
+    if (big) {
+        GemmArgs s = a;
+        build_tiles(s, G, group_cols, 256, 256);
+        choose_super(s, kSlotsPerXcd, 256, 256);
+        const int64_t supers = (int64_t)((s.m_tiles + s.sm - 1) / s.sm) * ((s.n_tiles + s.sn - 1) / s.sn);
+        const double stream = (double)((supers + kNumXcd - 1) / kNumXcd) * (10.0 + 0.025 * a.K);
+        const double mid = 5.0 + (double)((a.M + 63) / 64 * nt64) * (0.0075 + 1.4e-5 * a.K);
+        return mid < 0.95 * stream ? 64 : 0;
+    }
+    return N <= 128 ? 128 : 64;
+}
+
 int run_gemm(GemmArgs& a, int G, const int64_t* group_cols, int dtype, int out_dtype, hipStream_t st)
 {
     int64_t N_total = 0;
@@ -458,6 +500,16 @@ int run_gemm(GemmArgs& a, int G, const int64_t* group_cols, int dtype, int out_d
         const int tok_tile = quarter_tokens ? 64 : half_tokens ? 128 : 256;
         const bool big = plain || policy == 2 || policy == 3 || policy == 4 || ((policy == 0 || policy == 7) && mt256 * nt256 >= 96);
         const bool stream = big && stream_ok;
+        const int mid = policy == 0 && !plain && (stream || !big) ? mid_tile(a, G, group_cols, big) : 0;
+        if (mid) {
+            build_tiles(a, G, group_cols, mid, mid);
+#define BDA_LAUNCH(X, O) return mid == 64 ? launch_mid<X, O, 1, 1>(a, st) : launch_mid<X, O, 2, 2>(a, st)
+            if (dtype == BDA_F16 && out_dtype == BDA_F16) { BDA_LAUNCH(F16, uint16_t); }
+            if (dtype == BDA_F16 && out_dtype == BDA_F32) { BDA_LAUNCH(F16, float); }
+            if (dtype == BDA_BF16 && out_dtype == BDA_BF16) { BDA_LAUNCH(BF16, uint16_t); }
+            if (dtype == BDA_BF16 && out_dtype == BDA_F32) { BDA_LAUNCH(BF16, float); }
+#undef BDA_LAUNCH
+        }
         if (big) {
             build_tiles(a, G, group_cols, tok_tile, 256);
             choose_super(a, kSlotsPerXcd, tok_tile, 256);

@@ -347,6 +347,30 @@ def test_small_T_kernels_strided_buffers_and_exact_copy(T, policy):
         assert np.array_equal(copy[:, h * 128:(h + 1) * 128], w.c[:, off:off + 128]), (h, policy)
 
 
+# Launches outside the lean kernel's shapes: 64 x 64 tiles (128 x 128 up to 128 columns) whose halves share the
+# contraction.  Contractions of one chunk (the second half has none), of a part of a chunk, of an odd and an even
+# number of chunks; cut tiles in both directions; windows on both sides of a chunk and inside one.
+@pytest.mark.parametrize("dtype,out_dtype", [(wl.F16, wl.F16), (wl.BF16, wl.F32)])
+@pytest.mark.parametrize("T,d_c,d_h,H,offs,tile", [
+    (1100, 64, 32, [9, 1], [0, 32], 64),            # K = 32
+    (1090, 384, 96, [12, 12], [208, 48], 64),       # K = 288, windows inside chunks
+    (1500, 232, 64, [17, 3, 2], [160, 0, 8], 64),   # K = 168, three groups
+    (321, 416, 96, [30, 30], [0, 320], 64),         # K = 320: five chunks
+    (1537, 512, 128, [1], [128], 128),              # one 128-column group
+])
+def test_kv_small_tile_kernel(T, d_c, d_h, H, offs, tile, dtype, out_dtype):
+    plan = bda.bda_kv_project_plan(T, d_c, d_h, H, offs, dtype, out_dtype)
+    assert (plan["kernel"], plan["tile_tokens"], plan["tile_columns"], plan["threads"]) == (bda.KERNEL_MFMA, tile, tile, 512)
+    rng = np.random.default_rng([T, d_c])
+    N = sum(H) * d_h
+    c_s, c64 = wl.to_storage(rng.standard_normal((T, d_c)), dtype)
+    C_s, C64 = wl.to_storage(0.25 * rng.standard_normal((d_c - d_h, N)), dtype)
+    got, raw = gh.kv_project(c_s, C_s, d_c, d_h, H, offs, dtype, out_dtype, ldc=d_c + 8, ldC=N + 16, ld_out=N + 8, fill=3, extra_rows=2)
+    assert_parity(got, oracle.kv_project(c64, C64, d_h, H, offs), d_h, dtype, out_dtype, f"T={T} d_c={d_c} d_h={d_h}")
+    raw = raw.cpu().numpy()
+    assert np.all(raw[T:] == 3) and np.all(raw[:, N:] == 3)
+
+
 def test_kv_general_kernel_for_unaligned_shapes():
     # d_h = 20 and d_c = 52 satisfy none of the MFMA path's alignment rules
     w = wl.custom_kv_workload("unaligned", T=77, d_c=52, d_h=20, H=[2, 3], std=0.1, rms_norm=False,
