@@ -346,31 +346,45 @@ __global__ __launch_bounds__(512) void bwd_latent_kernel(const BwdArgs p)
             const unsigned char* const tok_s = lds + tok_rd + LS * L::TOK_STAGE;
             const unsigned char* const wgt_s = lds + wgt_rd + LS * L::WGT_STAGE;
             const int off = cur.off;
-            // (a wave whose columns all lie in the window has no rows of C: the staged zeros are not multiplied.
-            // With d_h = 128 those waves had half again as many MFMAs as the others and set the launch's time.)
-            if (!(off <= colm0 && colm0 + 32 * TN <= off + p.d_h))
-                bwd_mma_chunk<X, TT, TN>(acc, [&](int ks, u32x4 (&fw)[TN], u32x4 (&ft)[TT]) {
-#pragma unroll
-                    for (int ni = 0; ni < TN; ++ni) fw[ni] = *(const u32x4*)(wgt_s + ni * 32 * kRowBytes + ks * 32);
-#pragma unroll
-                    for (int ti = 0; ti < TT; ++ti) ft[ti] = *(const u32x4*)(tok_s + ti * 32 * kRowBytes + ks * 32);
-                });
-            // window rows of Wfull: output columns nc + 16 ks + k' feed latent column off + jk + k'.  After the
-            // chunk's other MFMAs, with the G fragments read again: most waves and chunks have none of them, and
-            // the steps above stay free of branches.
-            if (off < colm0 + 32 * TN && off + p.d_h > colm0) {
+            if constexpr (TT * TN == 1) {
+                // One tile per wave: the window's MFMA beside the step's own, from the same fragment.  (The order below
+                // took 198 us against 191 at 202 tokens, N = 30464, where a chunk's chain of latencies is the time.)
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks) {
+                    const u32x4 fw = *(const u32x4*)(wgt_s + ks * 32), ft = *(const u32x4*)(tok_s + ks * 32);
+                    acc[0][0] = X::mfma(fw, ft, acc[0][0]);
                     int jk = cur.jc + 16 * ks;
                     if (jk >= p.d_h) jk -= p.d_h;
+                    const int d = off + jk - colm0;
+                    if (d > -16 && d < 32) acc[0][0] = X::mfma(shifted_identity_frag<X>(d, l31, lhi), ft, acc[0][0]);
+                }
+            } else {
+                // (a wave whose columns all lie in the window has no rows of C: the staged zeros are not multiplied.
+                // With d_h = 128 those waves had half again as many MFMAs as the others and set the launch's time.)
+                if (!(off <= colm0 && colm0 + 32 * TN <= off + p.d_h))
+                    bwd_mma_chunk<X, TT, TN>(acc, [&](int ks, u32x4 (&fw)[TN], u32x4 (&ft)[TT]) {
 #pragma unroll
-                    for (int ni = 0; ni < TN; ++ni) {
-                        const int d = off + jk - (colm0 + 32 * ni);
-                        if (d > -16 && d < 32) {   // uniform over the wave
-                            const u32x4 f = shifted_identity_frag<X>(d, l31, lhi);
+                        for (int ni = 0; ni < TN; ++ni) fw[ni] = *(const u32x4*)(wgt_s + ni * 32 * kRowBytes + ks * 32);
 #pragma unroll
-                            for (int ti = 0; ti < TT; ++ti)
-                                acc[ni][ti] = X::mfma(f, *(const u32x4*)(tok_s + ti * 32 * kRowBytes + ks * 32), acc[ni][ti]);
+                        for (int ti = 0; ti < TT; ++ti) ft[ti] = *(const u32x4*)(tok_s + ti * 32 * kRowBytes + ks * 32);
+                    });
+                // window rows of Wfull: output columns nc + 16 ks + k' feed latent column off + jk + k'.  After the
+                // chunk's other MFMAs, with the G fragments read again: most waves and chunks have none of them, and
+                // the steps above stay free of branches.
+                if (off < colm0 + 32 * TN && off + p.d_h > colm0) {
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks) {
+                        int jk = cur.jc + 16 * ks;
+                        if (jk >= p.d_h) jk -= p.d_h;
+#pragma unroll
+                        for (int ni = 0; ni < TN; ++ni) {
+                            const int d = off + jk - (colm0 + 32 * ni);
+                            if (d > -16 && d < 32) {   // uniform over the wave
+                                const u32x4 f = shifted_identity_frag<X>(d, l31, lhi);
+#pragma unroll
+                                for (int ti = 0; ti < TT; ++ti)
+                                    acc[ni][ti] = X::mfma(f, *(const u32x4*)(tok_s + ti * 32 * kRowBytes + ks * 32), acc[ni][ti]);
+                            }
                         }
                     }
                 }
