@@ -500,7 +500,7 @@ int run_gemm(GemmArgs& a, int G, const int64_t* group_cols, int dtype, int out_d
         const int tok_tile = quarter_tokens ? 64 : half_tokens ? 128 : 256;
         const bool big = plain || policy == 2 || policy == 3 || policy == 4 || ((policy == 0 || policy == 7) && mt256 * nt256 >= 96);
         const bool stream = big && stream_ok;
-        const int mid = policy == 0 && !plain && (stream || !big) ? mid_tile(a, G, group_cols, big) : 0;
+        const int mid = (policy == 0 || policy == 7) && !plain && (stream || !big) ? mid_tile(a, G, group_cols, big) : 0;
         if (mid) {
             build_tiles(a, G, group_cols, mid, mid);
 #define BDA_LAUNCH(X, O) return mid == 64 ? launch_mid<X, O, 1, 1>(a, st) : launch_mid<X, O, 2, 2>(a, st)

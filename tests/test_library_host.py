@@ -342,3 +342,12 @@ def test_launch_plan_preconditions_of_the_lean_kernel():
     assert _plan(4096, [16, 16], [0, 0], bda.BDA_F16)["kernel"] == lean          # and nothing of it outlives the call
     with pytest.raises(bda.BdaError):
         _plan(4096, [16, 16], [0, 400], bda.BDA_F16)                    # window outside the latent
+
+
+def test_launch_plan_policy_7_is_the_automatic_choice_outside_the_lean_kernels_shapes():
+    """Tile policy 7 where the lean kernel does not apply acts as 0 without the few-token kernels (include/bda.h)."""
+    for T, H, offs, d_c, d_h in ((300, [30, 30], [0, 320], 416, 96), (1500, [17, 3, 2], [160, 0, 8], 232, 64), (20000, [5], [0], 96, 32),
+                                 (3001, [12, 12], [208, 48], 384, 96), (8192, [128, 127], [0, 0], 544, 128)):
+        auto = _plan(T, H, offs, bda.BDA_BF16, d_c=d_c, d_h=d_h)
+        assert auto["kernel"] in (bda.KERNEL_MFMA, bda.KERNEL_STREAM), (T, auto)
+        assert _plan(T, H, offs, bda.BDA_BF16, d_c=d_c, d_h=d_h, tile_policy=7) == auto, T
