@@ -371,6 +371,7 @@ int mid_tile(const GemmArgs& a, int G, const int64_t* group_cols, bool big)
 {
     int64_t N = 0, nt64 = 0;
     for (int g = 0; g < G; ++g) { N += group_cols[g]; nt64 += (group_cols[g] + 63) / 64; }
+    if ((a.M + 63) / 64 * nt64 > (1 << 22)) return 0;   // a workgroup of 512 per tile: 2^31 of the 2^32 work-items a launch may have
     if (big) {
         GemmArgs s = a;
         build_tiles(s, G, group_cols, 256, 256);

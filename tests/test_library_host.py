@@ -351,3 +351,12 @@ def test_launch_plan_policy_7_is_the_automatic_choice_outside_the_lean_kernels_s
         auto = _plan(T, H, offs, bda.BDA_BF16, d_c=d_c, d_h=d_h)
         assert auto["kernel"] in (bda.KERNEL_MFMA, bda.KERNEL_STREAM), (T, auto)
         assert _plan(T, H, offs, bda.BDA_BF16, d_c=d_c, d_h=d_h, tile_policy=7) == auto, T
+
+
+@pytest.mark.parametrize("T,H,d_c,d_h", [(500_000_000, [1], 64, 32), (600_000_000, [1], 64, 32), (2_000_000_000, [1], 64, 32),
+                                         (2_000_000_000, [1, 1, 1], 96, 32), (700_000_000, [2], 96, 32)])
+def test_launch_plan_of_very_many_tokens_fits_a_launch(T, H, d_c, d_h):
+    """A launch has fewer than 2^32 work-items: rules that give every tile a workgroup of its own end before that
+    (T x 64 latent values of 16 bits are 77 GB at 600 M tokens, which one GPU holds)."""
+    p = _plan(T, H, [0] * len(H), bda.BDA_BF16, d_c=d_c, d_h=d_h)
+    assert p["kernel"] != bda.KERNEL_NONE and p["workgroups"] * p["threads"] < 2 ** 32, p
