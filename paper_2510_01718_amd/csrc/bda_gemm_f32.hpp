@@ -72,9 +72,10 @@ struct GeneralTile {
     static constexpr int TOK_PPR = (TOK_KC ? BK : BT) / 4, WGT_PPR = (WGT_KC ? BK : BN) / 4;           // pieces of four per LDS row
     static constexpr int TOK_RPP = THREADS / TOK_PPR, WGT_RPP = THREADS / WGT_PPR;                     // LDS rows per pass
     static constexpr int TOK_LOADS = (TOK_KC ? BT : BK) / TOK_RPP, WGT_LOADS = (WGT_KC ? BN : BK) / WGT_RPP;
-    static constexpr int SETS = TT * TN > 1 ? 1 : 2;       // register sets: chunks in flight beyond the one being multiplied
+    static constexpr int SETS = TT * TN > 1 || KS == 1 ? 1 : 2;   // register sets: chunks in flight beyond the one being multiplied
+    static constexpr int STAGES = KS == 1 ? 1 : 2;                // of LDS
     static constexpr int SUMS = (KS - 1) * WT * WN * TT * TN * 16 * 64;
-    static constexpr int LDS_BYTES = 4 * (2 * STAGE > SUMS ? 2 * STAGE : SUMS);
+    static constexpr int LDS_BYTES = 4 * (STAGES * STAGE > SUMS ? STAGES * STAGE : SUMS);
     static_assert(THREADS % TOK_PPR == 0 && THREADS % WGT_PPR == 0 && KPG % 8 == 0);
     static_assert(TOK_LOADS * TOK_RPP == (TOK_KC ? BT : BK) && WGT_LOADS * WGT_RPP == (WGT_KC ? BN : BK));
     static_assert(LDS_BYTES <= 160 * 1024);
@@ -246,6 +247,25 @@ __global__ __launch_bounds__(64 * WT * WN * KS, TT * TN > 1 ? 2 : 4) void genera
         return (f32x4){s[k * pitch + x], s[(k + 1) * pitch + x], s[(k + 2) * pitch + x], s[(k + 3) * pitch + x]};
     };
     const int n_chunks = (int)((p.len + L::BK - 1) / L::BK);
+    f32x4 fw[2][TN], ft[2][TT];                         // fragments of one step and the next
+    auto read = [&](const float* tok_s, int s) {
+        const float* const wgt_s = tok_s + L::TOK_STAGE;
+        const int k = kg * KPG + 8 * s + 4 * lhi;
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) fw[s & 1][ni] = frag(wgt_s, L::WGT_PITCH, L::WGT_KC, (wn * TN + ni) * 32 + l31, k);
+#pragma unroll
+        for (int ti = 0; ti < TT; ++ti) ft[s & 1][ti] = frag(tok_s, L::TOK_PITCH, L::TOK_KC, (wt * TT + ti) * 32 + l31, k);
+    };
+    auto multiply = [&](int s) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+                for (int ti = 0; ti < TT; ++ti)
+                    acc[ni][ti] = VEC ? __builtin_amdgcn_mfma_f32_32x32x2f32(fw[s & 1][ni][e], ft[s & 1][ti][e], acc[ni][ti], 0, 0, 0)
+                                      : __builtin_amdgcn_mfma_f32_32x32x2f32(ft[s & 1][ti][e], fw[s & 1][ni][e], acc[ni][ti], 0, 0, 0);
+    };
     // Chunk c, in LDS half c % 2 (and, until it was stored there, register set c % SETS).  Where a wave has one
     // 32 x 32 tile the fragments of a step are requested before the products of the step before it; four tiles
     // give the compiler enough products between two steps' reads.
@@ -253,30 +273,15 @@ __global__ __launch_bounds__(64 * WT * WN * KS, TT * TN > 1 ? 2 : 4) void genera
         constexpr int S = decltype(set)::value;
         constexpr bool AHEAD = L::SETS == 2;
         const float* const tok_s = gsm + S * L::STAGE;
-        const float* const wgt_s = tok_s + L::TOK_STAGE;
-        f32x4 fw[2][TN], ft[2][TT];
-        auto read = [&](int s) {
-            const int k = kg * KPG + 8 * s + 4 * lhi;
-#pragma unroll
-            for (int ni = 0; ni < TN; ++ni) fw[s & 1][ni] = frag(wgt_s, L::WGT_PITCH, L::WGT_KC, (wn * TN + ni) * 32 + l31, k);
-#pragma unroll
-            for (int ti = 0; ti < TT; ++ti) ft[s & 1][ti] = frag(tok_s, L::TOK_PITCH, L::TOK_KC, (wt * TT + ti) * 32 + l31, k);
-        };
-        if (AHEAD) read(0);
+        if (AHEAD) read(tok_s, 0);
         load_chunk(std::integral_constant<int, (S + L::SETS) % 2>{}, c + L::SETS);
 #pragma unroll
         for (int s = 0; s < KPG / 8; ++s) {
-            if (!AHEAD) read(s);
-            else if (s + 1 < KPG / 8) read(s + 1);
+            if (!AHEAD) read(tok_s, s);
+            else if (s + 1 < KPG / 8) read(tok_s, s + 1);
             else store_chunk(std::integral_constant<int, 1 - S>{});   // into the half of chunk c - 1, free since the last barrier
             if (AHEAD) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-                    for (int ti = 0; ti < TT; ++ti)
-                        acc[ni][ti] = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[s & 1][ni][e], ft[s & 1][ti][e], acc[ni][ti], 0, 0, 0);
+            multiply(s);
             if (AHEAD) __builtin_amdgcn_sched_barrier(0);
         }
         if (!AHEAD) store_chunk(std::integral_constant<int, 1 - S>{});
@@ -285,17 +290,33 @@ __global__ __launch_bounds__(64 * WT * WN * KS, TT * TN > 1 ? 2 : 4) void genera
     const std::integral_constant<int, 0> set0;
     const std::integral_constant<int, 1> set1;
     load_chunk(set0, 0);
-    if (L::SETS == 2) load_chunk(set1, 1);
-    store_chunk(set0);
-    __syncthreads();
-    // (one way round the loop only, so that the compiler's count of loads in flight is exact)
-    if (n_chunks > 0)
+    if constexpr (L::STAGES == 1) {
+        // a chunk or a few: as little code as there can be (a launch of one chunk pays for fetching it)
         for (int c = 0;;) {
-            iteration(set0, c);
-            if (++c >= n_chunks) break;
-            iteration(set1, c);
-            if (++c >= n_chunks) break;
+            store_chunk(set0);
+            __syncthreads();
+            if (++c < n_chunks) load_chunk(set0, c);
+#pragma unroll
+            for (int s = 0; s < KPG / 8; ++s) {
+                read(gsm, s);
+                multiply(s);
+            }
+            if (c >= n_chunks) break;
+            __syncthreads();
         }
+    } else {
+        if (L::SETS == 2) load_chunk(set1, 1);
+        store_chunk(set0);
+        __syncthreads();
+        // (one way round the loop only, so that the compiler's count of loads in flight is exact)
+        if (n_chunks > 0)
+            for (int c = 0;;) {
+                iteration(set0, c);
+                if (++c >= n_chunks) break;
+                iteration(set1, c);
+                if (++c >= n_chunks) break;
+            }
+    }
 
     if constexpr (KS > 1) {
         auto slot = [&](int s) { return gsm + ((s - 1) * WT * WN + w) * (TT * TN * 16 * 64) + lane; };
@@ -322,60 +343,78 @@ __global__ __launch_bounds__(64 * WT * WN * KS, TT * TN > 1 ? 2 : 4) void genera
         }
     }
 
-    // a lane holds columns 8 rg + 4 lhi .. + 3 of row l31 of each 32 x 32 tile
+    if constexpr (VEC) {
+        // a lane holds columns 8 rg + 4 lhi .. + 3 of row l31 of each 32 x 32 tile
 #pragma unroll
-    for (int ti = 0; ti < TT; ++ti) {
-        const int row = (wt * TT + ti) * 32 + l31;
-        if (row >= rows_left) continue;
-        const InT* const a_row = tok + (m0 + row) * p.ld_tok + off;        // Forward: the row's window
-        OutT* const o_row = (OutT*)p.out + (m0 + row) * p.ld_out + n0;
+        for (int ti = 0; ti < TT; ++ti) {
+            const int row = (wt * TT + ti) * 32 + l31;
+            if (row >= rows_left) continue;
+            const InT* const a_row = tok + (m0 + row) * p.ld_tok + off;    // Forward: the row's window
+            OutT* const o_row = (OutT*)p.out + (m0 + row) * p.ld_out + n0;
 #pragma unroll
-        for (int ni = 0; ni < TN; ++ni)
+            for (int ni = 0; ni < TN; ++ni)
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-                const int col = (wn * TN + ni) * 32 + rg * 8 + lhi * 4;
-                const float e0 = acc[ni][ti][rg * 4 + 0], e1 = acc[ni][ti][rg * 4 + 1];
-                const float e2 = acc[ni][ti][rg * 4 + 2], e3 = acc[ni][ti][rg * 4 + 3];
-                f32x4 v = {e0, e1, e2, e3};
-                if constexpr (VEC) {
+                for (int rg = 0; rg < 4; ++rg) {
+                    const int col = (wn * TN + ni) * 32 + rg * 8 + lhi * 4;
                     if (col >= cols_left) continue;                        // widths are multiples of four
+                    const float e0 = acc[ni][ti][rg * 4 + 0], e1 = acc[ni][ti][rg * 4 + 1];
+                    const float e2 = acc[ni][ti][rg * 4 + 2], e3 = acc[ni][ti][rg * 4 + 3];
+                    f32x4 v = {e0, e1, e2, e3};
                     if (P == Product::Forward && p.ident) {
                         const f32x4 id = *(const f32x4*)(a_row + (int)((n0 - p.col_start[g] + col) % p.d_h));
 #pragma unroll
                         for (int e = 0; e < 4; ++e) v[e] += id[e];
                     }
                     *(f32x4*)(o_row + col) = v;
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if (col + e >= cols_left) continue;
-                        float s = v[e];
-                        if (P == Product::Forward && p.ident) s += load_as_f32(a_row + (int)((n0 - p.col_start[g] + col + e) % p.d_h));
-                        store_from_f32(o_row + col + e, s);
-                    }
                 }
-            }
+        }
+    } else {
+        // a lane holds rows 8 rg + 4 lhi + e of column l31: one store is two rows of 32 consecutive elements (with the
+        // VEC kernels' order an element of each of 32 rows: bf16, 8192 x 8001 over 8 elements 299 us against 57)
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) {
+            const int col = (wn * TN + ni) * 32 + l31;
+            if (col >= cols_left) continue;
+            const int j = P == Product::Forward && p.ident ? (int)((n0 - p.col_start[g] + col) % p.d_h) : 0;
+            const InT* const a_col = tok + m0 * p.ld_tok + off + j;        // Forward: the column of the window
+            OutT* const o_col = (OutT*)p.out + m0 * p.ld_out + n0 + col;
+#pragma unroll
+            for (int ti = 0; ti < TT; ++ti)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int row = (wt * TT + ti) * 32 + (r >> 2) * 8 + lhi * 4 + (r & 3);
+                    if (row >= rows_left) continue;
+                    float v = acc[ni][ti][r];
+                    if (P == Product::Forward && p.ident) v += load_as_f32(a_col + row * p.ld_tok);
+                    store_from_f32(o_col + row * p.ld_out, v);
+                }
+        }
     }
 }
 
 // ---------------------------------------------------------------------------------------------
 // Launch.  Workgroup tiles, in 32 x 32 units per wave, waves, k-groups and contraction elements per group and
-// chunk (VEC kernels; the element-wise ones have the second and the last):
+// chunk (VEC kernels; the element-wise ones have 64 x 64 and 32 x 32 with two and eight groups, and the short one):
 //   0   128 x 128   2 x 2 per wave, 2 x 2 waves, 2 groups of 32
 //   1    64 x  64   1 x 1, 2 x 2, 2 groups of 32
 //   2    64 x  32   1 x 1, 2 x 1, 4 groups of 16
 //   3    32 x  32   1 x 1, 1 x 1, 8 groups of 16
+//   4    64 x  64   1 x 1, 2 x 2, 1 group of 16: contractions of at most one chunk of the others
 // ---------------------------------------------------------------------------------------------
-constexpr int kGeneralTiles = 4;
-constexpr int kGeneralBT[kGeneralTiles] = {128, 64, 64, 32}, kGeneralBN[kGeneralTiles] = {128, 64, 32, 32};
+constexpr int kGeneralTiles = 4, kGeneralShort = 4, kGeneralShortLen = 64;
+constexpr int kGeneralBT[] = {128, 64, 64, 32, 64}, kGeneralBN[] = {128, 64, 32, 32, 64};
 
 // The tile with the least time over the 256 compute units: rounds x matrix time x a factor for what the smaller
 // ones spend beside it.  Measured, us (float32, 4096 tokens, d_c = 512, d_h = 64, N = 1024; tiles 0 / 1 / 2 / 3):
 // forward (256 .. 4096 tiles) 42 / 46 / 53 / 71, latent gradient (128 .. 2048) 82 / 55 / 63 / 74, weight gradient
 // (32 .. 448) 280 / 87 / 51 / 48; one token, forward 34 / 13 / 9.4 / 7.8.
+// Up to 64 contraction elements the k-groups have nothing to share and a launch is its loads and stores.  Short
+// tile against the best of the others (geometric means over outputs of 1 x 64 .. 8192 x 8001; float32 in 16-byte
+// pieces / element by element): 8 elements 0.79 / 0.61, 32 0.91 / 0.76, 64 0.96 / 0.89, 100 1.04 / 0.91, 128 1.17 / 1.05.
 constexpr double kGeneralCost[kGeneralTiles] = {1.4, 1.6, 1.8, 2.2};
-inline int general_tile(int64_t rows, const int64_t* group_cols, int G, bool vec)
+inline int general_tile(int64_t rows, int64_t len, const int64_t* group_cols, int G, bool vec)
 {
+    if (len <= kGeneralShortLen) return kGeneralShort;
     int best = 0;
     double best_cost = 0.0;
     for (int i = 0; i < kGeneralTiles; ++i) {
@@ -419,8 +458,10 @@ auto with_general_tile(F&& f)
                                            std::integral_constant<int, 2>{}, std::integral_constant<int, 2>{}, std::integral_constant<int, 32>{});
     else if constexpr (TILE == 2) return f(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{},
                                            std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{}, std::integral_constant<int, 16>{});
-    else return f(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{},
-                  std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{}, std::integral_constant<int, 16>{});
+    else if constexpr (TILE == 3) return f(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{},
+                                           std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{}, std::integral_constant<int, 16>{});
+    else return f(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{},
+                  std::integral_constant<int, 2>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{});
 }
 
 // Workgroups of a launch: one per tile (a few more where they do not fit one grid dimension).
@@ -448,17 +489,19 @@ int launch_general_typed(GeneralArgs& a, const int64_t* group_cols, int G, Launc
 {
     bool vec = false;
     if constexpr (std::is_same_v<InT, float>) vec = general_vec(a, P, group_cols, G);
-    const int tile = general_tile(a.rows, group_cols, G, vec);
+    const int tile = general_tile(a.rows, a.len, group_cols, G, vec);
     general_tiles(a, group_cols, G, tile);
     if constexpr (std::is_same_v<InT, float>)
         if (vec) {
             if (tile == 0) return launch_general_tile<P, InT, OutT, true, 0>(launch);
             if (tile == 1) return launch_general_tile<P, InT, OutT, true, 1>(launch);
             if (tile == 2) return launch_general_tile<P, InT, OutT, true, 2>(launch);
-            return launch_general_tile<P, InT, OutT, true, 3>(launch);
+            if (tile == 3) return launch_general_tile<P, InT, OutT, true, 3>(launch);
+            return launch_general_tile<P, InT, OutT, true, 4>(launch);
         }
     if (tile == 1) return launch_general_tile<P, InT, OutT, false, 1>(launch);
-    return launch_general_tile<P, InT, OutT, false, 3>(launch);
+    if (tile == 3) return launch_general_tile<P, InT, OutT, false, 3>(launch);
+    return launch_general_tile<P, InT, OutT, false, 4>(launch);
 }
 
 // Fills in the tile grid of `a` and calls `launch` with the kernel for these types.

@@ -97,16 +97,16 @@ def test_backward_general_kernels(dtype):
         _check(33, 64, 16, [2], [8], dtype, grad_dtype=wl.F32)
 
 
-# The general kernel's tiles (128 x 128 .. 32 x 32), each product's remainders in rows, columns and contraction,
-# windows that differ between groups, and sizes at which 16-byte pieces do not apply (odd head width or pitch).
+# The general kernel: each product's remainders in rows, columns and contraction, windows that differ between groups,
+# and sizes at which 16-byte pieces do not apply (odd head width or pitch).  (Every tile: test_general_kernel_every_tile.)
 GENERAL_SHAPES = [
     (1, 96, 32, [1, 2], [0, 64], 0),            # one token: 32 x 32 tiles, contractions below and above one chunk
     (31, 512, 64, [8, 8], [0, 448], 0),
     (33, 132, 20, [3, 2], [4, 112], 0),         # d_h not a multiple of 32 or 16
     (700, 512, 64, [8, 8], [448, 128], 4),
-    (1030, 160, 80, [13, 4], [16, 0], 0),       # 64 x 32 and 64 x 64 tiles, cut
+    (1030, 160, 80, [13, 4], [16, 0], 0),       # 64 x 32 and 32 x 32 tiles, cut
     (2050, 288, 96, [12, 11], [0, 192], 0),
-    (4100, 256, 128, [7, 6], [128, 32], 0),     # 128 x 128 tiles, cut
+    (4100, 256, 128, [7, 6], [128, 32], 0),     # gradients of 64 x 32 tiles, cut
     (130, 97, 33, [2, 1], [5, 31], 0),          # element by element
     (900, 128, 64, [9, 9], [0, 64], 1),
 ]
@@ -123,6 +123,82 @@ def test_float32_general_kernel_tiles(T, d_c, d_h, H, offs, pad):
     assert_parity(got, oracle.kv_project(c64, C64, d_h, H, offs), d_h, wl.F32, wl.F32, f"forward T={T} d_c={d_c} d_h={d_h}")
     raw = raw.cpu().numpy()
     assert np.all(raw[T:] == 7.5) and np.all(raw[:, N:] == 7.5)
+
+
+def _general_tile(rows, contraction, H, d_h, dtype, vec):
+    """Tile of the general kernel for a product of these extents.  All three products choose by the same rule, so the
+    launch plan of a forward with the same output and contraction tells the gradients' tiles (contraction rounded up
+    to a multiple of four, which keeps 16-byte pieces possible; an odd pitch rules them out)."""
+    contraction = (contraction + 3) // 4 * 4
+    p = bda.bda_kv_project_plan(rows, contraction + d_h, d_h, H, [0] * len(H), dtype,
+                                ldC=None if vec else sum(H) * d_h + 1)
+    assert p["kernel"] == bda.KERNEL_GENERAL
+    return p["tile_tokens"], p["tile_columns"], p["threads"]
+
+
+T128, T64, T64x32, T32, SHORT = (128, 128, 512), (64, 64, 512), (64, 32, 512), (32, 32, 512), (64, 64, 256)
+_VEC = [
+    # product, tile, T, d_c, d_h, H, offs: cut rows, columns and contraction, one round of the tile over the compute units
+    ("forward", T128, 1990, 136, 64, [15, 15], [0, 72]),
+    ("forward", T64, 990, 144, 60, [8, 8], [8, 0]),
+    ("forward", T64x32, 990, 144, 60, [3, 5], [8, 84]),
+    ("forward", T32, 290, 144, 60, [3, 5], [8, 84]),
+    ("latent", T128, 7990, 476, 40, [1, 1], [4, 436]),
+    ("latent", T64, 1990, 476, 40, [1, 1], [4, 436]),
+    ("latent", T64x32, 990, 476, 40, [1, 1], [0, 100]),
+    ("latent", T32, 290, 476, 40, [2, 1], [0, 100]),
+    ("weight", T128, 70, 536, 40, [101, 99], [4, 496]),
+    ("weight", T64, 70, 536, 40, [26, 24], [4, 496]),
+    ("weight", T64x32, 333, 536, 40, [13, 12], [0, 60]),
+    ("weight", T32, 333, 536, 40, [5, 6], [0, 60]),
+    # short contractions: below, at and above a chunk of 16, up to the limit of 64
+    ("forward", SHORT, 130, 60, 40, [3, 2], [0, 20]),
+    ("forward", SHORT, 70, 104, 40, [3, 2], [0, 64]),
+    ("forward", SHORT, 1, 12, 8, [9], [4]),
+    ("latent", SHORT, 130, 84, 20, [1, 2], [0, 64]),
+    ("latent", SHORT, 300, 512, 64, [1], [128]),
+    ("weight", SHORT, 1, 104, 40, [3, 2], [0, 64]),
+    ("weight", SHORT, 17, 536, 40, [13, 12], [0, 60]),
+    ("weight", SHORT, 64, 200, 72, [5, 2], [12, 100]),
+]
+# element by element (an odd pitch): 64 x 64, 32 x 32 and the short tile
+_ELEM = [
+    ("forward", T64, 990, 144, 60, [8, 8], [8, 0]),
+    ("forward", T32, 290, 143, 60, [3, 5], [7, 83]),
+    ("forward", SHORT, 130, 61, 40, [3, 2], [0, 21]),
+    ("forward", SHORT, 66, 34, 33, [3], [1]),
+    ("latent", T64, 1990, 476, 40, [1, 1], [3, 436]),
+    ("latent", T32, 290, 475, 41, [1, 1], [3, 434]),
+    ("latent", SHORT, 130, 83, 21, [1, 2], [0, 62]),
+    ("weight", T64, 70, 536, 40, [26, 24], [3, 496]),
+    ("weight", T32, 333, 535, 41, [5, 6], [0, 60]),
+    ("weight", SHORT, 1, 103, 41, [3, 2], [0, 62]),
+    ("weight", SHORT, 33, 535, 41, [13, 12], [0, 60]),
+]
+
+
+@pytest.mark.parametrize("product,tile,T,d_c,d_h,H,offs,dtype,grad_dtype,pad",
+                         [c + (wl.F32, wl.F32, 4) for c in _VEC] +
+                         [c + (d, g, 1) for c in _ELEM for d, g in ((wl.F32, wl.F32), (wl.F16, wl.F16), (wl.BF16, wl.F32))])
+def test_general_kernel_every_tile(product, tile, T, d_c, d_h, H, offs, dtype, grad_dtype, pad):
+    """Each product with each tile of its rule, in 16-byte pieces and element by element; the rest of the padded rows
+    stays as it was.  Tolerance as in test_float32_general_kernel_tiles."""
+    N, K, vec = sum(H) * d_h, d_c - d_h, pad % 4 == 0
+    (c_s, c64), (g_s, g64), (C_s, C64) = _inputs(7, T, d_c, d_h, H, dtype)
+    what = f"{product} tile={tile} T={T} d_c={d_c} d_h={d_h} H={H} dtype={dtype}/{grad_dtype}"
+    if product == "forward":
+        assert _general_tile(T, K, H, d_h, dtype, vec) == tile, what
+        got, raw = gh.kv_project(c_s, C_s, d_c, d_h, H, offs, dtype, grad_dtype, ldc=d_c + pad, ldC=N + pad, ld_out=N + pad, fill=7, extra_rows=1)
+        assert_parity(got, oracle.kv_project(c64, C64, d_h, H, offs), d_h, dtype, grad_dtype, what)
+        raw = raw.cpu().numpy()
+        assert np.all(raw[T:] == 7) and np.all(raw[:, N:] == 7), what
+        return
+    latent = product == "latent"
+    assert _general_tile(T if latent else K, N if latent else T, [1] if latent else H, d_c if latent else d_h, dtype, vec) == tile, what
+    ref_c, ref_C = oracle.kv_project_backward(c64, g64, C64, d_h, H, offs)
+    gc, gC, gc_d, gC_d = _backward(c_s, g_s, C_s, T, d_c, d_h, H, offs, dtype, grad_dtype, pad, want=(latent, not latent), fill=7)
+    assert_parity(gc if latent else gC, ref_c if latent else ref_C, 1, dtype, grad_dtype, what)
+    assert torch.all(gc_d[:, d_c:] == 7) if latent else torch.all(gC_d[:, N:] == 7), what
 
 
 def test_backward_tile_shapes_chosen_by_size():
