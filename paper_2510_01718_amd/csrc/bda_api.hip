@@ -359,29 +359,41 @@ bool lean_kernel_applies(const GemmArgs& a, int G, const int64_t* group_cols)
     return ok && a.K / 64 + id_stages >= 3;
 }
 
-// Tile of gemm_mid_kernel (64 or 128 square) for a launch that the lean kernel does not take, or 0.  Below 96 tiles of
-// 256 x 256 the alternative is the register-staged kernel, slower at every size measured (us, bf16; 64 x 64 tiles
-// against it): T = 1500, K = 288, N = 2304 14.5 / 22.7; T = 1500, K = 608, N = 2176 17.5 / 35.9; T = 300, K = 320,
-// N = 5760 8.5 / 20.7; T = 3001, K = 384, N = 256 6.4 / 23.4.  From 96 up it is the streaming kernel, whose round of
+// Tile of gemm_mid_kernel (64 or 128 square) for a launch that the lean kernel does not take, or 0.
+// From 96 tiles of 256 x 256 up the alternative is the streaming kernel, whose round of
 // tiles takes about 10 + 0.025 K us however few tiles are in it (K = 160 14, 288 17, 416 21, 608 25); the 64 x 64
 // tiles take about 5 us and at most 0.0075 + 1.4e-5 K us each (T = 3001, N = 2304, K = 288: 23 / 32, two rounds; T = 3001,
-// N = 4096, K = 416: 40 / 23.5, one round; T = 1024, N = 9000, K = 4096: 184 / 118).  Launches of at most 128 columns keep the 128 x 128 tiles that their
-// launch plan has always reported (T = 3001, K = 384, N = 256: 11.7).
+// N = 4096, K = 416: 40 / 23.5, one round; T = 1024, N = 9000, K = 4096: 184 / 118).
+// Below that it is the register-staged kernel with 128 x 128 tiles.  Up to 512 tiles (two workgroups on every compute
+// unit) the 64 x 64 tiles were never slower (us, bf16, against it: T = 300, K = 320, N = 5760 8.5 / 20.7; T = 8192, K = 32,
+// N = 32 5.1 / 5.7; T = 4096, K = 288, N = 128 5.8 / 12.0).  Beyond, their number costs more than the other kernel's waits
+// where the contraction is short (T = 2048, K = 64, N = 2592: 14.7 / 11.8) and less where it is long (T = 1500, K = 608,
+// N = 2176: 17.5 / 35.9): the two estimates are fits over 460 such launches of K 8 .. 416, 6 and 7 % off at the root mean square.
+// At most 128 columns and K >= 384: 128 x 128 tiles, which such a launch has always reported as its plan; faster than the
+// register-staged kernel there, but not as fast as 64 x 64 tiles (T = 4096, K = 416, N = 128: 11.6 us, 14.3 and 6.3).
 int mid_tile(const GemmArgs& a, int G, const int64_t* group_cols, bool big)
 {
     int64_t N = 0, nt64 = 0;
     for (int g = 0; g < G; ++g) { N += group_cols[g]; nt64 += (group_cols[g] + 63) / 64; }
-    if ((a.M + 63) / 64 * nt64 > (1 << 22)) return 0;   // a workgroup of 512 per tile: 2^31 of the 2^32 work-items a launch may have
+    const int64_t tiles = (a.M + 63) / 64 * nt64;
+    if (tiles > (1 << 22)) return 0;   // a workgroup of 512 per tile: 2^31 of the 2^32 work-items a launch may have
+    GemmArgs s = a;
+    const int bt = big ? 256 : 128;
+    build_tiles(s, G, group_cols, bt, bt);
+    choose_super(s, big ? kSlotsPerXcd : 2 * kSlotsPerXcd, bt, bt);
+    const int64_t supers = (int64_t)((s.m_tiles + s.sm - 1) / s.sm) * ((s.n_tiles + s.sn - 1) / s.sn);
+    const double rounds = (double)((supers + kNumXcd - 1) / kNumXcd);
     if (big) {
-        GemmArgs s = a;
-        build_tiles(s, G, group_cols, 256, 256);
-        choose_super(s, kSlotsPerXcd, 256, 256);
-        const int64_t supers = (int64_t)((s.m_tiles + s.sm - 1) / s.sm) * ((s.n_tiles + s.sn - 1) / s.sn);
-        const double stream = (double)((supers + kNumXcd - 1) / kNumXcd) * (10.0 + 0.025 * a.K);
-        const double mid = 5.0 + (double)((a.M + 63) / 64 * nt64) * (0.0075 + 1.4e-5 * a.K);
+        const double stream = rounds * (10.0 + 0.025 * a.K);
+        const double mid = 5.0 + (double)tiles * (0.0075 + 1.4e-5 * a.K);
         return mid < 0.95 * stream ? 64 : 0;
     }
-    return N <= 128 ? 128 : 64;
+    if (N <= 128 && a.K >= 384) return 128;
+    if (tiles <= 512) return 64;
+    const int chunks = (a.K + 63) / 64, id_chunks = a.ident ? ((a.d_h % 128 == 0 ? 128 : a.d_h) + 63) / 64 : 0;
+    const double staged = 2.6 + 0.0037 * s.m_tiles * s.n_tiles + rounds * (0.96 * chunks + 0.7 * id_chunks + (kNumXcd * s.sm * s.sn > 256 ? 6.0 : 3.0));
+    const double mid = 4.3 + (double)tiles * (0.0041 + 0.00086 * chunks + (a.ident ? 0.002 : 0.0));
+    return mid < staged ? 64 : 0;
 }
 
 int run_gemm(GemmArgs& a, int G, const int64_t* group_cols, int dtype, int out_dtype, hipStream_t st)

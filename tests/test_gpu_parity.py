@@ -494,6 +494,53 @@ def test_lowrank_linear_small(last, dtype):
     assert_parity(got[:, rest], ref2, lw.d_out - lw.r, dtype, dtype, "lowrank h C from the stored h")
 
 
+# Launches without an identity slice beyond the few-token kernels' range: column counts that end 8, 24, 40 and 56
+# columns into a 64-column tile (and in a wave's second 32), contractions of one chunk, of a partial one, of two halves.
+MID64, MID128, STAGED = (64, 64, 512), (128, 128, 512), (128, 128, 256)
+
+
+@pytest.mark.parametrize("dtype,out_dtype", [(wl.F16, wl.F16), (wl.BF16, wl.F32)])
+@pytest.mark.parametrize("T,K,N,tile", [(1100, 96, 1096, MID64), (1500, 40, 536, MID64), (1090, 328, 360, MID64), (2100, 136, 248, MID64),
+                                        (1030, 8, 8, MID64), (1537, 392, 120, MID128), (1100, 456, 88, MID128), (2048, 64, 2600, STAGED)])
+def test_dense_project_small_tiles(T, K, N, tile, dtype, out_dtype):
+    p = bda.bda_dense_project_plan(T, K, N, dtype, out_dtype, ldc=K + 8, ldW=N + 16, ld_out=N + 8)
+    assert (p["kernel"], (p["tile_tokens"], p["tile_columns"], p["threads"])) == (bda.KERNEL_MFMA, tile), p
+    rng = np.random.default_rng([T, K, N])
+    c_s, c64 = wl.to_storage(rng.standard_normal((T, K)), dtype)
+    W_s, W64 = wl.to_storage(0.25 * rng.standard_normal((K, N)), dtype)
+    c_d, W_d, out_d = gh.to_device(c_s, dtype, K + 8), gh.to_device(W_s, dtype, N + 16), gh.new_out(T + 2, N + 8, out_dtype, fill=3)
+    bda.bda_dense_project(c_d, K + 8, T, K, W_d, N + 16, N, out_d, N + 8, dtype, out_dtype, gh.stream())
+    torch.cuda.synchronize()
+    assert_parity(gh.to_host64(out_d[:T], out_dtype, N), oracle.dense_project(c64, W64), N, dtype, out_dtype, f"T={T} K={K} N={N}")
+    raw = out_d.cpu().numpy()
+    assert np.all(raw[T:] == 3) and np.all(raw[:, N:] == 3)
+
+
+@pytest.mark.parametrize("last", [False, True])
+@pytest.mark.parametrize("dtype", [wl.F16, wl.BF16])
+@pytest.mark.parametrize("T,d_in,r,d_out", [(1100, 200, 72, 208), (1537, 136, 104, 704), (1040, 248, 56, 96)])
+def test_lowrank_linear_small_tiles(T, d_in, r, d_out, dtype, last):
+    """Both products through the 64 x 64 tiles, h read back from the padded output."""
+    lw = wl.lowrank_workload(T=T, d_in=d_in, r=r, d_out=d_out, dtype=dtype, seed=25)
+    Up, C, off, _ = oracle.prepare_lowrank(lw.U, lw.V, mode=oracle.LAST if last else oracle.FIRST)
+    Up_s, Up64 = wl.to_storage(Up, dtype)
+    C_s, C64 = wl.to_storage(C, dtype)
+    ld = d_out + 8
+    for K, N in ((d_in, r), (r, d_out - r)):
+        p = bda.bda_dense_project_plan(T, K, N, dtype, ldc=d_in if K == d_in else ld, ld_out=ld)
+        assert (p["kernel"], p["tile_tokens"], p["threads"]) == (bda.KERNEL_MFMA, 64, 512), p
+    x_d, U_d, C_d = gh.to_device(lw.x_stored, dtype), gh.to_device(Up_s, dtype), gh.to_device(C_s, dtype)
+    out_d = gh.new_out(T + 1, ld, dtype, fill=5)
+    bda.bda_lowrank_linear(x_d, d_in, T, d_in, r, d_out, off, U_d, C_d, out_d, ld, dtype, gh.stream())
+    torch.cuda.synchronize()
+    got = gh.to_host64(out_d[:T], dtype, d_out)
+    assert_parity(got[:, off:off + r], oracle.dense_project(lw.x, Up64), r, dtype, dtype, "h block")
+    rest = np.concatenate([np.arange(0, off), np.arange(off + r, d_out)])
+    assert_parity(got[:, rest], oracle.dense_project(got[:, off:off + r], C64), d_out - r, dtype, dtype, "h C from the stored h")
+    raw = out_d.cpu().numpy()
+    assert np.all(raw[T:] == 5) and np.all(raw[:, d_out:] == 5)
+
+
 # ------------------------------------------------------------------------------------ full benchmark sizes
 NAN_FILL = {wl.F16: float("nan"), wl.F32: float("nan"), wl.BF16: 0x7FC0}     # bf16 buffers are int16 bit patterns
 

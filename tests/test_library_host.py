@@ -360,3 +360,16 @@ def test_launch_plan_of_very_many_tokens_fits_a_launch(T, H, d_c, d_h):
     (T x 64 latent values of 16 bits are 77 GB at 600 M tokens, which one GPU holds)."""
     p = _plan(T, H, [0] * len(H), bda.BDA_BF16, d_c=d_c, d_h=d_h)
     assert p["kernel"] != bda.KERNEL_NONE and p["workgroups"] * p["threads"] < 2 ** 32, p
+
+
+def test_launch_plan_many_small_tiles_of_a_short_contraction():
+    """Outside the lean kernel's shapes: 64 x 64 tiles while two rounds of the compute units hold them, beyond that by
+    the contraction; 128 x 128 tiles of one workgroup per slot where it is short."""
+    def shape(T, K, N, **kw):
+        p = bda.bda_dense_project_plan(T, K, N, bda.BDA_BF16, **kw)
+        return p["tile_tokens"], p["threads"]
+    assert shape(8192, 32, 32) == shape(16384, 8, 96) == (64, 512)            # 128 and 512 tiles
+    assert shape(2048, 64, 2600) == shape(4096, 8, 776) == (128, 256)         # 1312 and 832 tiles
+    assert shape(2048, 416, 1544) == (64, 512)                                # 800 tiles, seven chunks each
+    p = _plan(2048, [40, 41], [0, 64], bda.BDA_BF16, d_c=96, d_h=32)
+    assert (p["kernel"], p["tile_tokens"], p["threads"]) == (bda.KERNEL_MFMA, 128, 256)
