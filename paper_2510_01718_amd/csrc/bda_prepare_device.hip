@@ -77,7 +77,7 @@ template <> __device__ __forceinline__ void store_rounded<__bf16>(void* p, int64
 }
 
 constexpr int kPrepThreads = 256;
-constexpr int kPrepLdsDh = 128;               // largest head width whose basis block is inverted in LDS
+constexpr int kPrepLdsDh = 128;               // largest head width whose basis block is inverted in registers (invert_kernel)
 constexpr int kPrepMaxDh = 256;               // largest head width at all (block in the workspace)
 constexpr int kPrepRows = 16;                 // rows of W_h[Bbar,:] staged per pass
 constexpr int kMaxCandidates = 256;
@@ -102,7 +102,7 @@ struct PrepArgs {
     int w_type, c_type;          // element types of W / side and of C / side_out
     int per_row;                 // O: pieces of d_h columns in a row of the companion output (see Slot)
     uint32_t per_row_magic;
-    int write_side, measure;     // strip_kernel: store the companion block / sum the reconstruction errors
+    int write_side, measure;     // strip_kernel: store the companion block; sum the reconstruction errors
 };
 
 // Start of window `z` of this launch, or -1.
@@ -699,17 +699,26 @@ __global__ __launch_bounds__(kPrepThreads) void residual_kernel(const PrepArgs a
 // LDS (any window's columns of them are the row operand).  What a window costs is then only its own product
 // 32 x (d_c - d_h) x d_h, whose column operand - the rows of the stored Chat - comes from the L2.
 //
-// 8 waves; wave w owns the 16-column tiles w, w + 8, ... of P, both 16-row tiles of each.  Contraction in
+// Wave w of nw owns the 16-column tiles w, w + nw, ... of P, both 16-row tiles of each.  Contraction in
 // blocks of 32: lane group g takes elements 8 g .. 8 g + 7 of a block (one wide load), element s of each
 // group in step s - the same order for both operands, so it is only the order of the sum that changes.
 // Each lane adds its squares in a fixed order, the lanes of a wave, the waves and (in select_kernel) the
 // parts of a head likewise: the result does not depend on scheduling or on how windows are batched.
 // Bound: the double-precision matrix rate.  Against a companion kernel and an error kernel that formed all
 // three products per window in vector FMAs fed from LDS (0.05 + 0.35 ms per window for 16 heads of 128,
-// d_c 512, d_side 2048): a 25-window search of keys and values 27.5 -> 8.2 ms, two windows for 128 heads 5.4 -> 2.2 ms; with a block's row operand read once for all tiles, the column operands
-// fetched a block ahead and contiguous for W_o too, 7.0 ms (46 TFLOP/s while a window is measured).
+// d_c 512, d_side 2048): a 25-window search of keys and values 27.5 -> 8.2 ms, two windows for 128 heads
+// 5.4 -> 2.2 ms; with a block's row operand read once for all tiles, the column operands fetched a block
+// ahead and contiguous for W_o too, 7.0 ms (46 TFLOP/s while a window is measured).
+// A wave holds up to 256 registers of tiles, so a compute unit takes eight waves: with narrow latents or
+// heads they must be several workgroups, or most of them have no tile (one form of eight waves for all: 120
+// heads of 16, d_c 80, d_side 2048, one window, 160 us against 69 with the vector FMAs; 56 now).
 // ---------------------------------------------------------------------------------------------
-constexpr int kStripThreads = 512, kStripRows = 32, kStripMaxDc = 512, kStripTiles = kStripMaxDc / 128;
+constexpr int kStripThreads = 512, kStripRows = 32, kStripMaxDc = 512, kStripWaves = kStripThreads / 64;
+
+// Wide: measures, 257 .. 512 latent columns; 8 waves, as many tiles each as their registers hold.  Narrow: measures, up to 256.
+// Window: no measurement, only the tiles that the window meets (of 256 columns at any start: 17).
+enum class StripForm { Wide, Narrow, Window };
+constexpr int strip_tiles(StripForm f) { return f == StripForm::Wide ? kStripMaxDc / 16 / kStripWaves : f == StripForm::Narrow ? 2 : 3; }   // 16-column tiles per wave
 
 template <typename T> __device__ __forceinline__ T rounded(double v)
 {
@@ -747,66 +756,84 @@ __device__ __forceinline__ Eight<T> fetch8(const T* p, int valid, bool vec)
     return r;
 }
 
-__host__ __device__ inline int strip_pitch(int d_c) { return (d_c + 15) / 16 * 16 + 2; }
-inline int strip_lds_bytes(int d_c, int n)
+// Columns of P that a strip keeps (a multiple of 16): all of them to measure windows, or the tiles that one window of
+// any start meets; LDS rows of doubles for them and for the strip of S.
+__host__ __device__ constexpr int strip_width(bool measure, int d_c, int n) { return ((measure ? d_c : n + 15) + 15) / 16 * 16; }
+__host__ __device__ constexpr int strip_pitch_p(int width) { return width + 2; }
+__host__ __device__ constexpr int strip_pitch_s(int n) { return (n + 31) / 32 * 32 + 2; }
+__host__ __device__ constexpr int strip_words(int width, int n)
 {
-    const int a = strip_pitch(d_c), b = (n + 31) / 32 * 32 + 2;
-    return kStripRows * (a > b ? a : b) * (int)sizeof(double);
+    const int p = strip_pitch_p(width), s = strip_pitch_s(n);
+    return kStripRows * (p > s ? p : s);
 }
 
-template <typename WT, typename CT>
+template <typename WT, typename CT, StripForm F>
 __global__ __launch_bounds__(kStripThreads) void strip_kernel(const PrepArgs a)
 {
+    constexpr bool MEASURE = F != StripForm::Window;
+    constexpr int TILES = strip_tiles(F);
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     double* const ph = (double*)smem_raw;      // first the strip of S, then the rounded strip of P
-    __shared__ double s_sum[kStripThreads / 64][kMaxCandidates];
     const int n = a.d_h, d_c = a.d_c, t = threadIdx.x, lane = t & 63, c = lane & 15, g = lane >> 4;
+    const int threads = F == StripForm::Wide ? kStripThreads : blockDim.x, nw = threads >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int h = blockIdx.x;
     const int off0 = window_start(a);
     if (off0 < 0) return;
     const int64_t col0 = (int64_t)h * n;
     const bool q_side = a.side_kind == BDA_SIDE_Q;
-    const int n_blk = (n + 31) >> 5, npk = n_blk * 32, lds_s = npk + 2, lds_p = strip_pitch(d_c);
-    const int z_lo = a.measure ? (int)((int64_t)a.n_cand * blockIdx.z / gridDim.z) : 0;
-    const int z_hi = a.measure ? (int)((int64_t)a.n_cand * (blockIdx.z + 1) / gridDim.z) : 0;
+    const int n_blk = (n + 31) >> 5, npk = n_blk * 32, lds_s = strip_pitch_s(n);
+    const int width = strip_width(MEASURE, d_c, n), lds_p = strip_pitch_p(width);
+    const int base = MEASURE ? 0 : off0 & ~15;                              // first column of P that is kept
+    const int l_end = MEASURE ? d_c : off0 + n;                             // end of the columns needed
+    const int z_lo = MEASURE ? (int)((int64_t)a.n_cand * blockIdx.z / gridDim.z) : 0;
+    const int z_hi = MEASURE ? (int)((int64_t)a.n_cand * (blockIdx.z + 1) / gridDim.z) : 0;
+    double* const sums = ph + strip_words(width, n);                        // [wave][window - z_lo]
+    const int n_z = z_hi - z_lo;
     const WT* const W = (const WT*)a.W;
     const WT* const S = (const WT*)a.side;
     CT* const side_out = (CT*)a.side_out;
     const bool w_vec = n % 8 == 0 && (uintptr_t)W % 16 == 0 && (a.ldw * (int64_t)sizeof(WT)) % 16 == 0;
-    for (int z = lane; z < z_hi - z_lo; z += 64) s_sum[wave][z] = 0.0;
+    for (int z = lane; z < n_z; z += 64) sums[wave * n_z + z] = 0.0;
 
     const int n_strips = (a.d_side + kStripRows - 1) / kStripRows;
     for (int strip = blockIdx.y; strip < n_strips; strip += gridDim.y) {
         const int s0 = strip * kStripRows;
         __syncthreads();                       // the strip before is no longer read
-        if (q_side) {
+        if (q_side && npk == 32) {             // several rows per wave and load; zeros beside the narrow ones
+            const int shift = n <= 4 ? 2 : n <= 8 ? 3 : n <= 16 ? 4 : 5, kw = 1 << shift, k = t & (kw - 1);
+#pragma unroll 4
+            for (int r = t >> shift; r < kStripRows; r += threads >> shift)
+                ph[r * lds_s + k] = (k < n && s0 + r < a.d_side) ? widened<WT>(S[(int64_t)(s0 + r) * a.ld_side + col0 + k]) : 0.0;
+            if (kw < 32)
+                for (int r = t >> 5; r < kStripRows; r += 2 * nw)
+                    if ((t & 31) >= kw) ph[r * lds_s + (t & 31)] = 0.0;
+        } else if (q_side) {
             for (int k = lane; k < npk; k += 64)
-#pragma unroll
-                for (int r = wave; r < kStripRows; r += 8)
+#pragma unroll 4
+                for (int r = wave; r < kStripRows; r += nw)
                     ph[r * lds_s + k] = (k < n && s0 + r < a.d_side) ? widened<WT>(S[(int64_t)(s0 + r) * a.ld_side + col0 + k]) : 0.0;
         } else {
             const int r = t % kStripRows;
 #pragma unroll 4
-            for (int k = t / kStripRows; k < npk; k += kStripThreads / kStripRows)
+            for (int k = t / kStripRows; k < npk; k += threads / kStripRows)
                 ph[r * lds_s + k] = (k < n && s0 + r < a.d_side) ? widened<WT>(S[(col0 + k) * a.ld_side + s0 + r]) : 0.0;
         }
         __syncthreads();
 
-        // ---- P: rows s0 .. s0 + 31, this wave's column tiles (without a measurement only those the window meets) ----
-        f64x4 P[kStripTiles][2];
-        bool live[kStripTiles];
+        // ---- P: rows s0 .. s0 + 31, this wave's column tiles ----
+        f64x4 P[TILES][2];
+        bool live[TILES];
 #pragma unroll
-        for (int j = 0; j < kStripTiles; ++j) {
+        for (int j = 0; j < TILES; ++j) {
             P[j][0] = P[j][1] = (f64x4){0.0, 0.0, 0.0, 0.0};
-            const int l0 = (wave + 8 * j) * 16;
-            live[j] = l0 < d_c && (a.measure || (l0 + 16 > off0 && l0 < off0 + n));
+            live[j] = base + (wave + nw * j) * 16 < l_end;
         }
-        Eight<WT> w[kStripTiles];
+        Eight<WT> w[TILES];
         auto fetch_w = [&](int b) {
 #pragma unroll
-            for (int j = 0; j < kStripTiles; ++j) {
-                const int l = (wave + 8 * j) * 16 + c, k0 = 32 * b + 8 * g;
+            for (int j = 0; j < TILES; ++j) {
+                const int l = base + (wave + nw * j) * 16 + c, k0 = 32 * b + 8 * g;
                 w[j] = fetch8<WT>(W + (int64_t)l * a.ldw + col0 + k0, live[j] && l < d_c ? n - k0 : 0, w_vec);
             }
         };
@@ -815,9 +842,9 @@ __global__ __launch_bounds__(kStripThreads) void strip_kernel(const PrepArgs a)
         for (int b = 0; b < n_blk; ++b) {
             const int k0 = 32 * b + 8 * g;
             if (!kAheadW) fetch_w(b);
-            Eight<WT> now[kStripTiles];
+            Eight<WT> now[TILES];
 #pragma unroll
-            for (int j = 0; j < kStripTiles; ++j) now[j] = w[j];
+            for (int j = 0; j < TILES; ++j) now[j] = w[j];
             if (kAheadW && b + 1 < n_blk) fetch_w(b + 1);
             double av[2][8];
 #pragma unroll
@@ -825,7 +852,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_kernel(const PrepArgs a)
 #pragma unroll
                 for (int s = 0; s < 8; ++s) av[rt][s] = ph[(16 * rt + c) * lds_s + k0 + s];
 #pragma unroll
-            for (int j = 0; j < kStripTiles; ++j)
+            for (int j = 0; j < TILES; ++j)
                 if (live[j]) {
 #pragma unroll
                     for (int s = 0; s < 8; ++s) {
@@ -837,22 +864,22 @@ __global__ __launch_bounds__(kStripThreads) void strip_kernel(const PrepArgs a)
         }
         __syncthreads();                       // the strip of S is no longer read
 #pragma unroll
-        for (int j = 0; j < kStripTiles; ++j) {
-            const int l = (wave + 8 * j) * 16 + c;
+        for (int j = 0; j < TILES; ++j) {
+            const int l = base + (wave + nw * j) * 16 + c;
             if (live[j] && l < d_c) {
 #pragma unroll
                 for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) ph[(16 * rt + 4 * r + g) * lds_p + l] = widened<CT>(rounded<CT>(P[j][rt][r]));
+                    for (int r = 0; r < 4; ++r) ph[(16 * rt + 4 * r + g) * lds_p + l - base] = widened<CT>(rounded<CT>(P[j][rt][r]));
             }
         }
         __syncthreads();
 
         if (a.write_side) {
-            for (int e = t; e < kStripRows * n; e += kStripThreads) {
+            for (int e = t; e < kStripRows * n; e += threads) {
                 const int r = q_side ? e / n : e % kStripRows, i = q_side ? e % n : e / kStripRows;
                 if (s0 + r < a.d_side) {
-                    const CT v = rounded<CT>(ph[r * lds_p + off0 + i]);
+                    const CT v = rounded<CT>(ph[r * lds_p + off0 - base + i]);
                     if (q_side) side_out[(int64_t)(s0 + r) * a.ld_side_out + col0 + i] = v;
                     else side_out[(col0 + i) * a.ld_side_out + s0 + r] = v;
                 }
@@ -861,77 +888,80 @@ __global__ __launch_bounds__(kStripThreads) void strip_kernel(const PrepArgs a)
 
         // ---- the windows: blocks of the contraction outside, this wave's tiles inside, so that a block's row operand is
         // read once for all of them; the column operands are fetched one block ahead, across windows ----
-        Eight<CT> ct[kStripTiles];
-        auto fetch_c = [&](int z, int b) {
-            const int off = window_start(a, z), k0 = 32 * b + 8 * g;
-            const Slot slot = slot_of(a, z);
-            const bool c_vec = n % 8 == 0 && (uintptr_t)slot.p % 16 == 0 && (slot.ld * (int64_t)sizeof(CT)) % 16 == 0;
+        if constexpr (MEASURE) {
+            Eight<CT> ct[TILES];
+            auto fetch_c = [&](int z, int b) {
+                const int off = window_start(a, z), k0 = 32 * b + 8 * g;
+                const Slot slot = slot_of(a, z);
+                const bool c_vec = n % 8 == 0 && (uintptr_t)slot.p % 16 == 0 && (slot.ld * (int64_t)sizeof(CT)) % 16 == 0;
 #pragma unroll
-            for (int j = 0; j < kStripTiles; ++j) {
-                const int l = (wave + 8 * j) * 16 + c;
-                const bool outside = l < d_c && (l < off || l >= off + n);      // (a lane inside the window adds nothing)
-                ct[j] = fetch8<CT>((const CT*)slot.p + slot_row(slot, l < off ? l : l - n, h, n) + k0, outside ? n - k0 : 0, c_vec);
-            }
-        };
-        if (kAheadC && z_lo < z_hi) fetch_c(z_lo, 0);
-        for (int z = z_lo; z < z_hi; ++z) {
-            const int off = window_start(a, z);
-            f64x4 acc[kStripTiles][2];
-#pragma unroll
-            for (int j = 0; j < kStripTiles; ++j) { acc[j][0] = -P[j][0]; acc[j][1] = -P[j][1]; }
-            for (int b = 0; b < n_blk; ++b) {
-                const int k0 = 32 * b + 8 * g;
-                if (!kAheadC) fetch_c(z, b);
-                Eight<CT> now[kStripTiles];
-#pragma unroll
-                for (int j = 0; j < kStripTiles; ++j) now[j] = ct[j];
-                if (kAheadC) {
-                    if (b + 1 < n_blk) fetch_c(z, b + 1);
-                    else if (z + 1 < z_hi) fetch_c(z + 1, 0);
+                for (int j = 0; j < TILES; ++j) {
+                    const int l = (wave + nw * j) * 16 + c;
+                    const bool outside = l < d_c && (l < off || l >= off + n);      // (a lane inside the window adds nothing)
+                    ct[j] = fetch8<CT>((const CT*)slot.p + slot_row(slot, l < off ? l : l - n, h, n) + k0, outside ? n - k0 : 0, c_vec);
                 }
+            };
+            if (kAheadC && z_lo < z_hi) fetch_c(z_lo, 0);
+            for (int z = z_lo; z < z_hi; ++z) {
+                const int off = window_start(a, z);
+                f64x4 acc[TILES][2];
 #pragma unroll
-                for (int half = 0; half < 8; half += 4) {
-                    double av[2][4];
+                for (int j = 0; j < TILES; ++j) { acc[j][0] = -P[j][0]; acc[j][1] = -P[j][1]; }
+                for (int b = 0; b < n_blk; ++b) {
+                    const int k0 = 32 * b + 8 * g;
+                    if (!kAheadC) fetch_c(z, b);
+                    Eight<CT> now[TILES];
 #pragma unroll
-                    for (int rt = 0; rt < 2; ++rt)
+                    for (int j = 0; j < TILES; ++j) now[j] = ct[j];
+                    if (kAheadC) {
+                        if (b + 1 < n_blk) fetch_c(z, b + 1);
+                        else if (z + 1 < z_hi) fetch_c(z + 1, 0);
+                    }
 #pragma unroll
-                        for (int s = 0; s < 4; ++s) av[rt][s] = k0 + half + s < n ? ph[(16 * rt + c) * lds_p + off + k0 + half + s] : 0.0;
+                    for (int half = 0; half < 8; half += 4) {
+                        double av[2][4];
 #pragma unroll
-                    for (int j = 0; j < kStripTiles; ++j) {
-                        const int l0 = (wave + 8 * j) * 16;
-                        if (l0 < d_c && (l0 < off || l0 + 16 > off + n)) {
+                        for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-                            for (int s = 0; s < 4; ++s) {
-                                const double bv = widened<CT>(now[j].e[half + s]);
-                                acc[j][0] = mfma_f64(av[0][s], bv, acc[j][0]);
-                                acc[j][1] = mfma_f64(av[1][s], bv, acc[j][1]);
+                            for (int s = 0; s < 4; ++s) av[rt][s] = k0 + half + s < n ? ph[(16 * rt + c) * lds_p + off + k0 + half + s] : 0.0;
+#pragma unroll
+                        for (int j = 0; j < TILES; ++j) {
+                            const int l0 = (wave + nw * j) * 16;
+                            if (l0 < d_c && (l0 < off || l0 + 16 > off + n)) {
+#pragma unroll
+                                for (int s = 0; s < 4; ++s) {
+                                    const double bv = widened<CT>(now[j].e[half + s]);
+                                    acc[j][0] = mfma_f64(av[0][s], bv, acc[j][0]);
+                                    acc[j][1] = mfma_f64(av[1][s], bv, acc[j][1]);
+                                }
                             }
                         }
                     }
                 }
+                double r2 = 0.0;
+#pragma unroll
+                for (int j = 0; j < TILES; ++j) {
+                    const int l = (wave + nw * j) * 16 + c;
+                    const bool in_window = l >= off && l < off + n;
+#pragma unroll
+                    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            double d = acc[j][rt][r];
+                            if (in_window) d += ph[(16 * rt + 4 * r + g) * lds_p + l];
+                            r2 = fma(d, d, r2);
+                        }
+                }
+                for (int s = 32; s >= 1; s >>= 1) r2 += __shfl_xor(r2, s, 64);
+                if (lane == 0) sums[wave * n_z + z - z_lo] += r2;
             }
-            double r2 = 0.0;
-#pragma unroll
-            for (int j = 0; j < kStripTiles; ++j) {
-                const int l = (wave + 8 * j) * 16 + c;
-                const bool in_window = l >= off && l < off + n;
-#pragma unroll
-                for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        double d = acc[j][rt][r];
-                        if (in_window) d += ph[(16 * rt + 4 * r + g) * lds_p + l];
-                        r2 = fma(d, d, r2);
-                    }
-            }
-            for (int s = 32; s >= 1; s >>= 1) r2 += __shfl_xor(r2, s, 64);
-            if (lane == 0) s_sum[wave][z - z_lo] += r2;
         }
     }
+    if (!MEASURE) return;
     __syncthreads();
-    for (int z = z_lo + t; z < z_hi; z += kStripThreads) {
+    for (int z = z_lo + t; z < z_hi; z += threads) {
         double sum = 0.0;
-        for (int w = 0; w < kStripThreads / 64; ++w) sum += s_sum[w][z - z_lo];
+        for (int w = 0; w < nw; ++w) sum += sums[w * n_z + z - z_lo];
         a.partials[((size_t)(a.cand + z) * a.H + h) * a.n_parts + blockIdx.y] = sum;
     }
 }
@@ -1048,21 +1078,37 @@ int launch_prepare(PrepArgs a, int batch, hipStream_t st)
     return BDA_OK;
 }
 
+// Waves of a workgroup: as few as hold the strip's column tiles in their registers, so that narrow latents and heads
+// leave none idle and a compute unit takes several workgroups; more, up to one per tile, while the launch would not
+// give every compute unit eight waves.
+template <typename WT, typename CT, StripForm F>
+int launch_strip(const PrepArgs& a, hipStream_t st)
+{
+    static LdsLimitState once;
+    constexpr bool measure = F != StripForm::Window;
+    constexpr int max_dc = F == StripForm::Narrow ? kStripMaxDc / 2 : kStripMaxDc;
+    constexpr int max_lds = (strip_words(strip_width(measure, max_dc, kPrepMaxDh), kPrepMaxDh) + (measure ? kStripWaves * kMaxCandidates : 0)) * (int)sizeof(double);
+    if (int rc = raise_lds((const void*)strip_kernel<WT, CT, F>, max_lds, once)) return rc;
+    const int64_t n_strips = ((int64_t)a.d_side + kStripRows - 1) / kStripRows;
+    const int width = strip_width(measure, a.d_c, a.d_h), tiles = width / 16;
+    int nw = F == StripForm::Wide ? kStripWaves : 1;
+    while (nw * strip_tiles(F) < tiles || (nw < kStripWaves && nw < tiles && a.H * nw * (measure ? std::min<int64_t>(n_strips, a.n_parts) : n_strips) < 2048)) nw *= 2;
+    // a part of a head's error sum is a workgroup; where those leave the chip idle they also share out the windows
+    const int64_t parts = measure ? a.n_parts : std::max<int64_t>(1, std::min<int64_t>(n_strips, 16384 / ((int64_t)a.H * nw)));
+    const int64_t busy = a.H * std::min(n_strips, parts) * nw;
+    const int split = measure ? (int)std::max<int64_t>(1, std::min<int64_t>(4096 / busy, a.n_cand)) : 1;
+    const int lds = (strip_words(width, a.d_h) + (measure ? nw * ((a.n_cand + split - 1) / split) : 0)) * (int)sizeof(double);
+    hipLaunchKernelGGL((strip_kernel<WT, CT, F>), dim3(a.H, (unsigned)parts, split), dim3(64 * nw), lds, st, a);
+    return check_launch("companion kernel");
+}
+
 // Companion block and (a.measure) reconstruction errors of the windows of this launch.
 template <typename WT, typename CT>
 int launch_companion(PrepArgs a, hipStream_t st)
 {
-    const int64_t n_strips = ((int64_t)a.d_side + kStripRows - 1) / kStripRows;
     if (a.d_c <= kStripMaxDc) {
-        static LdsLimitState once;
-        const int lds = strip_lds_bytes(a.d_c, a.d_h);
-        if (int rc = raise_lds((const void*)strip_kernel<WT, CT>, strip_lds_bytes(kStripMaxDc, kPrepMaxDh), once)) return rc;
-        // a part of a head's error sum is a workgroup; where those leave the chip idle they also share out the windows
-        const int64_t parts = a.measure ? a.n_parts : std::max<int64_t>(1, std::min<int64_t>(n_strips, 2048 / a.H));
-        const int64_t busy = a.H * std::min(n_strips, parts);
-        const int split = a.measure ? (int)std::max<int64_t>(1, std::min<int64_t>(512 / busy, a.n_cand)) : 1;
-        hipLaunchKernelGGL((strip_kernel<WT, CT>), dim3(a.H, (unsigned)parts, split), dim3(kStripThreads), lds, st, a);
-        return check_launch("companion kernel");
+        if (!a.measure) return launch_strip<WT, CT, StripForm::Window>(a, st);
+        return a.d_c > kStripMaxDc / 2 ? launch_strip<WT, CT, StripForm::Wide>(a, st) : launch_strip<WT, CT, StripForm::Narrow>(a, st);
     }
     // wider latents: their strips do not fit the LDS; one window per launch, the companion block first
     const int64_t tiles = (((int64_t)a.d_side + 63) / 64) * ((a.d_h + 63) / 64);   // 64 x 64 tiles of the companion block, at most 64 workgroups a head

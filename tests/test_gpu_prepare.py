@@ -210,3 +210,117 @@ def test_prepare_device_ex_windows_prepared_together(d_c, H, d_h, d_side, side_k
     tiles and windows that end on and off the kernels' tile sizes."""
     W, Wq, Wo = _weights(d_c, H, d_h, d_side, seed=60 + d_c + d_side)
     _check_against_oracle(W, d_c, H, d_h, store, Wq if side_kind == oracle.SIDE_Q else Wo, side_kind, mode)
+
+
+def _padded(stored, dtype, ld, shift=0):
+    """Device matrix of row pitch ld whose first element lies `shift` elements into its allocation; the rest is FILL."""
+    a = np.ascontiguousarray(stored)
+    a = a.view(np.int16) if dtype == wl.BF16 else a
+    buf = torch.full((a.shape[0] * ld + shift,), FILL, dtype=_TDT[dtype], device="cuda")
+    view = buf[shift:].view(a.shape[0], ld)
+    view[:, :a.shape[1]] = torch.from_numpy(a.copy()).cuda()
+    return buf, view
+
+
+def _run_stored(W_s, w_dtype, d_c, H, d_h, c_dtype, side_s, side_kind, mode, explicit_offset=0, want_resid=True, pad_in=0, pad_out=0, shift=0):
+    """bda_prepare_device_ex on weights as stored (any type, padded rows, any base); everything beyond the outputs'
+    columns must stay FILL."""
+    N, K = H * d_h, d_c - d_h
+    d_side = side_s.shape[0 if side_kind == oracle.SIDE_Q else 1]
+    W_b, W_d = _padded(W_s, w_dtype, N + pad_in, shift)
+    s_b, s_d = _padded(side_s, w_dtype, side_s.shape[1] + pad_in, shift)
+    fill = lambda rows, cols: _padded(np.full((rows, 0), 0, dtype=np.uint16 if c_dtype == wl.BF16 else np.float32), c_dtype, cols, shift)
+    C_b, C_d = fill(K, N + pad_out)
+    o_b, o_d = fill(side_s.shape[0], side_s.shape[1] + pad_out)
+    off_d = torch.full((1,), -99, dtype=torch.int32, device="cuda")
+    resid_d = torch.zeros(3, dtype=torch.float64, device="cuda") if want_resid else None
+    flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+    need = bda.bda_prepare_device_workspace_bytes(d_c, H, d_h, mode, want_resid)
+    ws = torch.full((max(need, 16),), 0x5A, dtype=torch.uint8, device="cuda")
+    bda.bda_prepare_device_ex(W_d, N + pad_in, w_dtype, d_c, H, d_h, C_d, N + pad_out, c_dtype, side=s_d, ld_side=side_s.shape[1] + pad_in,
+                              d_side=d_side, side_kind=side_kind, side_out=o_d, ld_side_out=side_s.shape[1] + pad_out, mode=mode,
+                              explicit_offset=explicit_offset, basis_offset_out=off_d, resid_out=resid_d, singular_head=flag,
+                              workspace=ws, workspace_bytes=need, stream=gh.stream())
+    torch.cuda.synchronize()
+    assert torch.all(C_d[:, N:] == FILL) and torch.all(o_d[:, side_s.shape[1]:] == FILL)
+    assert torch.all(C_b[:shift] == FILL) and torch.all(o_b[:shift] == FILL)
+    return dict(C=_host(C_d[:, :N].contiguous(), c_dtype), side=_host(o_d[:, :side_s.shape[1]].contiguous(), c_dtype), off=int(off_d.item()),
+                resid=None if resid_d is None else resid_d.cpu().numpy(), flag=int(flag.item()))
+
+
+@pytest.mark.parametrize("w_dtype,store", [(wl.F32, wl.F16), (wl.F16, wl.F16), (wl.BF16, wl.BF16), (wl.F16, wl.F32), (wl.F32, wl.BF16)])
+@pytest.mark.parametrize("side_kind", [oracle.SIDE_Q, oracle.SIDE_O])
+@pytest.mark.parametrize("pad_in,pad_out,shift", [(0, 0, 0), (8, 8, 0), (3, 5, 0), (8, 8, 1)])     # wide fetches; pitches and bases that rule them out
+@pytest.mark.parametrize("d_c,H,d_h,d_side,mode", [
+    (128, 3, 32, 200, oracle.OFFSET_SEARCH),       # three windows per launch with W_q, more with W_o; narrow strips
+    (400, 2, 64, 700, oracle.RESIDUAL_MIN),        # wide strips, both windows in one launch
+    (120, 5, 24, 70, oracle.LAST),                 # one window, measured; it starts inside a column tile (96 = 6 x 16, of 24)
+])
+def test_prepare_device_ex_weights_as_stored(w_dtype, store, side_kind, pad_in, pad_out, shift, d_c, H, d_h, d_side, mode):
+    """Weights in the types they are shipped in, with rows and bases that allow 16-byte fetches and that do not; stored
+    C's of several windows in a padded companion output."""
+    W, Wq, Wo = _weights(d_c, H, d_h, d_side, seed=900 + d_c)
+    W_s, W64 = wl.to_storage(W, w_dtype)
+    side_s, side64 = wl.to_storage(Wq if side_kind == oracle.SIDE_Q else Wo, w_dtype)
+    C_ref, side_ref, off_ref, resid_ref = oracle.prepare(W64, d_c, H, d_h, side=side64, side_kind=side_kind, mode=mode, store_dtype=store)
+    exact = _run_stored(W_s, w_dtype, d_c, H, d_h, wl.F64, side_s, side_kind, oracle.EXPLICIT, off_ref, False)
+    assert np.max(np.abs(exact["C"] - C_ref)) <= 1e-9 * np.max(np.abs(C_ref))
+    assert np.max(np.abs(exact["side"] - side_ref)) <= 1e-12 * np.max(np.abs(side_ref))
+    got = _run_stored(W_s, w_dtype, d_c, H, d_h, store, side_s, side_kind, mode, 0, True, pad_in, pad_out, shift)
+    assert got["flag"] == 0 and got["off"] == off_ref, (got["off"], got["resid"], resid_ref)
+    assert np.array_equal(got["C"], wl.to_storage(exact["C"], store)[1])
+    assert np.array_equal(got["side"], wl.to_storage(exact["side"], store)[1])
+    for g, r in zip(got["resid"], [resid_ref.get(0, np.nan), resid_ref.get(d_c - d_h, np.nan), resid_ref[off_ref]]):
+        assert (np.isnan(g) and np.isnan(r)) or abs(g - r) <= 1e-6 * abs(r), (got["resid"], resid_ref)
+
+
+@pytest.mark.parametrize("d_c,H,d_h,d_side,off", [(20, 3, 4, 70, 16), (24, 70, 8, 33, 9), (64, 40, 16, 300, 17), (90, 3, 33, 40, 57), (144, 2, 48, 65, 41),
+                                                   (300, 2, 113, 31, 187), (260, 1, 128, 100, 0), (512, 2, 250, 33, 262), (512, 1, 256, 40, 255)])
+@pytest.mark.parametrize("side_kind", [oracle.SIDE_Q, oracle.SIDE_O])
+def test_prepare_device_ex_companion_of_one_window(d_c, H, d_h, d_side, off, side_kind):
+    """The companion alone (no residuals): windows at any start, of widths that meet one to seventeen column tiles,
+    workgroups of one to eight waves."""
+    W, Wq, Wo = _weights(d_c, H, d_h, d_side, seed=1300 + d_c, weak_first=False)
+    W_s, W64 = wl.to_storage(W, wl.F32)
+    side_s, side64 = wl.to_storage(Wq if side_kind == oracle.SIDE_Q else Wo, wl.F32)
+    C_ref, side_ref, _, _ = oracle.prepare(W64, d_c, H, d_h, side=side64, side_kind=side_kind, mode=oracle.EXPLICIT, explicit_offset=off)
+    got = _run_stored(W_s, wl.F32, d_c, H, d_h, wl.F64, side_s, side_kind, oracle.EXPLICIT, off, False, 1, 2)
+    assert got["flag"] == 0 and got["off"] == off
+    assert np.max(np.abs(got["C"] - C_ref)) <= 1e-9 * np.max(np.abs(C_ref))
+    assert np.max(np.abs(got["side"] - side_ref)) <= 1e-12 * np.max(np.abs(side_ref))
+
+
+@pytest.mark.parametrize("side_kind", [oracle.SIDE_Q, oracle.SIDE_O])
+@pytest.mark.parametrize("bad", [0, 16, 48, 80, 96])
+def test_prepare_device_ex_singular_window_in_a_batch(side_kind, bad):
+    """One singular candidate in one head of a search that prepares several windows per launch (seven windows, three
+    per launch with W_q: first and middle of a launch, last of one, alone in the last): passed over, +inf where its
+    residual is asked for, no flag."""
+    d_c, H, d_h, d_side, store = 128, 3, 32, 200, wl.F16
+    W, Wq, Wo = _weights(d_c, H, d_h, d_side, seed=640, weak_first=False)
+    W[bad + d_h - 1, d_h:2 * d_h] = W[bad, d_h:2 * d_h]       # head 1: the window's first and last row equal, both in no other candidate
+    side = Wq if side_kind == oracle.SIDE_Q else Wo
+    refs = {o: oracle.prepare(W, d_c, H, d_h, side=side, side_kind=side_kind, mode=oracle.EXPLICIT, explicit_offset=o, store_dtype=store)
+            for o in range(0, d_c - d_h + 1, 16) if o != bad}
+    resid = {o: r[3][o] for o, r in refs.items()}
+    best = min(resid, key=lambda o: (resid[o], o))
+    got = _run(W, d_c, H, d_h, store, side, side_kind, oracle.OFFSET_SEARCH)
+    assert got["off"] == best and got["flag"] == 0, (got["off"], got["resid"], resid)
+    for g, r in zip(got["resid"], [resid.get(0, np.inf), resid.get(d_c - d_h, np.inf), resid[best]]):
+        assert (np.isinf(g) and np.isinf(r)) or abs(g - r) <= 1e-6 * abs(r), (got["resid"], resid)
+    exact = _run(W, d_c, H, d_h, wl.F64, side, side_kind, oracle.EXPLICIT, best)
+    assert np.max(np.abs(exact["C"] - refs[best][0])) <= 1e-9 * np.max(np.abs(refs[best][0]))
+    assert np.array_equal(got["C"], wl.to_storage(exact["C"], store)[1])
+    assert np.array_equal(got["side"], wl.to_storage(exact["side"], store)[1])
+
+
+@pytest.mark.parametrize("side_kind", [oracle.SIDE_Q, oracle.SIDE_O])
+@pytest.mark.parametrize("mode", [oracle.RESIDUAL_MIN, oracle.OFFSET_SEARCH])
+def test_prepare_device_ex_every_window_singular_with_a_companion(side_kind, mode):
+    """A head of rank below d_h: no window is chosen, and the pass for the chosen window leaves C and the flag alone."""
+    d_c, H, d_h, d_side = 128, 3, 32, 200
+    W, Wq, Wo = _weights(d_c, H, d_h, d_side, seed=650, weak_first=False)
+    W[:, 2 * d_h + 5] = W[:, 2 * d_h + 9]                     # head 2: two equal columns
+    got = _run(W, d_c, H, d_h, wl.F16, Wq if side_kind == oracle.SIDE_Q else Wo, side_kind, mode)
+    assert got["off"] == -1 and got["flag"] == 0 and np.all(np.isinf(got["resid"]))
+    assert np.all(got["C"][:, 2 * d_h:] == FILL)              # (a head that was singular in every window has no C)
