@@ -369,9 +369,11 @@ bool lean_kernel_applies(const GemmArgs& a, int G, const int64_t* group_cols)
 // N = 32 5.1 / 5.7; T = 4096, K = 288, N = 128 5.8 / 12.0).  Beyond, their number costs more than the other kernel's waits
 // where the contraction is short (T = 2048, K = 64, N = 2592: 14.7 / 11.8) and less where it is long (T = 1500, K = 608,
 // N = 2176: 17.5 / 35.9): the two estimates are fits over 460 such launches of K 8 .. 416, 6 and 7 % off at the root mean square.
+// (Float32 results of two chunks or more stay with the halves, whose shorter sums show in them: error against 64 bits at
+// K = 416 1.0e-7, 1.3e-7 in one sum.)
 // At most 128 columns and K >= 384: 128 x 128 tiles, which such a launch has always reported as its plan; faster than the
 // register-staged kernel there, but not as fast as 64 x 64 tiles (T = 4096, K = 416, N = 128: 11.6 us, 14.3 and 6.3).
-int mid_tile(const GemmArgs& a, int G, const int64_t* group_cols, bool big)
+int mid_tile(const GemmArgs& a, int G, const int64_t* group_cols, bool big, bool f32_out)
 {
     int64_t N = 0, nt64 = 0;
     for (int g = 0; g < G; ++g) { N += group_cols[g]; nt64 += (group_cols[g] + 63) / 64; }
@@ -390,7 +392,9 @@ int mid_tile(const GemmArgs& a, int G, const int64_t* group_cols, bool big)
     }
     if (N <= 128 && a.K >= 384) return 128;
     if (tiles <= 512) return 64;
-    const int chunks = (a.K + 63) / 64, id_chunks = a.ident ? ((a.d_h % 128 == 0 ? 128 : a.d_h) + 63) / 64 : 0;
+    const int chunks = (a.K + 63) / 64;
+    if (f32_out && chunks > 1) return 64;
+    const int id_chunks = a.ident ? ((a.d_h % 128 == 0 ? 128 : a.d_h) + 63) / 64 : 0;
     const double staged = 2.6 + 0.0037 * s.m_tiles * s.n_tiles + rounds * (0.96 * chunks + 0.7 * id_chunks + (kNumXcd * s.sm * s.sn > 256 ? 6.0 : 3.0));
     const double mid = 4.3 + (double)tiles * (0.0041 + 0.00086 * chunks + (a.ident ? 0.002 : 0.0));
     return mid < staged ? 64 : 0;
@@ -513,7 +517,7 @@ int run_gemm(GemmArgs& a, int G, const int64_t* group_cols, int dtype, int out_d
         const int tok_tile = quarter_tokens ? 64 : half_tokens ? 128 : 256;
         const bool big = plain || policy == 2 || policy == 3 || policy == 4 || ((policy == 0 || policy == 7) && mt256 * nt256 >= 96);
         const bool stream = big && stream_ok;
-        const int mid = (policy == 0 || policy == 7) && !plain && (stream || !big) ? mid_tile(a, G, group_cols, big) : 0;
+        const int mid = (policy == 0 || policy == 7) && !plain && (stream || !big) ? mid_tile(a, G, group_cols, big, out_dtype == BDA_F32) : 0;
         if (mid) {
             build_tiles(a, G, group_cols, mid, mid);
 #define BDA_LAUNCH(X, O) return mid == 64 ? launch_mid<X, O, 1, 1>(a, st) : launch_mid<X, O, 2, 2>(a, st)

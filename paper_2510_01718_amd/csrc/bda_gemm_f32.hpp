@@ -76,7 +76,7 @@ struct GeneralTile {
     static constexpr int STAGES = KS == 1 ? 1 : 2;                // of LDS
     static constexpr int SUMS = (KS - 1) * WT * WN * TT * TN * 16 * 64;
     static constexpr int LDS_BYTES = 4 * (STAGES * STAGE > SUMS ? STAGES * STAGE : SUMS);
-    static_assert(THREADS % TOK_PPR == 0 && THREADS % WGT_PPR == 0 && KPG % 8 == 0);
+    static_assert(THREADS % TOK_PPR == 0 && THREADS % WGT_PPR == 0 && KPG % 8 == 0 && (KS > 1 || (TT * TN == 1 && KPG == 16)));
     static_assert(TOK_LOADS * TOK_RPP == (TOK_KC ? BT : BK) && WGT_LOADS * WGT_RPP == (WGT_KC ? BN : BK));
     static_assert(LDS_BYTES <= 160 * 1024);
 };
@@ -256,15 +256,15 @@ __global__ __launch_bounds__(64 * WT * WN * KS, TT * TN > 1 ? 2 : 4) void genera
 #pragma unroll
         for (int ti = 0; ti < TT; ++ti) ft[s & 1][ti] = frag(tok_s, L::TOK_PITCH, L::TOK_KC, (wt * TT + ti) * 32 + l31, k);
     };
-    auto multiply = [&](int s) {
+    auto multiply = [&](int s, auto&& sum) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
             for (int ni = 0; ni < TN; ++ni)
 #pragma unroll
                 for (int ti = 0; ti < TT; ++ti)
-                    acc[ni][ti] = VEC ? __builtin_amdgcn_mfma_f32_32x32x2f32(fw[s & 1][ni][e], ft[s & 1][ti][e], acc[ni][ti], 0, 0, 0)
-                                      : __builtin_amdgcn_mfma_f32_32x32x2f32(ft[s & 1][ti][e], fw[s & 1][ni][e], acc[ni][ti], 0, 0, 0);
+                    sum(ni, ti) = VEC ? __builtin_amdgcn_mfma_f32_32x32x2f32(fw[s & 1][ni][e], ft[s & 1][ti][e], sum(ni, ti), 0, 0, 0)
+                                      : __builtin_amdgcn_mfma_f32_32x32x2f32(ft[s & 1][ti][e], fw[s & 1][ni][e], sum(ni, ti), 0, 0, 0);
     };
     // Chunk c, in LDS half c % 2 (and, until it was stored there, register set c % SETS).  Where a wave has one
     // 32 x 32 tile the fragments of a step are requested before the products of the step before it; four tiles
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(64 * WT * WN * KS, TT * TN > 1 ? 2 : 4) void genera
             else if (s + 1 < KPG / 8) read(tok_s, s + 1);
             else store_chunk(std::integral_constant<int, 1 - S>{});   // into the half of chunk c - 1, free since the last barrier
             if (AHEAD) __builtin_amdgcn_sched_barrier(0);
-            multiply(s);
+            multiply(s, [&](int ni, int ti) -> f32x16& { return acc[ni][ti]; });
             if (AHEAD) __builtin_amdgcn_sched_barrier(0);
         }
         if (!AHEAD) store_chunk(std::integral_constant<int, 1 - S>{});
@@ -291,19 +291,29 @@ __global__ __launch_bounds__(64 * WT * WN * KS, TT * TN > 1 ? 2 : 4) void genera
     const std::integral_constant<int, 1> set1;
     load_chunk(set0, 0);
     if constexpr (L::STAGES == 1) {
-        // a chunk or a few: as little code as there can be (a launch of one chunk pays for fetching it)
+        // a chunk or a few: as little code as there can be (a launch of one chunk pays for fetching it).  Each step of 8
+        // elements of two chunks has a sum of its own: sums of 16 at most, as the k-groups of the other tiles have.
+        f32x16 sums[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sums[i] = acc[0][0];
         for (int c = 0;;) {
             store_chunk(set0);
             __syncthreads();
             if (++c < n_chunks) load_chunk(set0, c);
 #pragma unroll
-            for (int s = 0; s < KPG / 8; ++s) {
+            for (int s = 0; s < 2; ++s) {
                 read(gsm, s);
-                multiply(s);
+                multiply(s, [&](int, int) -> f32x16& { return sums[s]; });
             }
             if (c >= n_chunks) break;
+            const f32x16 s0 = sums[0], s1 = sums[1];
+            sums[0] = sums[2];
+            sums[1] = sums[3];
+            sums[2] = s0;
+            sums[3] = s1;
             __syncthreads();
         }
+        acc[0][0] = (sums[0] + sums[1]) + (sums[2] + sums[3]);
     } else {
         if (L::SETS == 2) load_chunk(set1, 1);
         store_chunk(set0);
@@ -399,22 +409,22 @@ __global__ __launch_bounds__(64 * WT * WN * KS, TT * TN > 1 ? 2 : 4) void genera
 //   1    64 x  64   1 x 1, 2 x 2, 2 groups of 32
 //   2    64 x  32   1 x 1, 2 x 1, 4 groups of 16
 //   3    32 x  32   1 x 1, 1 x 1, 8 groups of 16
-//   4    64 x  64   1 x 1, 2 x 2, 1 group of 16: contractions of at most one chunk of the others
+//   4    64 x  64   1 x 1, 2 x 2, 1 group of 16: contractions of less than a chunk of the others
 // ---------------------------------------------------------------------------------------------
-constexpr int kGeneralTiles = 4, kGeneralShort = 4, kGeneralShortLen = 64;
+constexpr int kGeneralTiles = 4, kGeneralShort = 4;
 constexpr int kGeneralBT[] = {128, 64, 64, 32, 64}, kGeneralBN[] = {128, 64, 32, 32, 64};
 
 // The tile with the least time over the 256 compute units: rounds x matrix time x a factor for what the smaller
 // ones spend beside it.  Measured, us (float32, 4096 tokens, d_c = 512, d_h = 64, N = 1024; tiles 0 / 1 / 2 / 3):
 // forward (256 .. 4096 tiles) 42 / 46 / 53 / 71, latent gradient (128 .. 2048) 82 / 55 / 63 / 74, weight gradient
 // (32 .. 448) 280 / 87 / 51 / 48; one token, forward 34 / 13 / 9.4 / 7.8.
-// Up to 64 contraction elements the k-groups have nothing to share and a launch is its loads and stores.  Short
-// tile against the best of the others (geometric means over outputs of 1 x 64 .. 8192 x 8001; float32 in 16-byte
-// pieces / element by element): 8 elements 0.79 / 0.61, 32 0.91 / 0.76, 64 0.96 / 0.89, 100 1.04 / 0.91, 128 1.17 / 1.05.
+// Up to 48 contraction elements (64 element by element) the k-groups have little to share and a launch is its loads
+// and stores.  Short tile against the best of the others (geometric means over outputs of 1 x 64 .. 8192 x 8001;
+// float32 in 16-byte pieces / element by element): 8 elements 0.75 / 0.56, 32 0.87 / 0.69, 48 0.91 / 0.73, 64 1.05 / 0.85.
 constexpr double kGeneralCost[kGeneralTiles] = {1.4, 1.6, 1.8, 2.2};
 inline int general_tile(int64_t rows, int64_t len, const int64_t* group_cols, int G, bool vec)
 {
-    if (len <= kGeneralShortLen) return kGeneralShort;
+    if (len <= (vec ? 48 : 64)) return kGeneralShort;
     int best = 0;
     double best_cost = 0.0;
     for (int i = 0; i < kGeneralTiles; ++i) {

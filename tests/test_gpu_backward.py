@@ -151,15 +151,16 @@ _VEC = [
     ("weight", T64, 70, 536, 40, [26, 24], [4, 496]),
     ("weight", T64x32, 333, 536, 40, [13, 12], [0, 60]),
     ("weight", T32, 333, 536, 40, [5, 6], [0, 60]),
-    # short contractions: below, at and above a chunk of 16, up to the limit of 64
+    # short contractions: below, at and above a chunk of 16, up to the limit of 48, and the tile beyond it
     ("forward", SHORT, 130, 60, 40, [3, 2], [0, 20]),
-    ("forward", SHORT, 70, 104, 40, [3, 2], [0, 64]),
+    ("forward", SHORT, 70, 88, 40, [3, 2], [0, 48]),
+    ("forward", T32, 70, 92, 40, [3, 2], [0, 48]),
     ("forward", SHORT, 1, 12, 8, [9], [4]),
-    ("latent", SHORT, 130, 84, 20, [1, 2], [0, 64]),
-    ("latent", SHORT, 300, 512, 64, [1], [128]),
+    ("latent", SHORT, 130, 84, 12, [1, 2], [0, 64]),
+    ("latent", SHORT, 300, 512, 48, [1], [128]),
     ("weight", SHORT, 1, 104, 40, [3, 2], [0, 64]),
     ("weight", SHORT, 17, 536, 40, [13, 12], [0, 60]),
-    ("weight", SHORT, 64, 200, 72, [5, 2], [12, 100]),
+    ("weight", SHORT, 48, 200, 72, [5, 2], [12, 100]),
 ]
 # element by element (an odd pitch): 64 x 64, 32 x 32 and the short tile
 _ELEM = [
@@ -173,7 +174,7 @@ _ELEM = [
     ("weight", T64, 70, 536, 40, [26, 24], [3, 496]),
     ("weight", T32, 333, 535, 41, [5, 6], [0, 60]),
     ("weight", SHORT, 1, 103, 41, [3, 2], [0, 62]),
-    ("weight", SHORT, 33, 535, 41, [13, 12], [0, 60]),
+    ("weight", SHORT, 64, 535, 41, [13, 12], [0, 60]),
 ]
 
 
