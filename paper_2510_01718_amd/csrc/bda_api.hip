@@ -393,11 +393,11 @@ int mid_tile(const GemmArgs& a, int G, const int64_t* group_cols, bool big, bool
     if (N <= 128 && a.K >= 384) return 128;
     if (tiles <= 512) return 64;
     const int chunks = (a.K + 63) / 64;
-    if (f32_out && chunks > 1) return 64;
+    if (chunks > (f32_out ? 1 : 5)) return 64;
     const int id_chunks = a.ident ? ((a.d_h % 128 == 0 ? 128 : a.d_h) + 63) / 64 : 0;
     const double staged = 2.6 + 0.0037 * s.m_tiles * s.n_tiles + rounds * (0.96 * chunks + 0.7 * id_chunks + (kNumXcd * s.sm * s.sn > 256 ? 6.0 : 3.0));
     const double mid = 4.3 + (double)tiles * (0.0041 + 0.00086 * chunks + (a.ident ? 0.002 : 0.0));
-    return mid < staged ? 64 : 0;
+    return mid < (chunks > 1 ? 1.08 : 1.0) * staged ? 64 : 0;   // (two chunks or more: either is at most a little slower than the other)
 }
 
 int run_gemm(GemmArgs& a, int G, const int64_t* group_cols, int dtype, int out_dtype, hipStream_t st)
