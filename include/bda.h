@@ -103,11 +103,14 @@ int bda_prepare_lowrank(const double* U, const double* V, int d_in, int r, int d
  * bda_prepare on the GPU (Algorithm "BD Attention Preparation (QK)", Appendix "BD for VO in MHA",
  * Algorithm "BD Decomposition (Row)" and Appendix "Residual-Min with Offset Search" for the window
  * choice): C_h = W_h[Bbar,:] W_h[B,:]^{-1}, the companion blocks W_q^h W_h[B,:]^T or W_h[B,:] W_o^h,
- * and the window that minimises the mean residual of the stored form.  One workgroup per head,
- * float64 arithmetic (Gauss-Jordan inverse of the basis block with partial pivoting, then the
- * products); a search prepares every candidate window in turn into the outputs, measures the
- * reconstruction error of what was stored, selects on the device, and prepares the chosen window once
- * more.  Asynchronous on `stream`; nothing comes back to the host and nothing is allocated.
+ * and the window that minimises the mean residual of the stored form.  Float64 arithmetic
+ * (Gauss-Jordan inverse of the basis block with partial pivoting, then the products), one workgroup
+ * per head and window, or several that share its rows.  A search prepares candidate windows into the
+ * outputs - one at a time into C, and with a companion, d_h <= 128 and d_c <= 512 as many more per
+ * launch as side_out has room for (its rows and columns serve as scratch until the chosen window is
+ * written) - measures the reconstruction error of what was stored, selects on the device, and
+ * prepares the chosen window once more.  Asynchronous on `stream`; nothing comes back to the host and
+ * nothing is allocated.
  *   W        device, d_c x (H d_h), ld = ldw, element type w_dtype (any bda_dtype).
  *   side     device or NULL: companion weight as in bda_prepare (W_q: d_side x H d_h; W_o: H d_h x
  *            d_side), ld = ld_side, element type w_dtype.
@@ -118,7 +121,8 @@ int bda_prepare_lowrank(const double* U, const double* V, int d_in, int r, int d
  *            element is rounded once, to nearest even, from the float64 result - ready for
  *            bda_kv_project.
  *   side_out device (NULL without a companion), shape of `side`, ld = ld_side_out, element type
- *            c_dtype, rounded the same way.
+ *            c_dtype, rounded the same way.  Written during a search as well (see above); elements
+ *            beyond its columns are never touched.
  *   basis_offset_out   device int (may be NULL for a single-window mode without resid_out): the
  *            chosen window start once the call has run, or -1 if every candidate was singular (C
  *            and side_out then hold no result).
@@ -156,7 +160,7 @@ int bda_prepare_device_ex(const void* W, int64_t ldw, bda_dtype w_dtype, int d_c
  * that is part of the library's device code: every GPU the library runs on holds it from the moment the
  * library's code is loaded there until the process ends.  The call allocates and frees nothing.
  * Limits: what bda_prepare_device_ex would need with one basis block (1 KiB + 8 bytes x candidate windows
- * x H x min(16, 1024 / H) + 8 d_h^2 for d_h > 128) must fit the 8 MiB; beyond that the call fails with
+ * x H x max(1, min(64, 1024 / H)) + 8 d_h^2 for d_h > 128) must fit the 8 MiB; beyond that the call fails with
  * BDA_EINVAL and a message that names both sizes.  For d_h > 128 as many heads are prepared per launch as
  * basis blocks fit the rest of the array.  Every call on a GPU shares that GPU's array (it clears what it
  * needs cleared): calls that overlap on one GPU - two streams, two threads - race; keep them in order.
@@ -238,8 +242,9 @@ int bda_lowrank_linear(const void* x, int64_t ldx, int64_t T, int d_in, int r, i
  * Each gradient is one launch on `stream`; products are accumulated in float32 (fp16/bf16 inputs use
  * MFMA; the head sum on the window is part of the same accumulation) and rounded once when stored.
  * The MFMA path needs 16-byte aligned pointers, ld's, d_c and basis offsets that are multiples of 8
- * and d_h a multiple of 32; anything else (and BDA_F32 inputs) runs a slower general
- * kernel on the float32 matrix instructions with the same result contract.  Gradients must not overlap the inputs or each other.
+ * and d_h a multiple of 32; anything else (and BDA_F32 inputs) runs a slower general kernel on the
+ * float32 matrix instructions with the same result contract.  Gradients must not overlap the inputs or
+ * each other.
  * Errors: BDA_EINVAL, BDA_EDTYPE, BDA_EHIP.
  */
 int bda_kv_project_backward(const void* c, int64_t ldc, const void* d_out, int64_t ld_dout,
@@ -291,9 +296,10 @@ int bda_kv_project_packed(const void* c, int64_t ldc, int64_t T, int d_c, int d_
  *   7 = 64 x 256 with the lean streaming kernel where it applies (else as 0 without the small-T
  *       kernels).
  * bda_kv_project_backward_ex honours 1 (128 x 128 output tiles) and treats the rest as automatic.
- * Results do not depend on the policy beyond which kernel computes them (the order of the float32
- * summation over k is the same for every tile shape).  Errors: as the plain call, plus BDA_EINVAL
- * for a policy outside 0 .. 7.
+ * Results do not depend on the policy beyond which kernel computes them.  Every kernel and tile shape
+ * adds the products over k in a fixed order of its own (one sum, or partial sums of groups of waves that
+ * are then added), so two of them agree to the rounding of float32 sums, and calls that differ in T
+ * alone may differ by as much.  Errors: as the plain call, plus BDA_EINVAL for a policy outside 0 .. 7.
  */
 int bda_kv_project_ex(const void* c, int64_t ldc, int64_t T, int d_c, int d_h,
                       int G, const int* H, const int* basis_offset,
