@@ -1054,7 +1054,8 @@ int launch_invert(const PrepArgs& a, hipStream_t st)
     static LdsLimitState once;
     constexpr int lds = invert_lds_bytes<NB>();
     if (int rc = raise_lds((const void*)invert_kernel<NB>, lds, once)) return rc;
-    // workgroups per head and window: up to one per compute unit, at most one per row tile
+    // workgroups per head and window: up to one per compute unit, at most one per row tile.  (They repeat the inversion
+    // and share the rows after it: the call alone is faster, and calls on other streams find the chip full.)
     const int row_tiles = (a.d_c - a.d_h + 15) / 16;
     int per_head = 256 / (a.H * a.n_cand);
     per_head = per_head < 1 ? 1 : per_head > row_tiles ? row_tiles : per_head;
