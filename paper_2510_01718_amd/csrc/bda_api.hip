@@ -209,12 +209,12 @@ int launch_duo(const GemmArgs& a, hipStream_t st)
     return err == hipSuccess ? BDA_OK : fail(BDA_EHIP, "kernel launch: %s", hipGetErrorString(err));
 }
 
-// LDS of the 32-column small-T kernel: slice of C, token rows (TOK_LDS), float32 partial sums of the
-// four waves (in the token rows' space when there are two token blocks).
+// LDS of the 32-column small-T kernel: slice of C (in pairs of 16 rows, as it is requested), token rows (TOK_LDS),
+// float32 partial sums of the four waves (in the token rows' space when there are two token blocks).
 template <int NTB, bool TOK_LDS>
 int decode_lds_bytes(int K)
 {
-    const int wgt = ((K + 15) / 16) * 1024, part = NTB * 16384;
+    const int wgt = ((K + 31) / 32) * 2048, part = NTB * 16384;
     const int tok = TOK_LDS ? ((K + 63) / 64) * NTB * 4096 : 0;
     return (TOK_LDS && NTB == 2) ? wgt + std::max(tok, part) : wgt + tok + part;
 }

@@ -132,7 +132,9 @@ __global__ __launch_bounds__(256) void kv_decode_kernel(const GemmArgs p_in)
     const int a_off = sg.a_off;
     const int T = (int)p.M;
     const int nks = (p.K + 15) >> 4;                     // k-steps of 16
-    const int wgt_bytes = nks * 16 * 64;                 // LDS: [k][32 columns] 16-bit
+    // LDS: [k][32 columns] 16-bit, in whole pairs of k-steps: the second instruction of a pair past the last
+    // k-step stores its zeros there, and the token rows behind it are on their way at the same time
+    const int wgt_bytes = ((nks + 1) & ~1) * 1024;
 
     // ---- the slice of C: K rows x 64 bytes, 16 rows per DMA instruction (first of all: everything
     // else the kernel does before its MFMAs hides behind this request) --------------------------------

@@ -469,6 +469,26 @@ def test_dense_project_few_tokens(T, policy):
     assert_parity(gh.to_host64(out_d, dtype), ref, 64, dtype, dtype, "dense few tokens")
 
 
+@pytest.mark.parametrize("dtype,out_dtype", [(wl.F16, wl.F16), (wl.BF16, wl.F32)])
+@pytest.mark.parametrize("T,K", [(33, 16), (64, 40), (40, 80), (64, 176), (40, 296), (33, 304), (64, 496)])
+def test_few_tokens_odd_number_of_k_steps(T, K, dtype, out_dtype):
+    """33 .. 64 tokens, whose rows go through LDS behind the slice of C: the last request of the slice is half empty.
+    Every launch of many gives the same result, and that is the oracle's."""
+    N = 1184
+    p = bda.bda_dense_project_plan(T, K, N, dtype, out_dtype)
+    assert (p["kernel"], p["tile_tokens"], p["tile_columns"]) == (bda.KERNEL_DECODE, 64, 32), p
+    rng = np.random.default_rng([T, K])
+    c_s, c64 = wl.to_storage(rng.standard_normal((T, K)), dtype)
+    W_s, W64 = wl.to_storage(0.25 * rng.standard_normal((K, N)), dtype)
+    c_d, W_d = gh.to_device(c_s, dtype), gh.to_device(W_s, dtype)
+    outs = [gh.new_out(T, N, out_dtype) for _ in range(40)]
+    for o in outs:
+        bda.bda_dense_project(c_d, K, T, K, W_d, N, N, o, N, dtype, out_dtype, gh.stream())
+    torch.cuda.synchronize()
+    assert_parity(gh.to_host64(outs[0], out_dtype), oracle.dense_project(c64, W64), N, dtype, out_dtype, f"T={T} K={K}")
+    assert all(torch.equal(o, outs[0]) for o in outs)
+
+
 @pytest.mark.parametrize("last", [False, True])
 @pytest.mark.parametrize("dtype", [wl.F16, wl.BF16])
 def test_lowrank_linear_small(last, dtype):

@@ -373,3 +373,12 @@ def test_launch_plan_many_small_tiles_of_a_short_contraction():
     assert shape(2048, 416, 1544) == (64, 512)                                # 800 tiles, seven chunks each
     p = _plan(2048, [40, 41], [0, 64], bda.BDA_BF16, d_c=96, d_h=32)
     assert (p["kernel"], p["tile_tokens"], p["threads"]) == (bda.KERNEL_MFMA, 128, 256)
+
+
+@pytest.mark.parametrize("K", [8, 16, 40, 176, 296, 304, 496, 512])
+def test_launch_plan_few_tokens_lds_holds_whole_request_pairs(K):
+    # 33 .. 64 tokens: the slice of C is requested 32 rows at a time and the token rows lie behind it, so the slice's
+    # space ends with a whole request (else the zeros past an odd number of k-steps fall into the first token rows)
+    p = _plan(40, [5, 1], [8, 0], bda.BDA_F16, d_c=K + 64, d_h=64)
+    assert (p["kernel"], p["tile_tokens"], p["tile_columns"]) == (bda.KERNEL_DECODE, 64, 32)
+    assert p["lds_bytes"] == 2048 * -(-K // 32) + max(8192 * -(-K // 64), 32768)
