@@ -291,29 +291,25 @@ __global__ __launch_bounds__(64 * WT * WN * KS, TT * TN > 1 ? 2 : 4) void genera
     const std::integral_constant<int, 1> set1;
     load_chunk(set0, 0);
     if constexpr (L::STAGES == 1) {
-        // a chunk or a few: as little code as there can be (a launch of one chunk pays for fetching it).  Each step of 8
-        // elements of two chunks has a sum of its own: sums of 16 at most, as the k-groups of the other tiles have.
-        f32x16 sums[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sums[i] = acc[0][0];
+        // a chunk or a few: as little code as there can be (a launch of one chunk pays for fetching it).  Each of a chunk's
+        // two steps has a sum of its own, which is added to the total: sums of 8, as short as the k-groups of the other
+        // tiles have them or shorter.
         for (int c = 0;;) {
             store_chunk(set0);
             __syncthreads();
             if (++c < n_chunks) load_chunk(set0, c);
+            f32x16 sums[2];
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sums[s][r] = 0.0f;
                 read(gsm, s);
                 multiply(s, [&](int, int) -> f32x16& { return sums[s]; });
             }
+            acc[0][0] += sums[0] + sums[1];
             if (c >= n_chunks) break;
-            const f32x16 s0 = sums[0], s1 = sums[1];
-            sums[0] = sums[2];
-            sums[1] = sums[3];
-            sums[2] = s0;
-            sums[3] = s1;
             __syncthreads();
         }
-        acc[0][0] = (sums[0] + sums[1]) + (sums[2] + sums[3]);
     } else {
         if (L::SETS == 2) load_chunk(set1, 1);
         store_chunk(set0);
@@ -409,7 +405,7 @@ __global__ __launch_bounds__(64 * WT * WN * KS, TT * TN > 1 ? 2 : 4) void genera
 //   1    64 x  64   1 x 1, 2 x 2, 2 groups of 32
 //   2    64 x  32   1 x 1, 2 x 1, 4 groups of 16
 //   3    32 x  32   1 x 1, 1 x 1, 8 groups of 16
-//   4    64 x  64   1 x 1, 2 x 2, 1 group of 16: contractions of less than a chunk of the others
+//   4    64 x  64   1 x 1, 2 x 2, 1 group of 16: contractions of less than a chunk of the others, or of a few
 // ---------------------------------------------------------------------------------------------
 constexpr int kGeneralTiles = 4, kGeneralShort = 4;
 constexpr int kGeneralBT[] = {128, 64, 64, 32, 64}, kGeneralBN[] = {128, 64, 32, 32, 64};
@@ -421,8 +417,13 @@ constexpr int kGeneralBT[] = {128, 64, 64, 32, 64}, kGeneralBN[] = {128, 64, 32,
 // Up to 48 contraction elements (64 element by element) the k-groups have little to share and a launch is its loads
 // and stores.  Short tile against the best of the others (geometric means over outputs of 1 x 64 .. 8192 x 8001;
 // float32 in 16-byte pieces / element by element): 8 elements 0.75 / 0.56, 32 0.87 / 0.69, 48 0.91 / 0.73, 64 1.05 / 0.85.
+// Element by element and with more than 256 tiles of 64 x 64, longer contractions take it too: there the loads are the
+// time, the other tiles fetch up to two chunks of 64 or 128 for little more than one, and 32 x 32 tiles fetch everything
+// twice as often.  us, the others / short: forward, bf16, 95 elements and 288 tiles 27.8 / 13.7, 107 and 532 40.0 / 19.2;
+// float32, 125 and 517 35.1 / 20.6; f16, 226 and 324 35.3 / 24.6.  The limits are where it stops being faster (188 and 363
+// 19.6 / 21.7, 252 and 378 23.9 / 26.0); the latent gradient's are lower for its look at the windows (201 and 280 35.3 / 37.4).
 constexpr double kGeneralCost[kGeneralTiles] = {1.4, 1.6, 1.8, 2.2};
-inline int general_tile(int64_t rows, int64_t len, const int64_t* group_cols, int G, bool vec)
+inline int general_tile(Product prod, int64_t rows, int64_t len, const int64_t* group_cols, int G, bool vec)
 {
     if (len <= (vec ? 48 : 64)) return kGeneralShort;
     int best = 0;
@@ -434,6 +435,12 @@ inline int general_tile(int64_t rows, int64_t len, const int64_t* group_cols, in
         const int64_t tiles = (rows + kGeneralBT[i] - 1) / kGeneralBT[i] * nt;
         const double cost = (double)((tiles + 255) / 256) * kGeneralBT[i] * kGeneralBN[i] * kGeneralCost[i];
         if (best_cost == 0.0 || cost < best_cost) { best_cost = cost; best = i; }
+    }
+    if (!vec) {
+        int64_t tiles = 0;
+        for (int g = 0; g < G; ++g) tiles += (rows + 63) / 64 * ((group_cols[g] + 63) / 64);
+        const int most = prod == Product::Latent ? (best == 3 ? 160 : 80) : best == 3 ? 300 : tiles <= 512 ? 112 : 200;
+        if (tiles > 256 && len <= most) return kGeneralShort;
     }
     return best;
 }
@@ -499,7 +506,7 @@ int launch_general_typed(GeneralArgs& a, const int64_t* group_cols, int G, Launc
 {
     bool vec = false;
     if constexpr (std::is_same_v<InT, float>) vec = general_vec(a, P, group_cols, G);
-    const int tile = general_tile(a.rows, a.len, group_cols, G, vec);
+    const int tile = general_tile(P, a.rows, a.len, group_cols, G, vec);
     general_tiles(a, group_cols, G, tile);
     if constexpr (std::is_same_v<InT, float>)
         if (vec) {

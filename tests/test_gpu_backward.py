@@ -128,7 +128,8 @@ def test_float32_general_kernel_tiles(T, d_c, d_h, H, offs, pad):
 def _general_tile(rows, contraction, H, d_h, dtype, vec):
     """Tile of the general kernel for a product of these extents.  All three products choose by the same rule, so the
     launch plan of a forward with the same output and contraction tells the gradients' tiles (contraction rounded up
-    to a multiple of four, which keeps 16-byte pieces possible; an odd pitch rules them out)."""
+    to a multiple of four, which keeps 16-byte pieces possible; an odd pitch rules them out).  (Limits of the latent
+    gradient's own: element by element, beyond 256 tiles of 64 x 64 and 80 elements.)"""
     contraction = (contraction + 3) // 4 * 4
     p = bda.bda_kv_project_plan(rows, contraction + d_h, d_h, H, [0] * len(H), dtype,
                                 ldC=None if vec else sum(H) * d_h + 1)
@@ -168,6 +169,12 @@ _ELEM = [
     ("forward", T32, 290, 143, 60, [3, 5], [7, 83]),
     ("forward", SHORT, 130, 61, 40, [3, 2], [0, 21]),
     ("forward", SHORT, 66, 34, 33, [3], [1]),
+    # beyond 256 tiles of 64 x 64: the short tile for several of its chunks, up to a limit
+    ("forward", SHORT, 1400, 172, 60, [8, 8], [8, 0]),
+    ("forward", T64, 1400, 176, 60, [8, 8], [8, 0]),
+    ("forward", SHORT, 1100, 360, 60, [8, 8], [8, 0]),
+    ("latent", SHORT, 2100, 475, 40, [1, 1], [3, 435]),
+    ("weight", SHORT, 115, 535, 40, [26, 28], [3, 495]),
     ("latent", T64, 1990, 476, 40, [1, 1], [3, 436]),
     ("latent", T32, 290, 475, 41, [1, 1], [3, 434]),
     ("latent", SHORT, 130, 83, 21, [1, 2], [0, 62]),
