@@ -421,7 +421,8 @@ constexpr int kGeneralBT[] = {128, 64, 64, 32, 64}, kGeneralBN[] = {128, 64, 32,
 // time, the other tiles fetch up to two chunks of 64 or 128 for little more than one, and 32 x 32 tiles fetch everything
 // twice as often.  us, the others / short: forward, bf16, 95 elements and 288 tiles 27.8 / 13.7, 107 and 532 40.0 / 19.2;
 // float32, 125 and 517 35.1 / 20.6; f16, 226 and 324 35.3 / 24.6.  The limits are where it stops being faster (188 and 363
-// 19.6 / 21.7, 252 and 378 23.9 / 26.0); the latent gradient's are lower for its look at the windows (201 and 280 35.3 / 37.4).
+// 19.6 / 21.7, 252 and 378 23.9 / 26.0); the latent gradient's are lower for its look at the windows (100 and 384
+// 17.4 / 21.8, 201 and 280 35.3 / 37.4; but 92 and 1115 41.6 / 29.9, 150 and 1032 58.8 / 45.8).
 constexpr double kGeneralCost[kGeneralTiles] = {1.4, 1.6, 1.8, 2.2};
 inline int general_tile(Product prod, int64_t rows, int64_t len, const int64_t* group_cols, int G, bool vec)
 {
@@ -439,7 +440,7 @@ inline int general_tile(Product prod, int64_t rows, int64_t len, const int64_t* 
     if (!vec) {
         int64_t tiles = 0;
         for (int g = 0; g < G; ++g) tiles += (rows + 63) / 64 * ((group_cols[g] + 63) / 64);
-        const int most = prod == Product::Latent ? (best == 3 ? 160 : 80) : best == 3 ? 300 : tiles <= 512 ? 112 : 200;
+        const int most = prod == Product::Latent ? (best == 3 || tiles > 512 ? 160 : 80) : best == 3 ? 300 : tiles <= 512 ? 112 : 200;
         if (tiles > 256 && len <= most) return kGeneralShort;
     }
     return best;
