@@ -29,42 +29,92 @@ int launched()
     return err == hipSuccess ? BDA_OK : fail(BDA_EHIP, "kernel launch: %s", hipGetErrorString(err));
 }
 
-template <typename X, typename OutT, int TT, int TN, bool WEIGHT>
-int launch_mfma(const BwdArgs& a, hipStream_t st)
+// The gradients' tiles, largest first.
+typedef RingShape<128, 128, 1, 2, 4, 64, 4> LatentLarge;
+typedef RingShape<64, 128, 1, 2, 4, 64, 4> LatentMiddle;
+typedef RingShape<64, 64, 1, 1, 8, 128, 4> LatentSmall;
+typedef RingShape<192, 256, 2, 4, 1, 32, 5> WeightLarge;
+typedef RingShape<128, 256, 2, 4, 1, 32, 6> WeightMiddle;
+typedef RingShape<64, 128, 1, 2, 4, 64, 4> WeightSmall;
+typedef RingShape<64, 64, 1, 1, 4, 64, 4> WeightSmallest;
+
+// Tile grid of shape C: its number of tiles; rows x group_cols = extent of the output.
+template <typename C>
+int64_t ring_grid(BwdArgs& a, int64_t rows, const int64_t* group_cols, int G)
+{
+    int64_t n_tiles = 0;
+    a.tile_start[0] = 0;
+    for (int g = 0; g < G; ++g) {
+        n_tiles += (group_cols[g] + C::BN - 1) / C::BN;
+        a.tile_start[g + 1] = (int)n_tiles;
+    }
+    const int64_t m_tiles = (rows + C::BT - 1) / C::BT;
+    a.n_tiles = (int)n_tiles;
+    a.m_tiles = (int)m_tiles;
+    return m_tiles * n_tiles;
+}
+
+template <typename X, typename OutT, typename C, bool WEIGHT>
+int launch_ring(BwdArgs& a, int64_t rows, const int64_t* group_cols, int G, hipStream_t st)
 {
     static LdsLimitState once;
-    constexpr int lds = WEIGHT ? BwdWeightLds<TT, TN>::BYTES : BwdLds<TT, TN>::BYTES;
-    const int total = a.m_tiles * a.n_tiles;
-    const int grid = kNumXcd * ((total + kNumXcd - 1) / kNumXcd);
-    if constexpr (WEIGHT) {
-        auto kern = bwd_weight_kernel<X, OutT, TT, TN>;
-        if (int rc = allow_lds(kern, lds, once)) return rc;
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, st, a);
-    } else {
-        auto kern = bwd_latent_kernel<X, OutT, TT, TN>;
-        if (int rc = allow_lds(kern, lds, once)) return rc;
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, st, a);
-    }
+    const int64_t total = ring_grid<C>(a, rows, group_cols, G);
+    const int64_t grid = kNumXcd * ((total + kNumXcd - 1) / kNumXcd);
+    if (grid * C::THREADS >= (int64_t)1 << 32) return fail(BDA_EINVAL, "gradient of %lld tiles: too many for a launch", (long long)total);
+    constexpr int lds = WEIGHT ? C::BYTES : C::LATENT_BYTES;
+    const auto kern = [] {
+        if constexpr (WEIGHT) return ring_weight_kernel<X, OutT, C>;
+        else return ring_latent_kernel<X, OutT, C>;
+    }();
+    if (int rc = allow_lds(kern, lds, once)) return rc;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(C::THREADS), lds, st, a);
     return launched();
 }
 
-// The largest tile that still gives every compute unit a workgroup; rows x cols = extent of the output.
+// The tile whose rounds over the 256 compute units (a workgroup each; two of the weight gradient's smallest) are estimated
+// to take the least.  The factors are times measured over the tiles, per 64 elements of the contraction and, for the weight
+// gradient, in us; over 60 drawn launches the rule's tile is within 7 % of the fastest one.  A wrong tile: 4096 tokens,
+// d_c = 512, N = 4096 latent 33 / 26 / 34 us with the large, middle, small one; 1024 tokens 31 / 22 / 17; 8192 tokens,
+// N = 32768 276 / 387 / 441; weight, 4096 tokens, K = 384, N = 4096 65 / 43 / 24 / 28 with the four, 301 tokens, N = 7424
+// 11 / 8.9 / 12.7 / 11.4, 5861 tokens, N = 2560 89 / 58 / 33 / 28.
 template <typename X, typename OutT, bool WEIGHT>
 int launch_sized(BwdArgs& a, int64_t rows, const int64_t* group_cols, int G, hipStream_t st)
 {
-    auto grid = [&](int bt, int bn) {
-        a.tile_start[0] = 0;
-        for (int g = 0; g < G; ++g) a.tile_start[g + 1] = a.tile_start[g] + (int)((group_cols[g] + bn - 1) / bn);
-        a.n_tiles = a.tile_start[G];
-        a.m_tiles = (int)((rows + bt - 1) / bt);
-        return (int64_t)a.m_tiles * a.n_tiles;
-    };
-    const int policy = tile_policy();   // 1 forces the 128 x 128 tile (testing hook)
-    // (64 x 128 tiles were measured too: never faster than 64 x 64, which keeps two workgroups on a
-    // compute unit)
-    if (grid(128, 128) >= 256 || policy == 1) return launch_mfma<X, OutT, 2, 2, WEIGHT>(a, st);
-    grid(64, 64);
-    return launch_mfma<X, OutT, 1, 1, WEIGHT>(a, st);
+    auto rounds = [](int64_t tiles, int64_t slots) { return (double)((tiles + slots - 1) / slots); };
+    int pick = tile_policy() - 1;              // 1, 2, ...: that tile, from the largest (testing hook)
+    if constexpr (WEIGHT) {
+        if (pick < 0 || pick > 3) {
+            const double chunks = (double)((a.T + 63) / 64), start = 2.0;   // a round's first requests and stores: about 2 us
+            const int64_t smallest = ring_grid<WeightSmallest>(a, rows, group_cols, G);
+            const double cost[4] = {rounds(ring_grid<WeightLarge>(a, rows, group_cols, G), 256) * (1.25 * chunks + start),
+                                    rounds(ring_grid<WeightMiddle>(a, rows, group_cols, G), 256) * (0.8 * chunks + start),
+                                    rounds(ring_grid<WeightSmall>(a, rows, group_cols, G), 256) * (0.4 * chunks + start),
+                                    smallest <= 256 ? 0.24 * chunks + start : rounds(smallest, 512) * (0.45 * chunks + start)};
+            pick = 0;
+            for (int i = 1; i < 4; ++i)
+                if (cost[i] < cost[pick]) pick = i;
+        }
+        switch (pick) {
+        case 0: return launch_ring<X, OutT, WeightLarge, true>(a, rows, group_cols, G, st);
+        case 1: return launch_ring<X, OutT, WeightMiddle, true>(a, rows, group_cols, G, st);
+        case 2: return launch_ring<X, OutT, WeightSmall, true>(a, rows, group_cols, G, st);
+        default: return launch_ring<X, OutT, WeightSmallest, true>(a, rows, group_cols, G, st);
+        }
+    } else {
+        if (pick < 0 || pick > 2) {
+            const double cost[3] = {rounds(ring_grid<LatentLarge>(a, rows, group_cols, G), 256) * 1.35,
+                                    rounds(ring_grid<LatentMiddle>(a, rows, group_cols, G), 256),
+                                    rounds(ring_grid<LatentSmall>(a, rows, group_cols, G), 256) * 0.76};
+            pick = 0;
+            for (int i = 1; i < 3; ++i)
+                if (cost[i] < cost[pick]) pick = i;
+        }
+        switch (pick) {
+        case 0: return launch_ring<X, OutT, LatentLarge, false>(a, rows, group_cols, G, st);
+        case 1: return launch_ring<X, OutT, LatentMiddle, false>(a, rows, group_cols, G, st);
+        default: return launch_ring<X, OutT, LatentSmall, false>(a, rows, group_cols, G, st);
+        }
+    }
 }
 
 template <bool WEIGHT>

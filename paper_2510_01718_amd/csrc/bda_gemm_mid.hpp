@@ -5,15 +5,126 @@
 //
 // Such launches are bound by what a tile takes from its first load to its last store: a tile of 256 x 256 is on
 // few compute units and each of its stages has decisions per lane.  Here a workgroup is 8 waves = 2 halves of
-// 2 x 2 waves that take alternate chunks of 64 of the contraction (as in the gradient kernels: their LDS layouts,
-// fragment reads and sum of the halves are used); the first four chunks are requested before the first wait, so a
+// 2 x 2 waves that take alternate chunks of 64 of the contraction and whose float32 sums are added through LDS in a
+// fixed order; the first four chunks are requested before the first wait, so a
 // contraction of 256 waits for memory once; 64 x 64 tiles leave two workgroups on a compute unit, which cover one
 // another's prologue and epilogue.  The identity slice costs no stages: it is loaded as 8 bytes per lane and
 // 8 x 32 results while the halves are added, and summed in float32 before the one rounding.
 #pragma once
-#include "bda_bwd_kernels.hpp"
+#include <type_traits>
+
+#include "bda_gemm_kernels.hpp"
 
 namespace bda {
+
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f)
+{
+    if constexpr (N > 0) {
+        static_for<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
+}
+
+// Tiles are dealt to the dies in contiguous runs (workgroup b runs on die b % 8), so that tiles
+// that are neighbours in the run order -- they share one operand -- meet in the same L2.
+__device__ __forceinline__ int tile_of_block(int total)
+{
+    const int per_xcd = (total + kNumXcd - 1) / kNumXcd;
+    const int slot = blockIdx.x / kNumXcd;
+    const int tile = (blockIdx.x % kNumXcd) * per_xcd + slot;
+    return (slot < per_xcd && tile < total) ? tile : -1;
+}
+
+// Operands whose contraction index is the slow one in memory keep their rows in LDS, unpadded; their MFMA fragments come from
+// ds_read_b64_tr_b16: each lane names four consecutive columns of one row and receives four consecutive rows of one column.
+// Piece p (16 bytes) of row r sits at p ^ transpose_swz(r), so that the four rows one such read touches (64 bytes each) fall
+// into different quarters of the 256-byte bank line: rows of an odd number of 128 bytes pair up in a line and the pair
+// number picks the half; rows of whole lines pick the quarter by their number.  (The counter of bank conflicts: four cycles
+// per active one with 8 x 8 blocks transposed in registers, 0.8 with rows padded by 32 bytes, none so.)
+__host__ __device__ constexpr int transpose_swz(int pitch, int r) { return pitch % 256 == 128 ? ((r >> 1) & 1) * 4 : (r & 3) * 4; }
+
+template <typename X, typename OutT, int TT, int TN>
+__device__ __forceinline__ void mid_epilogue(const f32x16 (&acc)[TN][TT], __amdgpu_buffer_rsrc_t rD, int64_t ldo,
+                                             int cols_left, int wt, int wn, int l31, int lhi)
+{
+    const uint32_t ep_lane = (uint32_t)(wt * (32 * TT) + l31) * (uint32_t)(ldo * sizeof(OutT)) +
+                             (uint32_t)(wn * (32 * TN) + lhi * 4) * (uint32_t)sizeof(OutT);
+    const uint32_t ep_row_step = 32u * (uint32_t)(ldo * sizeof(OutT));
+#pragma unroll
+    for (int ti = 0; ti < TT; ++ti) {
+        const uint32_t row_off = ep_lane + (uint32_t)ti * ep_row_step;
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) {
+                const int c0 = ni * 32 + rg * 8;
+                if (wn * (32 * TN) + c0 >= cols_left) continue;   // uniform per wave: widths are multiples of 8
+                const uint32_t off = row_off + (uint32_t)c0 * (uint32_t)sizeof(OutT);
+                if constexpr (sizeof(OutT) == 4) {
+                    const float e0 = acc[ni][ti][rg * 4 + 0], e1 = acc[ni][ti][rg * 4 + 1];
+                    const float e2 = acc[ni][ti][rg * 4 + 2], e3 = acc[ni][ti][rg * 4 + 3];
+                    const f32x4 vf = {e0, e1, e2, e3};
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, vf), rD, off, 0, 0);
+                } else {
+                    u32x2 v;
+                    v[0] = X::pack2(acc[ni][ti][rg * 4 + 0], acc[ni][ti][rg * 4 + 1]);
+                    v[1] = X::pack2(acc[ni][ti][rg * 4 + 2], acc[ni][ti][rg * 4 + 3]);
+                    __builtin_amdgcn_raw_buffer_store_b64(v, rD, off, 0, 0);
+                }
+            }
+        }
+    }
+}
+
+// One staged chunk: 4 k-steps of TT x TN MFMAs.  read(ks, fw, ft) fetches the fragments of a step from LDS; they
+// are requested a step (one tile per wave: two steps) before their MFMAs, so that the reads' latency runs beside
+// the MFMAs instead of between them.
+template <typename X, int TT, int TN, typename Read>
+__device__ __forceinline__ void mid_mma_chunk(f32x16 (&acc)[TN][TT], Read&& read)
+{
+    constexpr int AHEAD = TT * TN == 1 ? 2 : 1, SETS = AHEAD + 1;
+    u32x4 fw[SETS][TN], ft[SETS][TT];
+#pragma unroll
+    for (int ks = 0; ks < AHEAD; ++ks) read(ks, fw[ks], ft[ks]);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        if (ks + AHEAD < 4) read(ks + AHEAD, fw[(ks + AHEAD) % SETS], ft[(ks + AHEAD) % SETS]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+            for (int ti = 0; ti < TT; ++ti) acc[ni][ti] = X::mfma(fw[ks % SETS][ni], ft[ks % SETS][ti], acc[ni][ti]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Adds half 1's accumulators to half 0's through LDS (all 8 waves call this after the last chunk).
+template <int TT, int TN>
+__device__ __forceinline__ void mid_reduce_halves(unsigned char* smem, f32x16 (&acc)[TN][TT], int half, int w4, int lane)
+{
+    __syncthreads();   // every wave is done reading the staged tiles
+    float* x = (float*)smem + (w4 * (TT * TN * 16)) * 64 + lane;
+    if (half == 1) {
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+            for (int ti = 0; ti < TT; ++ti)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) x[((ni * TT + ti) * 16 + r) * 64] = acc[ni][ti][r];
+    }
+    __syncthreads();
+    if (half == 0) {
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+            for (int ti = 0; ti < TT; ++ti)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[ni][ti][r] += x[((ni * TT + ti) * 16 + r) * 64];
+    }
+}
+
 
 template <int TT, int TN>
 struct MidLds {
@@ -31,7 +142,6 @@ template <typename X, typename OutT, int TT, int TN>
 __global__ __launch_bounds__(512, TT * TN > 1 ? 2 : 4) void gemm_mid_kernel(const GemmArgs p)
 {
     using L = MidLds<TT, TN>;
-    using W = BwdWeightLds<TT, TN>;                                 // swizzle of the weight rows
     constexpr int BT = L::BT, BN = L::BN;
     constexpr int TOK_LOADS = BT / 32;
     constexpr int WGT_PER_ROW = BN / 8, WGT_LOADS = 64 * WGT_PER_ROW / 256, WGT_ROWS_PER_PASS = 256 / WGT_PER_ROW;
@@ -40,7 +150,7 @@ __global__ __launch_bounds__(512, TT * TN > 1 ? 2 : 4) void gemm_mid_kernel(cons
     typedef __attribute__((address_space(3))) unsigned char* lds_u8;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
-    const int tile = bwd_tile_of_block(p.m_tiles * p.n_tiles);
+    const int tile = tile_of_block(p.m_tiles * p.n_tiles);
     if (tile < 0) return;
     const int mt = tile / p.n_tiles, nt = tile % p.n_tiles;         // the column tiles of one token tile share its rows
 
@@ -72,7 +182,7 @@ __global__ __launch_bounds__(512, TT * TN > 1 ? 2 : 4) void gemm_mid_kernel(cons
     const uint32_t tok_base = (uint32_t)trow * a_pitch;
     const int wpiece = tid % WGT_PER_ROW, wrow = tid / WGT_PER_ROW;
     const uint32_t wgt_base = wpiece * 8 < cols_left ? (uint32_t)wrow * b_pitch + (uint32_t)wpiece * 16u : kBadOffset;
-    const uint32_t wgt_lds = (uint32_t)(wrow * L::WGT_PITCH + ((wpiece ^ W::swz(L::WGT_PITCH, wrow)) * 16));
+    const uint32_t wgt_lds = (uint32_t)(wrow * L::WGT_PITCH + ((wpiece ^ transpose_swz(L::WGT_PITCH, wrow)) * 16));
     const int n_chunks = (p.K + 63) >> 6;
     const int n_it = (n_chunks + 1) >> 1;                           // chunks of this half: 2 it + half
 
@@ -109,7 +219,7 @@ __global__ __launch_bounds__(512, TT * TN > 1 ? 2 : 4) void gemm_mid_kernel(cons
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[ni][ti][r] = 0.0f;
 
-    // weight fragments: transposing reads, addressed as in bwd_weight_kernel
+    // weight fragments: transposing reads, see transpose_swz
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8)lds;
     const int c_s = lane & 15, c_q = lane >> 4;
     const int fr_row = 8 * (c_q >> 1) + (c_s >> 2), fr_col = 16 * (c_q & 1) + 4 * (c_s & 3);
@@ -117,7 +227,7 @@ __global__ __launch_bounds__(512, TT * TN > 1 ? 2 : 4) void gemm_mid_kernel(cons
 #pragma unroll
     for (int ni = 0; ni < TN; ++ni) {
         const int cb = (wn * (32 * TN) + 32 * ni + fr_col) * 2;
-        a_wgt[ni] = lds0 + (uint32_t)(L::WGT_BASE + fr_row * L::WGT_PITCH + (((cb >> 4) ^ W::swz(L::WGT_PITCH, fr_row)) << 4) + (cb & 15));
+        a_wgt[ni] = lds0 + (uint32_t)(L::WGT_BASE + fr_row * L::WGT_PITCH + (((cb >> 4) ^ transpose_swz(L::WGT_PITCH, fr_row)) << 4) + (cb & 15));
     }
     auto wgt_frag = [&](uint32_t addr) {
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(uintptr_t)addr);
@@ -132,7 +242,7 @@ __global__ __launch_bounds__(512, TT * TN > 1 ? 2 : 4) void gemm_mid_kernel(cons
         constexpr int S = decltype(set)::value;
         load_chunk(set, it + 2);
         const unsigned char* const tok_s = lds + tok_rd + S * L::TOK_STAGE;
-        bwd_mma_chunk<X, TT, TN>(acc, [&](int ks, u32x4 (&fw)[TN], u32x4 (&ft)[TT]) {
+        mid_mma_chunk<X, TT, TN>(acc, [&](int ks, u32x4 (&fw)[TN], u32x4 (&ft)[TT]) {
 #pragma unroll
             for (int ni = 0; ni < TN; ++ni) fw[ni] = wgt_frag(a_wgt[ni] + S * L::WGT_STAGE + 16 * ks * L::WGT_PITCH);
 #pragma unroll
@@ -170,7 +280,7 @@ __global__ __launch_bounds__(512, TT * TN > 1 ? 2 : 4) void gemm_mid_kernel(cons
                         rA, (uint32_t)(wt * (32 * TT) + ti * 32 + l31) * a_pitch + (uint32_t)(j0 + rg * 8 + lhi * 4) * 2u, 0, 0);
         }
     }
-    bwd_reduce_halves<TT, TN>(smem, acc, half, w4, lane);
+    mid_reduce_halves<TT, TN>(smem, acc, half, w4, lane);
     if (half != 0) return;
     if (ident) {
 #pragma unroll
@@ -183,7 +293,7 @@ __global__ __launch_bounds__(512, TT * TN > 1 ? 2 : 4) void gemm_mid_kernel(cons
                     acc[ni][ti][r] += X::to_f32((uint16_t)(r & 1 ? v >> 16 : v));
                 }
     }
-    bwd_epilogue<X, OutT, TT, TN>(acc, rD, p.ldd, cols_left, wt, wn, l31, lhi);
+    mid_epilogue<X, OutT, TT, TN>(acc, rD, p.ldd, cols_left, wt, wn, l31, lhi);
 }
 
 }  // namespace bda

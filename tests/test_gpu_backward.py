@@ -218,6 +218,45 @@ def test_backward_tile_shapes_chosen_by_size():
     _check(8200, 512, 128, [1], [128], wl.BF16)
 
 
+# Edges of every tile (policies 1 .. 4): outputs of a tile and a few rows or columns, contractions shorter than the ring of stages
+# and one element past a stage, windows that cut a 32-column block at either end, groups that end inside a tile and a stage.
+EDGES = [
+    (193, 448, 64, [5, 1], [16, 376]),
+    (129, 576, 192, [1, 2], [40, 344]),
+    (65, 136, 96, [1, 1, 1], [0, 24, 40]),
+    (1, 200, 32, [9], [88]),
+    (33, 264, 256, [1], [8]),
+    (257, 328, 128, [3], [200]),
+    (520, 64, 32, [17, 8], [0, 32]),
+]
+
+
+@pytest.mark.parametrize("dtype,grad_dtype", [(wl.F16, wl.F32), (wl.BF16, wl.BF16)])
+@pytest.mark.parametrize("T,d_c,d_h,H,offs", EDGES)
+@pytest.mark.parametrize("policy", [1, 2, 3, 4])
+def test_backward_every_tile_edges(T, d_c, d_h, H, offs, dtype, grad_dtype, policy):
+    """Tolerance as everywhere here; the longest contraction has 1056 terms, whose float32 sums are off by about
+    sqrt(1056) 2^-24 = 2e-6 of the result's size, far below a result's own rounding."""
+    _check(T, d_c, d_h, H, offs, dtype, grad_dtype=grad_dtype, pad=8, policy=policy, seed=17)
+
+
+def test_backward_gradients_aligned_to_eight_bytes():
+    """16-bit gradients may start on any multiple of 8 bytes: a column view of a wider buffer."""
+    T, d_c, d_h, H, offs, dtype = 200, 256, 64, [2, 3], [0, 128], wl.F16
+    (c_s, c64), (g_s, g64), (C_s, C64) = _inputs(19, T, d_c, d_h, H, dtype)
+    ref_c, ref_C = oracle.kv_project_backward(c64, g64, C64, d_h, H, offs)
+    N, K = sum(H) * d_h, d_c - d_h
+    c_d, g_d, C_d = gh.to_device(c_s, dtype), gh.to_device(g_s, dtype), gh.to_device(C_s, dtype)
+    gc_d, gC_d = gh.new_out(T, d_c + 8, dtype, 3.0), gh.new_out(K, N + 8, dtype, 3.0)
+    bda.bda_kv_project_backward(c_d, d_c, g_d, N, C_d, N, T, d_c, d_h, H, offs, gc_d.data_ptr() + 8, d_c + 8, gC_d.data_ptr() + 8, N + 8,
+                                dtype, dtype, gh.stream())
+    torch.cuda.synchronize()
+    gc, gC = gh.to_host64(gc_d, dtype), gh.to_host64(gC_d, dtype)
+    assert_parity(gc[:, 4:-4], ref_c, 1, dtype, dtype, "grad_c")
+    assert_parity(gC[:, 4:-4], ref_C, 1, dtype, dtype, "grad_C")
+    assert np.all(gc[:, :4] == 3) and np.all(gc[:, -4:] == 3) and np.all(gC[:, :4] == 3) and np.all(gC[:, -4:] == 3)
+
+
 def test_backward_each_gradient_alone_and_no_tokens():
     T, d_c, d_h, H, offs, dtype = 90, 256, 64, [2, 1], [0, 192], wl.F16
     (c_s, c64), (g_s, g64), (C_s, C64) = _inputs(9, T, d_c, d_h, H, dtype)
