@@ -100,9 +100,10 @@ struct PrepArgs {
     int h0;                      // first head of this launch (batches when the block lives in the workspace)
     int cand, n_cand, n_parts;   // first candidate window of this launch and their number
     int w_type, c_type;          // element types of W / side and of C / side_out
-    int per_row;                 // O: pieces of d_h columns in a row of the companion output (see Slot)
-    uint32_t per_row_magic;
+    int search, c_slots;         // candidate windows in the outputs; how many of them in C (see Slot)
+    uint32_t width_magic;        // ceil(2^32 / d_h) (O)
     int write_side, measure;     // strip_kernel: store the companion block; sum the reconstruction errors
+    int lane_sums;               // measure_kernel: one sum per lane in LDS
 };
 
 // Start of window `z` of this launch, or -1.
@@ -114,27 +115,27 @@ __device__ __forceinline__ int window_start(const PrepArgs& a, int z = 0)
 }
 
 // Where window `z` of a launch keeps its stored C: row kk of head h, d_h contiguous elements, begins at element
-// slot_row() of the array.  The first window has C itself.  During a search the companion output is free until
-// the chosen window is prepared, and holds the others: d_c - d_h of its rows each (Q: the layout of C), or as
-// many pieces of d_h columns of the head's own d_h rows, a.per_row of them in a row (O).
+// slot_row() of the array.  The call's one window has C itself.  During a search C and the companion output are free until
+// the chosen window is written and hold the candidates': C one of them (a.c_slots) and the companion output the others,
+// d_c - d_h of its rows each (Q: the layout of C), or as many pieces of d_h columns of the head's own d_h rows, a column of
+// pieces after the other (O: so that 16 consecutive rows from a multiple of 16 on stay together where d_h has that factor).
 struct Slot {
     void* p;
     int64_t ld;
-    int first, per_row;          // pieces before this window's; 0: rows of C's layout
-    uint32_t magic;              // ceil(2^32 / per_row)
+    int first;                   // rows or pieces before this window's
+    uint32_t magic;              // ceil(2^32 / d_h); 0: rows of C's layout
 };
 __device__ __forceinline__ Slot slot_of(const PrepArgs& a, int z)
 {
-    const int first = (z - 1) * (a.d_c - a.d_h);
-    if (z == 0) return {a.C, a.ldC, 0, 0, 0};
-    return {a.side_out, a.ld_side_out, first, a.per_row, a.per_row_magic};
+    if (!a.search || z < a.c_slots) return {a.C, a.ldC, 0, 0};
+    return {a.side_out, a.ld_side_out, (z - a.c_slots) * (a.d_c - a.d_h), a.side_kind == BDA_SIDE_O ? a.width_magic : 0};
 }
 __device__ __forceinline__ int64_t slot_row(const Slot& s, int kk, int h, int n)
 {
     const int q = s.first + kk;
-    if (!s.per_row) return q * s.ld + (int64_t)h * n;
-    const int row = s.per_row == 1 ? q : (int)__umulhi((uint32_t)q, s.magic);
-    return ((int64_t)h * n + row) * s.ld + (q - row * s.per_row) * n;
+    if (!s.magic) return q * s.ld + (int64_t)h * n;
+    const int block = (int)__umulhi((uint32_t)q, s.magic);
+    return ((int64_t)h * n + (q - block * n)) * s.ld + block * n;
 }
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -152,6 +153,15 @@ __device__ __forceinline__ void with_type(int type, F&& f)
     else if (type == BDA_F16) f(_Float16{});
     else if (type == BDA_BF16) f(__bf16{});
     else f(double{});
+}
+
+template <int N, typename F>
+__device__ __forceinline__ void static_for_blocks(F&& f)
+{
+    if constexpr (N > 0) {
+        static_for_blocks<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
 }
 
 // Largest of a 32-bit value over the 64 lanes, in every lane.
@@ -730,6 +740,32 @@ template <typename T> __device__ __forceinline__ T rounded(double v)
 }
 template <typename T> __device__ __forceinline__ double widened(T v) { return load_as_double<T>(&v, 0); }
 
+// widened(rounded<T>(v)) in a few integer operations: the upper word of a double keeps M mantissa bits, to nearest even, and
+// below the smallest normal T the distance of neighbours stays 2^-E, which one addition rounds to.  (Written as rounded and
+// widened it is some 25 instructions, and vector instructions do not run beside the float64 MFMAs.)
+template <typename T>
+__device__ __forceinline__ double round_trip(double v)
+{
+    if constexpr (sizeof(T) != 2) {
+        return widened<T>(rounded<T>(v));
+    } else {
+        constexpr bool kHalf = std::is_same<T, _Float16>::value;
+        constexpr int M = kHalf ? 10 : 7;
+        constexpr double kMinNormal = kHalf ? 0x1p-14 : 0x1p-126, kUlp = kHalf ? 0x1.8p28 : 0x1.8p-81, kMax = kHalf ? 65520.0 : 0x1.ffp127;
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        constexpr int drop = 52 - M;
+        const uint64_t r = (b + ((((uint64_t)1 << (drop - 1)) - 1) + ((b >> drop) & 1))) & ~(((uint64_t)1 << drop) - 1);
+        double x = __builtin_bit_cast(double, r);
+        const double mag = fabs(v);
+        if (mag < kMinNormal) {
+            const double s = copysign(kUlp, v);
+            x = copysign((v + s) - s, v);
+        }
+        if (mag >= kMax) x = copysign(__builtin_huge_val(), v);
+        return v == v ? x : v;
+    }
+}
+
 template <typename T>
 struct Eight {
     T e[8];
@@ -968,6 +1004,296 @@ __global__ __launch_bounds__(kStripThreads) void strip_kernel(const PrepArgs a)
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// strip_kernel's measuring forms for the shapes that nearly every projection has: head widths 32 NBLK, latents of whole
+// 16-column tiles, windows that start on multiples of 16, 16-byte aligned rows, 16-bit results.  A tile then lies inside a
+// window or outside it, a lane's operands are always eight elements, and nothing in the loops depends on the lane but
+// addresses.  What that buys is exact counts of loads in flight: with a branch per lane the compiler waits for every load
+// before it uses any, so that the blocks fetched ahead were waited for at once (MFMA pipes busy 55 %).  Buffer loads return
+// zeros past the arrays' ends.  LDS holds the strip of -Phat, and a window's first product starts from P itself.
+// Vector instructions do not run beside the float64 MFMAs (one between every two MFMAs of a loop costs 12 cycles, four 19,
+// of the MFMA's 64), so conversions come together, addresses are scalar and a lane's squares stay in LDS till the end.
+// Same sums as strip_kernel, in the same order but for a lane's squares over the strips.
+// Against strip_kernel: 25 windows of 16 heads for keys and values 7.05 -> 6.0 ms, two windows of 128 heads 2.15 -> 1.87 (with
+// the chosen window copied instead of prepared again; the matrix pipes busy 69 % of the time, 54 before).
+// ---------------------------------------------------------------------------------------------
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+constexpr uint32_t kNoOffset = 0x80000000u;   // beyond every range here
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t range_of(const void* p, int64_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+template <typename T>
+__device__ __forceinline__ Eight<T> load8(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
+{
+    constexpr int Q = (int)sizeof(T) / 2;
+    struct { u32x4_t w[Q]; } v;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) v.w[q] = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff + 16 * q, 0);
+    return __builtin_bit_cast(Eight<T>, v);
+}
+
+template <typename WT, typename CT, int NBLK, StripForm F>
+__global__ __launch_bounds__(kStripThreads) void measure_kernel(const PrepArgs a)
+{
+    constexpr int TILES = strip_tiles(F), n = 32 * NBLK, lds_s = strip_pitch_s(n);
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    double* const ph = (double*)smem_raw;      // first the strip of S, then the rounded strip of -P
+    const int d_c = a.d_c, t = threadIdx.x, lane = t & 63, c = lane & 15, g = lane >> 4;
+    const int threads = F == StripForm::Wide ? kStripThreads : blockDim.x, nw = threads >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int h = blockIdx.x, n_tiles = d_c / 16;
+    const int64_t col0 = (int64_t)h * n;
+    const bool q_side = a.side_kind == BDA_SIDE_Q;
+    const int lds_p = strip_pitch_p(d_c);
+    const int z_lo = (int)((int64_t)a.n_cand * blockIdx.z / gridDim.z), z_hi = (int)((int64_t)a.n_cand * (blockIdx.z + 1) / gridDim.z);
+    double* const sums = ph + strip_words(d_c, n);                           // [wave][window - z_lo]
+    const int n_z = z_hi - z_lo;
+    const WT* const S = (const WT*)a.side;
+    CT* const side_out = (CT*)a.side_out;
+    const bool lane_sums = a.lane_sums;
+    for (int z = lane; z < (lane_sums ? 64 * n_z : n_z); z += 64) sums[wave * n_z * (lane_sums ? 64 : 1) + z] = 0.0;
+
+    const __amdgpu_buffer_rsrc_t rW = range_of((const WT*)a.W + col0, ((int64_t)(d_c - 1) * a.ldw + n) * (int64_t)sizeof(WT));
+    const __amdgpu_buffer_rsrc_t rC = range_of(a.C, ((int64_t)(d_c - n - 1) * a.ldC + (int64_t)a.H * n) * (int64_t)sizeof(CT));
+    const int64_t out_rows = q_side ? a.d_side : (int64_t)a.H * n, out_cols = q_side ? (int64_t)a.H * n : a.d_side;
+    const __amdgpu_buffer_rsrc_t rO = range_of(a.side_out, ((out_rows - 1) * a.ld_side_out + out_cols) * (int64_t)sizeof(CT));
+    auto tile = [&](int j) { return wave + nw * j; };
+    auto in_window = [&](int off, int j) { return 16 * tile(j) >= off && 16 * tile(j) < off + n; };
+    const uint32_t c_lane = (uint32_t)(c * a.ldC + 8 * g) * (uint32_t)sizeof(CT), o_lane = (uint32_t)(c * a.ld_side_out + 8 * g) * (uint32_t)sizeof(CT);
+    uint32_t w_off[TILES];
+#pragma unroll
+    for (int j = 0; j < TILES; ++j)
+        w_off[j] = tile(j) < n_tiles ? (uint32_t)((16 * tile(j) + c) * a.ldw + 8 * g) * (uint32_t)sizeof(WT) : kNoOffset;
+
+    // The strip of S.  Eight waves have a fixed share of it, fetched while the windows of the strip before are measured (a
+    // compute unit holds one workgroup, so nothing else covers the fetch); fewer waves are several workgroups.
+    constexpr bool kAhead = F == StripForm::Wide;
+    constexpr int OWN = kAhead ? kStripRows * n / kStripThreads : 1;
+    WT own[OWN];
+    auto s_place = [&](int e, int& r, int& k) {  // element e of this thread's
+        const int i = e * kStripThreads + t;
+        r = q_side ? i / n : i % kStripRows;
+        k = q_side ? i % n : i / kStripRows;
+    };
+    auto fetch_s = [&](int s0) {
+#pragma unroll
+        for (int e = 0; e < OWN; ++e) {
+            int r, k;
+            s_place(e, r, k);
+            own[e] = (WT)0.0f;
+            if (s0 + r < a.d_side) own[e] = q_side ? S[(int64_t)(s0 + r) * a.ld_side + col0 + k] : S[(col0 + k) * a.ld_side + s0 + r];
+        }
+    };
+    const int n_strips = (a.d_side + kStripRows - 1) / kStripRows;
+    if (kAhead) fetch_s(blockIdx.y * kStripRows);
+    for (int strip = blockIdx.y; strip < n_strips; strip += gridDim.y) {
+        const int s0 = strip * kStripRows;
+        Eight<WT> w[2][TILES];
+#pragma unroll
+        for (int j = 0; j < TILES; ++j) w[0][j] = load8<WT>(rW, w_off[j], 0);
+        __syncthreads();                       // the strip before is no longer read
+        if constexpr (kAhead) {
+#pragma unroll
+            for (int e = 0; e < OWN; ++e) {
+                int r, k;
+                s_place(e, r, k);
+                ph[r * lds_s + k] = widened<WT>(own[e]);
+            }
+        } else if (q_side) {
+            constexpr int PER = n % 64 ? 32 : 64, ROWS = 64 / PER;            // columns and rows of a wave's load
+#pragma unroll
+            for (int k = 0; k < n; k += PER)
+#pragma unroll 4
+                for (int r = wave * ROWS + lane / PER; r < kStripRows; r += nw * ROWS) {
+                    const int kk = k + lane % PER;
+                    ph[r * lds_s + kk] = s0 + r < a.d_side ? widened<WT>(S[(int64_t)(s0 + r) * a.ld_side + col0 + kk]) : 0.0;
+                }
+        } else {
+            const int r = t % kStripRows;
+#pragma unroll 4
+            for (int k = t / kStripRows; k < n; k += threads / kStripRows)
+                ph[r * lds_s + k] = s0 + r < a.d_side ? widened<WT>(S[(col0 + k) * a.ld_side + s0 + r]) : 0.0;
+        }
+        __syncthreads();
+
+        // ---- P: rows s0 .. s0 + 31, this wave's column tiles ----
+        f64x4 P[TILES][2];
+#pragma unroll
+        for (int j = 0; j < TILES; ++j) P[j][0] = P[j][1] = (f64x4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int b = 0; b < NBLK; ++b) {
+            if (b + 1 < NBLK) {
+#pragma unroll
+                for (int j = 0; j < TILES; ++j) w[(b + 1) & 1][j] = load8<WT>(rW, w_off[j], (uint32_t)(32 * (b + 1) * sizeof(WT)));
+            }
+            f64x2 av[2][4];
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) av[rt][s] = *(const f64x2*)(ph + (16 * rt + c) * lds_s + 32 * b + 8 * g + 2 * s);
+#pragma unroll
+            for (int j = 0; j < TILES; ++j) {
+                if (tile(j) >= n_tiles) continue;
+                double bv[8];
+#pragma unroll
+                for (int s = 0; s < 8; ++s) bv[s] = widened<WT>(w[b & 1][j].e[s]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int s = 0; s < 8; ++s) {
+                    P[j][0] = mfma_f64(av[0][s >> 1][s & 1], bv[s], P[j][0]);
+                    P[j][1] = mfma_f64(av[1][s >> 1][s & 1], bv[s], P[j][1]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+
+        // Rows of the stored Chat for window z.  Everything that changes with the window is scalar: a tile's 16 rows are
+        // consecutive rows of the output (see Slot).  A tile inside the window, or past the last, fetches rows of another.
+        Eight<CT> ct[2][TILES];
+        int off = 0, next_off = 0;
+        bool in_c = false;
+        uint32_t c_soff[TILES];
+        auto enter_window = [&](int z) {
+            next_off = window_start(a, z);
+            const Slot slot = slot_of(a, z);
+            in_c = !a.search || z < a.c_slots;
+#pragma unroll
+            for (int j = 0; j < TILES; ++j) {
+                const int l0 = 16 * tile(j);
+                const int kk0 = l0 < next_off ? l0 : l0 >= next_off + n && l0 < d_c ? l0 - n : 0;
+                c_soff[j] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(slot_row(slot, kk0, h, n) * (int64_t)sizeof(CT)));
+            }
+        };
+        auto fetch = [&](auto set, uint32_t block) {
+            const __amdgpu_buffer_rsrc_t r = in_c ? rC : rO;
+            const uint32_t voff = in_c ? c_lane : o_lane;
+#pragma unroll
+            for (int j = 0; j < TILES; ++j) ct[decltype(set)::value][j] = load8<CT>(r, voff, c_soff[j] + block * (uint32_t)(32 * sizeof(CT)));
+        };
+        if (n_z > 0) {
+            enter_window(z_lo);
+            fetch(std::integral_constant<int, 0>{}, 0);
+        }
+        __syncthreads();                       // the strip of S is no longer read
+#pragma unroll
+        for (int j = 0; j < TILES; ++j)
+            if (tile(j) < n_tiles) {
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) ph[(16 * rt + 4 * r + g) * lds_p + 16 * tile(j) + c] = -round_trip<CT>(P[j][rt][r]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        __syncthreads();
+
+        if (a.write_side) {
+            const int off0 = window_start(a);
+            for (int e = t; e < kStripRows * n; e += threads) {
+                const int r = q_side ? e / n : e % kStripRows, i = q_side ? e % n : e / kStripRows;
+                if (s0 + r < a.d_side) {
+                    const CT v = rounded<CT>(-ph[r * lds_p + off0 + i]);
+                    if (q_side) side_out[(int64_t)(s0 + r) * a.ld_side_out + col0 + i] = v;
+                    else side_out[(col0 + i) * a.ld_side_out + s0 + r] = v;
+                }
+            }
+        }
+
+        if (kAhead && strip + (int)gridDim.y < n_strips) fetch_s(s0 + (int)gridDim.y * kStripRows);
+
+        // ---- the windows: blocks of the contraction outside, this wave's tiles inside, so that a block's row operand is read
+        // once for all of them; the column operands are fetched one block ahead, across windows ----
+        auto window = [&](auto set0, int z) {  // set0: where the window's first block has been fetched to
+            constexpr int S0 = decltype(set0)::value;
+            off = next_off;
+            f64x4 acc[TILES][2];
+            static_for_blocks<NBLK>([&](auto bc) {
+                constexpr int b = decltype(bc)::value, now = (S0 + b) & 1;
+                if constexpr (b + 1 == NBLK) {
+                    if (z + 1 < z_hi) enter_window(z + 1);   // (past the last window: its own blocks once more)
+                    fetch(std::integral_constant<int, 1 - now>{}, 0);
+                } else {
+                    fetch(std::integral_constant<int, 1 - now>{}, b + 1);
+                }
+#pragma unroll
+                for (int half = 0; half < 8; half += 4) {
+                    f64x2 av[2][2];
+#pragma unroll
+                    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                        for (int s = 0; s < 2; ++s) av[rt][s] = *(const f64x2*)(ph + (16 * rt + c) * lds_p + off + 32 * b + 8 * g + half + 2 * s);
+#pragma unroll
+                    for (int j = 0; j < TILES; ++j)
+                        if (tile(j) < n_tiles && !in_window(off, j)) {
+                            double bv[4];      // (together, ahead of the MFMAs: vector instructions between them cost three times as much)
+#pragma unroll
+                            for (int s = 0; s < 4; ++s) bv[s] = widened<CT>(ct[now][j].e[half + s]);
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                            for (int s = 0; s < 4; ++s) {
+                                acc[j][0] = mfma_f64(av[0][s >> 1][s & 1], bv[s], b + half + s == 0 ? P[j][0] : acc[j][0]);
+                                acc[j][1] = mfma_f64(av[1][s >> 1][s & 1], bv[s], b + half + s == 0 ? P[j][1] : acc[j][1]);
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                }
+            });
+            double r2 = 0.0;
+#pragma unroll
+            for (int j = 0; j < TILES; ++j) {
+                if (tile(j) >= n_tiles) continue;
+                if (in_window(off, j)) {
+#pragma unroll
+                    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const double d = P[j][rt][r] + ph[(16 * rt + 4 * r + g) * lds_p + 16 * tile(j) + c];
+                            r2 = fma(d, d, r2);
+                        }
+                } else {
+#pragma unroll
+                    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) r2 = fma(acc[j][rt][r], acc[j][rt][r], r2);
+                }
+            }
+            if (lane_sums) {                   // (added over the lanes once, at the end)
+                sums[(wave * n_z + z - z_lo) * 64 + lane] += r2;
+            } else {
+                for (int s = 32; s >= 1; s >>= 1) r2 += __shfl_xor(r2, s, 64);
+                if (lane == 0) sums[wave * n_z + z - z_lo] += r2;
+            }
+        };
+        const std::integral_constant<int, 0> set0;
+        const std::integral_constant<int, 1> set1;
+        if constexpr (NBLK % 2 == 0) {
+            for (int z = z_lo; z < z_hi; ++z) window(set0, z);
+        } else {
+            for (int z = z_lo;;) {
+                if (z >= z_hi) break;
+                window(set0, z++);
+                if (z >= z_hi) break;
+                window(set1, z++);
+            }
+        }
+    }
+    if (lane_sums)
+        for (int z = 0; z < n_z; ++z) {
+            double* const at = sums + (wave * n_z + z) * 64;
+            double r2 = at[lane];
+            for (int s = 32; s >= 1; s >>= 1) r2 += __shfl_xor(r2, s, 64);
+            if (lane == 0) at[0] = r2;
+        }
+    __syncthreads();
+    for (int z = z_lo + t; z < z_hi; z += threads) {
+        double sum = 0.0;
+        for (int w = 0; w < nw; ++w) sum += sums[(w * n_z + z - z_lo) * (lane_sums ? 64 : 1)];
+        a.partials[((size_t)(a.cand + z) * a.H + h) * a.n_parts + blockIdx.y] = sum;
+    }
+}
+
 struct SelectArgs {
     double* partials;           // (a head's first part is overwritten with the root of its sum)
     const int* cand_singular;
@@ -1020,6 +1346,24 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(const SelectArgs
     }
     *a.basis_offset_out = best_off;
     if (a.resid_out) { a.resid_out[0] = r_first; a.resid_out[1] = r_last; a.resid_out[2] = best; }
+}
+
+// The chosen window's stored C from its slot to C: a wave per piece of d_h elements at a time.
+template <typename CT>
+__global__ __launch_bounds__(256) void copy_kernel(const PrepArgs a)
+{
+    const int off = *a.off_ptr, n = a.d_h, K = a.d_c - n;
+    if (off < 0) return;
+    int z = 0;
+    while (z + 1 < a.n_cand && (a.off + z * a.off_step < a.off_last ? a.off + z * a.off_step : a.off_last) != off) ++z;
+    const Slot slot = slot_of(a, z);
+    const int lane = threadIdx.x & 63;
+    for (int64_t e = blockIdx.x * 4 + (threadIdx.x >> 6); e < (int64_t)K * a.H; e += gridDim.x * 4) {
+        const int h = (int)(e / K), kk = (int)(e % K);
+        const CT* const from = (const CT*)slot.p + slot_row(slot, kk, h, n);
+        CT* const to = (CT*)a.C + kk * a.ldC + (int64_t)h * n;
+        for (int i = lane; i < n; i += 64) to[i] = from[i];
+    }
 }
 
 __global__ void fill_int_kernel(int* p, int n, int v)
@@ -1081,6 +1425,31 @@ int launch_prepare(PrepArgs a, int batch, hipStream_t st)
     return BDA_OK;
 }
 
+// Whether measure_kernel takes the windows of this launch: see there.
+template <typename WT, typename CT>
+bool regular_windows(const PrepArgs& a)
+{
+    const int64_t N = (int64_t)a.H * a.d_h, limit = (int64_t)1 << 31;
+    const bool q = a.side_kind == BDA_SIDE_Q;
+    const int64_t out_rows = q ? a.d_side : N, out_cols = q ? N : a.d_side;
+    return a.d_h % 32 == 0 && a.d_h <= kPrepLdsDh && a.d_c % 16 == 0 && a.off % 16 == 0 && a.off_step % 16 == 0 && a.off_last % 16 == 0 && !a.off_ptr &&
+           aligned(a.W, 16) && a.ldw * (int64_t)sizeof(WT) % 16 == 0 && aligned(a.C, 16) && a.ldC * (int64_t)sizeof(CT) % 16 == 0 &&
+           (a.n_cand == 1 || (aligned(a.side_out, 16) && a.ld_side_out * (int64_t)sizeof(CT) % 16 == 0)) &&
+           a.d_c * a.ldw * (int64_t)sizeof(WT) < limit && a.d_c * a.ldC * (int64_t)sizeof(CT) < limit &&
+           ((out_rows - 1) * a.ld_side_out + out_cols) * (int64_t)sizeof(CT) < limit;
+}
+
+constexpr int kMeasureLds = 160 * 1024;
+
+template <typename WT, typename CT, int NBLK, StripForm F>
+int launch_measure(const PrepArgs& a, dim3 grid, int threads, int lds, int max_lds, hipStream_t st)
+{
+    static LdsLimitState once;
+    if (int rc = raise_lds((const void*)measure_kernel<WT, CT, NBLK, F>, max_lds, once)) return rc;
+    hipLaunchKernelGGL((measure_kernel<WT, CT, NBLK, F>), grid, dim3(threads), lds, st, a);
+    return check_launch("companion kernel");
+}
+
 // Waves of a workgroup: as few as hold the strip's column tiles in their registers, so that narrow latents and heads
 // leave none idle and a compute unit takes several workgroups; more, up to one per tile, while the launch would not
 // give every compute unit eight waves.
@@ -1101,6 +1470,22 @@ int launch_strip(const PrepArgs& a, hipStream_t st)
     const int64_t busy = a.H * std::min(n_strips, parts) * nw;
     const int split = measure ? (int)std::max<int64_t>(1, std::min<int64_t>(4096 / busy, a.n_cand)) : 1;
     const int lds = (strip_words(width, a.d_h) + (measure ? nw * ((a.n_cand + split - 1) / split) : 0)) * (int)sizeof(double);
+    if constexpr (measure && sizeof(CT) == 2 && sizeof(WT) <= 4) {
+        if (regular_windows<WT, CT>(a)) {
+            const dim3 grid(a.H, (unsigned)parts, split);
+            // the lanes' sums in LDS where they fit the limit that the kernel was given
+            PrepArgs m = a;
+            const int most = strip_words(width, a.d_h) * (int)sizeof(double) + nw * ((a.n_cand + split - 1) / split) * 64 * (int)sizeof(double);
+            m.lane_sums = most <= kMeasureLds;
+            const int lds_m = m.lane_sums ? most : lds;
+            switch (a.d_h / 32) {
+            case 1: return launch_measure<WT, CT, 1, F>(m, grid, 64 * nw, lds_m, kMeasureLds, st);
+            case 2: return launch_measure<WT, CT, 2, F>(m, grid, 64 * nw, lds_m, kMeasureLds, st);
+            case 3: return launch_measure<WT, CT, 3, F>(m, grid, 64 * nw, lds_m, kMeasureLds, st);
+            default: return launch_measure<WT, CT, 4, F>(m, grid, 64 * nw, lds_m, kMeasureLds, st);
+            }
+        }
+    }
     hipLaunchKernelGGL((strip_kernel<WT, CT, F>), dim3(a.H, (unsigned)parts, split), dim3(64 * nw), lds, st, a);
     return check_launch("companion kernel");
 }
@@ -1195,16 +1580,20 @@ int run_prepare(const PrepCall& c, const Plan& p, unsigned char* ws, hipStream_t
     a.measure = p.want_resid;
     // Candidate windows that one launch prepares and measures: as many stored C's as the outputs have room for
     // until the chosen window is known.
+    // A search of a few windows that the companion output can hold alone leaves C out of it: the chosen one is then
+    // copied to C, where larger searches prepare it once more (two windows of 128 heads: 178 us).
     int slots = 1;
+    const int K = c.d_c - c.d_h;
+    a.c_slots = 1;
     if (multi && companion && !p.big && c.d_c <= kStripMaxDc) {
-        const int K = c.d_c - c.d_h;
-        if (c.side_kind == BDA_SIDE_O) {
-            a.per_row = std::min(c.d_side / c.d_h, 1024);
-            a.per_row_magic = a.per_row > 1 ? (uint32_t)((((uint64_t)1 << 32) + a.per_row - 1) / a.per_row) : 0;
-            slots += c.d_h * a.per_row / K;
-        } else {
-            slots += c.d_side / K;
+        a.search = 1;
+        int beside = c.d_side / K;
+        if (c.side_kind == BDA_SIDE_O) {       // (one head width: a multiplication in place of the division; exact to 2^24 pieces)
+            a.width_magic = c.d_h > 1 ? (uint32_t)((((uint64_t)1 << 32) + c.d_h - 1) / c.d_h) : 0;
+            beside = c.d_h > 1 ? c.d_h * std::min(c.d_side / c.d_h, 1024) / K : 0;
         }
+        a.c_slots = beside >= p.n_cand ? 0 : 1;
+        slots = beside + a.c_slots;
     }
     for (int ci = 0; ci < p.n_cand; ci += slots) {
         a.cand = ci;
@@ -1230,15 +1619,23 @@ int run_prepare(const PrepCall& c, const Plan& p, unsigned char* ws, hipStream_t
         if (int rc = check_launch("fill kernel")) return rc;
     }
     if (multi) {
-        // the chosen window once more, into the outputs for good (its start is read on the device)
+        // the chosen window into the outputs for good (its start is read on the device)
+        const bool copy = a.search && a.c_slots == 0;
         a.off_ptr = c.basis_offset_out;
+        if (copy) {
+            const int64_t pieces = (int64_t)K * c.H;
+            hipLaunchKernelGGL((copy_kernel<CT>), dim3((unsigned)std::min<int64_t>((pieces + 7) / 8, 2048)), dim3(256), 0, st, a);
+            if (int rc = check_launch("copy kernel")) return rc;
+        }
+        a.search = 0;
         a.cand = 0;
         a.n_cand = 1;
         a.cand_singular = nullptr;
         a.status = c.singular_head;
         a.measure = 0;
         a.write_side = 1;
-        if (int rc = launch_prepare<WT, CT>(a, p.batch, st)) return rc;
+        if (!copy)
+            if (int rc = launch_prepare<WT, CT>(a, p.batch, st)) return rc;
         if (companion) return launch_companion<WT, CT>(a, st);
     }
     return BDA_OK;

@@ -274,6 +274,34 @@ def test_prepare_device_ex_weights_as_stored(w_dtype, store, side_kind, pad_in, 
         assert (np.isnan(g) and np.isnan(r)) or abs(g - r) <= 1e-6 * abs(r), (got["resid"], resid_ref)
 
 
+@pytest.mark.parametrize("w_dtype,store", [(wl.F32, wl.F16), (wl.BF16, wl.BF16)])
+@pytest.mark.parametrize("side_kind", [oracle.SIDE_Q, oracle.SIDE_O])
+@pytest.mark.parametrize("d_c,H,d_h,d_side,mode", [
+    (48, 2, 32, 97, oracle.OFFSET_SEARCH),         # three column tiles, the least; strips that end inside one
+    (272, 1, 96, 33, oracle.OFFSET_SEARCH),        # the fewest tiles of the eight-wave form, an odd number of blocks, windows one by one
+    (512, 2, 128, 500, oracle.OFFSET_SEARCH),      # the most; several batches of windows, the last one short
+    (256, 3, 128, 1030, oracle.RESIDUAL_MIN),      # both windows beside C, which the chosen one is copied to
+    (320, 2, 64, 300, oracle.LAST),                # one window, measured and written at once
+])
+def test_prepare_device_ex_regular_windows(w_dtype, store, side_kind, d_c, H, d_h, d_side, mode):
+    """The form for head widths of whole blocks of 32 and windows on whole column tiles."""
+    test_prepare_device_ex_weights_as_stored(w_dtype, store, side_kind, 0, 0, 0, d_c, H, d_h, d_side, mode)
+
+
+@pytest.mark.parametrize("store,scale", [(wl.F16, 1e-5), (wl.F16, 1e-8), (wl.F16, 3e7), (wl.BF16, 1e-37), (wl.BF16, 1.0)])
+def test_prepare_device_ex_companion_below_and_beyond_the_stored_range(store, scale):
+    """Companions that are stored as subnormal numbers, as zeros of either sign and as infinities."""
+    d_c, H, d_h, d_side = 96, 2, 32, 70
+    W, Wq, _ = _weights(d_c, H, d_h, d_side, seed=77, weak_first=False)
+    W_s, W64 = wl.to_storage(W, wl.F32)
+    side_s, side64 = wl.to_storage(Wq * scale, wl.F32)
+    exact = _run_stored(W_s, wl.F32, d_c, H, d_h, wl.F64, side_s, oracle.SIDE_Q, oracle.EXPLICIT, d_c - d_h, False)
+    got = _run_stored(W_s, wl.F32, d_c, H, d_h, store, side_s, oracle.SIDE_Q, oracle.LAST)
+    with np.errstate(over="ignore"):
+        assert np.array_equal(got["side"], wl.to_storage(exact["side"], store)[1])
+    assert got["off"] == d_c - d_h
+
+
 @pytest.mark.parametrize("d_c,H,d_h,d_side,off", [(20, 3, 4, 70, 16), (24, 70, 8, 33, 9), (64, 40, 16, 300, 17), (90, 3, 33, 40, 57), (144, 2, 48, 65, 41),
                                                    (300, 2, 113, 31, 187), (260, 1, 128, 100, 0), (512, 2, 250, 33, 262), (512, 1, 256, 40, 255)])
 @pytest.mark.parametrize("side_kind", [oracle.SIDE_Q, oracle.SIDE_O])
