@@ -138,6 +138,7 @@ __device__ __forceinline__ int64_t slot_row(const Slot& s, int kk, int h, int n)
     return ((int64_t)h * n + (q - block * n)) * s.ld + block * n;
 }
 
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // v_mfma_f64_16x16x4: lane (c = lane % 16, g = lane / 16) holds A[c][g] and B[g][c] and receives
@@ -184,38 +185,34 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
     return m;
 }
 
-// Inverse of the basis block and C_h = W_h[Bbar,:] A^{-1}, head widths up to 32 NB (NB = 1 .. 4).  512
-// threads = 16 rows x 32 columns of threads; a thread keeps rows ty + 16 u and columns tx + 32 v of the
-// block in registers through the whole elimination.  A step moves one column and one row (2 KiB) through
-// LDS and waits twice: the owners of column k write it, every wave finds the pivot for itself, the owners
-// of the pivot row write that, every thread updates its 8 NB^2 elements.  Rows are never interchanged: a
-// row that has been a pivot is left out of the later searches, and the permutation is applied where the
-// inverse is written to LDS for the product.  The column loop is unrolled over v and the pivot row's u is
-// a uniform switch, so every register index is a constant.
-// The pivot is the largest of the column to 13 bits of its mantissa (the key carries the row number in its
-// low bits): growth is bounded as with the exact largest, up to a factor 1 + 2^-13.
-// The product runs on v_mfma_f64_16x16x4: a wave takes 16 rows of W_h[Bbar,:] straight from memory into
-// registers (they are its A operand) against the inverse in LDS, whose pitch of 16 mod 32 doubles lets the
-// two k rows that one half of a wave reads fall into different halves of the banks.
-// (256 threads: 0.21 ms against 0.17 in a search's launches.)
-// Bound: the elimination's serial chain (128 steps), then the double-precision matrix rate.  A version that
-// kept the block in LDS and rewrote all of it in every step, with the product in vector FMAs, took 0.62 ms
-// for 16 heads of 128 and 0.88 ms for 128; this one about 0.15 ms (a layer's two 25-window searches with
-// companions: 52.1 -> 27.5 ms).
-constexpr int kInvertThreads = 512, kInvertRows = kInvertThreads / 32;
+// Inverse of the basis block and C_h = W_h[Bbar,:] A^{-1}, head widths up to 32 NB (NB = 1 .. 4), 512 threads.  The block
+// lies in LDS and is inverted in place by Gauss-Jordan elimination in panels of 16 columns:
+//   * one wave takes the panel into registers, one or two rows a lane, and does its 16 steps there: pivot search, broadcast of
+//     the pivot row (scalar registers) and update without a barrier or a trip through LDS;
+//   * all waves apply the panel to the other columns on v_mfma_f64_16x16x4: with P the panel's pivot rows and G what the steps
+//     left in its columns, A[i, J] (zero for i in P) + G[i, :] A[P, J].
+// Rows are never interchanged: a row that has been a pivot is left out of the later searches, and the permutation is applied
+// when the inverse is put in order for the product.  The pivot is the largest of the column to 13 bits of its mantissa (the
+// key carries the row number in its low bits): growth is bounded as with the exact largest, up to a factor 1 + 2^-13.
+// The product runs on the matrix cores too: a wave takes 16 rows of W_h[Bbar,:] straight from memory into registers (its A
+// operand) against the inverse in LDS.  The pitch of 2 mod 32 doubles keeps a lane's row of a panel and 16 rows of an operand
+// in different banks.
+// Bound: the chain of pivots (16 heads of 128: 128 steps of some 130 instructions of one wave, 75 us; panels applied 29, product
+// 18).  One step at a time over all columns, with two barriers and a row and a column through LDS each, took 146 us for 16
+// heads of 128 and 172 for a search's launch; this 126 and 151.
+constexpr int kInvertThreads = 512, kInvertRows = kInvertThreads / 32, kInvertWaves = kInvertThreads / 64;
 template <int NB>
-constexpr int invert_lds_bytes() { return 32 * NB * (32 * NB + 16) * (int)sizeof(double); }
+constexpr int invert_lds_bytes() { return 32 * NB * (32 * NB + 2) * (int)sizeof(double); }
 
 template <int NB>
 __global__ __launch_bounds__(kInvertThreads) void invert_kernel(const PrepArgs a)
 {
-    constexpr int NP = 32 * NB, NU = NP / kInvertRows, NV = NB, LD = NP + 16;
+    constexpr int NP = 32 * NB, NU = NP / kInvertRows, NV = NB, LD = NP + 2, RT = NP / 16, RPL = (NP + 63) / 64;
+    constexpr int COLS = kInvertWaves / RT, CT_MAX = (RT + COLS - 1) / COLS;   // waves side by side on a row tile; column tiles of one
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     double* const inv = (double*)smem_raw;
-    __shared__ double s_col[2][NP];
-    __shared__ double s_row[NP];
-    __shared__ double s_red[kInvertThreads / 64];
-    __shared__ int s_piv[NP], s_pos[NP];
+    __shared__ double s_red[kInvertWaves];
+    __shared__ int s_piv[NP], s_pos[NP], s_singular;
     const int n = a.d_h, t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int h = blockIdx.x, z = blockIdx.z;
@@ -223,9 +220,8 @@ __global__ __launch_bounds__(kInvertThreads) void invert_kernel(const PrepArgs a
     if (off < 0) return;                       // no usable window was found: nothing to prepare
     const int64_t col0 = (int64_t)h * n;
     const Slot slot = slot_of(a, z);
-    const int tx = t & 31, ty = t >> 5;
+    const int tx = t & 31, ty = t >> 5, c = lane & 15, g = lane >> 4;
 
-    double m[NU][NV];
     double part = 0.0;
     with_type(a.w_type, [&](auto tag) {
         typedef decltype(tag) WT;
@@ -234,109 +230,157 @@ __global__ __launch_bounds__(kInvertThreads) void invert_kernel(const PrepArgs a
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
                 const int i = ty + kInvertRows * u, j = tx + 32 * v;
-                m[u][v] = (i < n && j < n) ? load_as_double<WT>(a.W, (int64_t)(off + i) * a.ldw + col0 + j) : 0.0;
+                const double m = (i < n && j < n) ? load_as_double<WT>(a.W, (int64_t)(off + i) * a.ldw + col0 + j) : 0.0;
+                inv[i * LD + j] = m;
+                part = fma(m, m, part);
             }
     });
-#pragma unroll
-    for (int u = 0; u < NU; ++u)
-#pragma unroll
-        for (int v = 0; v < NV; ++v) part = fma(m[u][v], m[u][v], part);
     for (int s = 32; s >= 1; s >>= 1) part += __shfl_xor(part, s, 64);
     if (lane == 0) s_red[wave] = part;
+    if (t == 0) s_singular = 0;
+    if (t < NP) s_pos[t] = -1;
     __syncthreads();
     double scale = 0.0;
-    for (int w = 0; w < kInvertThreads / 64; ++w) scale += s_red[w];
+    for (int w = 0; w < kInvertWaves; ++w) scale += s_red[w];
     const double tiny = sqrt(scale) * n * 2.220446049250313e-16;
 
-    uint64_t used_lo = 0, used_hi = 0;         // rows that have been pivots (uniform)
-    bool singular = false;
+    bool used[RPL];                            // (wave 0) whether the lane's rows have been pivots
 #pragma unroll
-    for (int kv = 0; kv < NV; ++kv) {
-        for (int kk = 0; kk < 32 && 32 * kv + kk < n; ++kk) {
-            const int k = 32 * kv + kk;
-            double* const col = s_col[k & 1];
-            if (tx == kk) {
+    for (int u = 0; u < RPL; ++u) used[u] = lane + 64 * u >= n;
+    for (int k0 = 0; k0 < n; k0 += 16) {
+        const int nb = n - k0 < 16 ? n - k0 : 16;
+        if (wave == 0) {
+            double x[RPL][16];
 #pragma unroll
-                for (int u = 0; u < NU; ++u) col[ty + kInvertRows * u] = m[u][kv];
-            }
-            __syncthreads();
-            uint32_t key = 0;
-            const uint64_t lo = __builtin_bit_cast(uint64_t, col[NP > 32 ? lane : lane & 31]);
-            const uint64_t hi = NP > 64 ? __builtin_bit_cast(uint64_t, col[NP > 96 ? lane + 64 : 64 + (lane & 31)]) : lo;
-            if (lane < n && !((used_lo >> lane) & 1)) key = ((uint32_t)(lo >> 32) & 0x7fffff80u) | (uint32_t)(127 - lane);
-            if constexpr (NP > 64) {
-                if (lane + 64 < n && !((used_hi >> lane) & 1)) {
-                    const uint32_t key2 = ((uint32_t)(hi >> 32) & 0x7fffff80u) | (uint32_t)(63 - lane);
-                    key = key2 > key ? key2 : key;
+            for (int u = 0; u < RPL; ++u) {
+                const int row = lane + 64 * u < NP ? lane + 64 * u : NP - 1;
+#pragma unroll
+                for (int j = 0; j < 16; j += 2) {
+                    const f64x2 v = *(const f64x2*)(inv + row * LD + k0 + j);
+                    x[u][j] = v[0];
+                    x[u][j + 1] = v[1];
                 }
             }
-            const int p = 127 - (int)(wave_max_u32(key) & 127u);       // uniform: the pivot row (< n: some row is unused)
-            // (the pivot itself is in a lane's registers already)
-            const uint64_t pb = p < 64 ? lo : hi;
-            const uint32_t pb_lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)pb, p & 63);
-            const uint32_t pb_hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(pb >> 32), p & 63);
-            const double pv = __builtin_bit_cast(double, (uint64_t)pb_hi << 32 | pb_lo);
-            if (!(fabs(pv) > tiny)) { singular = true; break; }
-            const int pu = p / kInvertRows, pt = p % kInvertRows;
-            if (ty == pt) {
+            bool singular = false;
+            // (Unrolled over the columns.  In a loop, with the pivot's column always the first and the others moved down a place by
+            // the update, the moves made a step longer than the fetch of the unrolled code does: 144 us against 126.)
+            static_for_blocks<16>([&](auto qc) {
+                constexpr int q = decltype(qc)::value;
+                if (q >= nb || singular) return;
+                uint32_t key = 0;
 #pragma unroll
-                for (int u = 0; u < NU; ++u)
-                    if (u == pu) {
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) s_row[tx + 32 * v] = m[u][v];
-                    }
-            }
-            if (t == 0) { s_piv[k] = p; s_pos[p] = k; }
-            if (p < 64) used_lo |= (uint64_t)1 << p; else used_hi |= (uint64_t)1 << (p - 64);
-            const double ip = 1.0 / pv;
-            double f[NU];
-#pragma unroll
-            for (int u = 0; u < NU; ++u) f[u] = col[ty + kInvertRows * u];
-            __syncthreads();
-            double r[NV];
-#pragma unroll
-            for (int v = 0; v < NV; ++v) r[v] = s_row[tx + 32 * v] * ip;
-            if (tx == kk) r[kv] = ip;          // column k of the block is replaced by the inverse's
-#pragma unroll
-            for (int u = 0; u < NU; ++u)
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    const double cur = (v == kv && tx == kk) ? 0.0 : m[u][v];
-                    m[u][v] = fma(-f[u], r[v], cur);
+                for (int u = 0; u < RPL; ++u) {
+                    const uint32_t hi = (uint32_t)(__builtin_bit_cast(uint64_t, x[u][q]) >> 32);
+                    const uint32_t k = used[u] ? 0u : (hi & 0x7fffff80u) | (uint32_t)(127 - (lane + 64 * u));
+                    key = k > key ? k : key;
                 }
-            if (ty == pt) {
+                const int p = 127 - (int)(wave_max_u32(key) & 127u);       // uniform: the pivot row (< n: some row is unused)
+                const bool upper = RPL > 1 && p >= 64;
+                const int pl = p & 63;
+                double row[16];                // the pivot row, in scalar registers (a branch for its half: selects would be 32 more)
+                auto broadcast = [&](const double (&from)[16]) {
 #pragma unroll
-                for (int u = 0; u < NU; ++u)
-                    if (u == pu) {
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) m[u][v] = r[v];
+                    for (int j = 0; j < 16; ++j) {
+                        const uint64_t b = __builtin_bit_cast(uint64_t, from[j]);
+                        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, pl);
+                        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), pl);
+                        row[j] = __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
                     }
-            }
+                };
+                if (upper) broadcast(x[RPL - 1]);
+                else broadcast(x[0]);
+                const double pv = row[q];
+                if (!(fabs(pv) > tiny)) { singular = true; return; }
+                const double ip = 1.0 / pv;
+#pragma unroll
+                for (int u = 0; u < RPL; ++u) {
+                    const double f = x[u][q] * ip;
+#pragma unroll
+                    for (int j = 0; j < 16; ++j)
+                        if (j != q) x[u][j] = fma(-f, row[j], x[u][j]);
+                    x[u][q] = -f;              // column k of the block is replaced by the inverse's
+                }
+                auto pivot_row = [&](double (&to)[16], bool& is_used) {
+                    if (lane == pl) {
+#pragma unroll
+                        for (int j = 0; j < 16; ++j) to[j] = j == q ? ip : row[j] * ip;
+                        is_used = true;
+                    }
+                };
+                if (upper) pivot_row(x[RPL - 1], used[RPL - 1]);
+                else pivot_row(x[0], used[0]);
+                if (lane == 0) { s_piv[k0 + q] = p; s_pos[p] = k0 + q; }
+            });
+            if (singular && lane == 0) s_singular = 1;
+#pragma unroll
+            for (int u = 0; u < RPL; ++u)
+                if (lane + 64 * u < NP) {
+#pragma unroll
+                    for (int j = 0; j < 16; j += 2) *(f64x2*)(inv + (lane + 64 * u) * LD + k0 + j) = (f64x2){x[u][j], x[u][j + 1]};
+                }
         }
-        if (singular) break;
+        __syncthreads();
+        if (s_singular) break;
+        const bool works = wave < RT * COLS;   // (uniform; with RT = 6 two waves are left over)
+        const int rt = wave % RT, ct0 = wave / RT;
+        double ga[4], pb[CT_MAX][4];
+        bool pivot[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const bool in = 4 * s + g < nb;
+            const int prow = in ? s_piv[k0 + 4 * s + g] : 0;
+            ga[s] = in ? inv[(16 * rt + c) * LD + k0 + 4 * s + g] : 0.0;
+#pragma unroll
+            for (int i = 0; i < CT_MAX; ++i) {
+                const int ct = ct0 + COLS * i;
+                pb[i][s] = in && ct < RT ? inv[prow * LD + 16 * ct + c] : 0.0;
+            }
+            pivot[s] = s_pos[16 * rt + 4 * s + g] >= k0;
+        }
+        __syncthreads();                       // everybody has the pivot rows as they were
+#pragma unroll
+        for (int i = 0; i < CT_MAX; ++i) {
+            const int ct = ct0 + COLS * i;
+            if (!works || ct >= RT || 16 * ct == k0) continue;
+            f64x4 acc;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] = pivot[r] ? 0.0 : inv[(16 * rt + 4 * r + g) * LD + 16 * ct + c];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) acc = mfma_f64(ga[s], pb[i][s], acc);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) inv[(16 * rt + 4 * r + g) * LD + 16 * ct + c] = acc[r];
+        }
+        __syncthreads();
     }
-    if (singular) {
+    if (s_singular) {
         if (t == 0) {
             if (a.status) atomicMax(a.status, h + 1);
             if (a.cand_singular) a.cand_singular[a.cand + z] = 1;    // (every writer stores the same value)
         }
         return;
     }
-    __syncthreads();                           // s_piv and s_pos are complete
     // storage row p_k of the result is row k of (P A)^{-1}, and A^{-1} = (P A)^{-1} P
+    {
+        double m[NU][NV];
 #pragma unroll
-    for (int u = 0; u < NU; ++u)
+        for (int u = 0; u < NU; ++u)
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            const int i = ty + kInvertRows * u, j = tx + 32 * v;
-            const bool in = i < n && j < n;
-            inv[(i < n ? s_pos[i] : i) * LD + (j < n ? s_piv[j] : j)] = in ? m[u][v] : 0.0;
-        }
+            for (int v = 0; v < NV; ++v) m[u][v] = inv[(ty + kInvertRows * u) * LD + tx + 32 * v];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const int i = ty + kInvertRows * u, j = tx + 32 * v;
+                const bool in = i < n && j < n;
+                inv[(i < n ? s_pos[i] : i) * LD + (j < n ? s_piv[j] : j)] = in ? m[u][v] : 0.0;
+            }
+    }
     __syncthreads();
 
     // gridDim.y workgroups per head each invert the block for themselves (the same operations in the same
     // order, so the same inverse bit for bit) and share out the row tiles of the product.
-    const int K = a.d_c - n, c = lane & 15, g = lane >> 4;
+    const int K = a.d_c - n;
     for (int rt = (int)blockIdx.y + (int)gridDim.y * wave; rt * 16 < K; rt += (int)gridDim.y * (kInvertThreads / 64)) {
         const int ra = rt * 16 + c;            // this lane's row of the A operand
         const int src = ra < off ? ra : ra + n;
@@ -1018,7 +1062,6 @@ __global__ __launch_bounds__(kStripThreads) void strip_kernel(const PrepArgs a)
 // the chosen window copied instead of prepared again; the matrix pipes busy 69 % of the time, 54 before).
 // ---------------------------------------------------------------------------------------------
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-typedef double f64x2 __attribute__((ext_vector_type(2)));
 constexpr uint32_t kNoOffset = 0x80000000u;   // beyond every range here
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t range_of(const void* p, int64_t bytes)
