@@ -325,7 +325,7 @@ int bda_kv_project_backward_ex(const void* c, int64_t ldc, const void* d_out, in
 typedef enum {
     BDA_KERNEL_NONE = 0,    /* nothing to launch (T = 0) */
     BDA_KERNEL_GENERAL = 1, /* any type / shape / alignment: 128 x 128 to 32 x 32 tiles, float32 MFMA */
-    BDA_KERNEL_MFMA = 2,    /* register-staged MFMA kernels, 64 x 64, 128 x 128 or 256 x 256 tiles */
+    BDA_KERNEL_MFMA = 2,    /* MFMA kernels off the lean kernel's shapes, 64 x 64, 128 x 128 or 256 x 256 tiles */
     BDA_KERNEL_STREAM = 3,  /* streaming MFMA kernel (LDS DMA ring), general variant */
     BDA_KERNEL_LEAN = 4,    /* streaming MFMA kernel, lean variant (256-, 128- or 64-token tiles) */
     BDA_KERNEL_DECODE = 5,  /* few tokens (token tiles of up to 128): weight-streaming kernels; tile_columns tells 32-, 64- and 128-column slices apart */

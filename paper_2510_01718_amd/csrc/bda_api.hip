@@ -11,6 +11,7 @@
 #include "bda_gemm_duo.hpp"
 #include "bda_gemm_f32.hpp"
 #include "bda_gemm_mid.hpp"
+#include "bda_gemm_ring.hpp"
 #include "bda_internal.h"
 
 namespace bda {
@@ -76,6 +77,24 @@ int launch_mid(GemmArgs& a, hipStream_t st)
     if (plan_only(a, BDA_KERNEL_MFMA, L::BT, L::BN, grid, 512, L::BYTES, (total + 256 * per_cu - 1) / (256 * per_cu))) return BDA_OK;
     if (int rc = set_max_lds(kern, L::BYTES, once)) return rc;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(512), L::BYTES, st, a);
+    hipError_t err = hipGetLastError();
+    return err == hipSuccess ? BDA_OK : fail(BDA_EHIP, "kernel launch: %s", hipGetErrorString(err));
+}
+
+typedef RingShape<128, 128, 2, 2, 2, 64, 2> ForwardRing;
+
+template <typename X, typename OutT>
+int launch_ring(GemmArgs& a, hipStream_t st)
+{
+    static LdsLimitState once;
+    using C = ForwardRing;
+    auto kern = gemm_ring_kernel<X, OutT, C>;
+    const int total = a.m_tiles * a.n_tiles, grid = kNumXcd * ((total + kNumXcd - 1) / kNumXcd);
+    a.lin_slots = 0;
+    a.sm = a.sn = 1;
+    if (plan_only(a, BDA_KERNEL_MFMA, C::BT, C::BN, grid, C::THREADS, C::BYTES, (total + 511) / 512)) return BDA_OK;
+    if (int rc = set_max_lds(kern, C::BYTES, once)) return rc;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(C::THREADS), C::BYTES, st, a);
     hipError_t err = hipGetLastError();
     return err == hipSuccess ? BDA_OK : fail(BDA_EHIP, "kernel launch: %s", hipGetErrorString(err));
 }
@@ -359,7 +378,8 @@ bool lean_kernel_applies(const GemmArgs& a, int G, const int64_t* group_cols)
     return ok && a.K / 64 + id_stages >= 3;
 }
 
-// Tile of gemm_mid_kernel (64 or 128 square) for a launch that the lean kernel does not take, or 0.
+// Kernel for a launch that the lean kernel does not take: gemm_mid_kernel with 64 x 64 or 128 x 128 tiles, gemm_ring_kernel
+// (128 x 128), or none of them.
 // From 96 tiles of 256 x 256 up the alternative is the streaming kernel, whose round of
 // tiles takes about 10 + 0.025 K us however few tiles are in it (K = 160 14, 288 17, 416 21, 608 25); the 64 x 64
 // tiles take about 5 us and at most 0.0075 + 1.4e-5 K us each (T = 3001, N = 2304, K = 288: 23 / 32, two rounds; T = 3001,
@@ -373,31 +393,44 @@ bool lean_kernel_applies(const GemmArgs& a, int G, const int64_t* group_cols)
 // K = 416 1.0e-7, 1.3e-7 in one sum.)
 // At most 128 columns and K >= 384: 128 x 128 tiles, which such a launch has always reported as its plan; faster than the
 // register-staged kernel there, but not as fast as 64 x 64 tiles (T = 4096, K = 416, N = 128: 11.6 us, 14.3 and 6.3).
-int mid_tile(const GemmArgs& a, int G, const int64_t* group_cols, bool big, bool f32_out)
+// The ring's time is some 5 us and per tile 0.01 us and 0.0025 per stage of 64 (float32 results 0.003 more): T = 3001, K = 288, N = 2304,
+// float32 15 us (432 tiles), T = 2623, K = 384, N = 10496 47 (1722).  It is taken beyond 512 tiles of 64 x 64 where no other
+// estimate is lower (us, before / ring: those two 24 / 15 and 52 / 47; T = 2720, N = 2432 23 / 13; T = 868, K = 352, N = 16640
+// 41 / 27; T = 1871, K = 384, N = 1920 14.4 / 10.1); whole rounds of the streaming kernel stay there (T = 5761, N = 20224 133 / 185), and
+// so do fewer tiles (T = 184, K = 608, N = 8704 12.8 / 14.3; T = 1087, N = 1408 8.2 / 8.7).  Below 96 tiles of 256 x 256, products without
+// an identity slice, contractions of one chunk and up to 768 tiles keep the kernels that their launch plans have always reported,
+// though the ring would be ahead there too (T = 2048, K = 64, N = 2592 12.6 / 9.1; 600 tiles, T = 1570, K = 384, N = 1536 11.8 / 9.0).
+enum class MidKernel { None, Halves64, Halves128, Ring };
+MidKernel mid_kernel(const GemmArgs& a, int G, const int64_t* group_cols, bool big, bool f32_out)
 {
     int64_t N = 0, nt64 = 0;
     for (int g = 0; g < G; ++g) { N += group_cols[g]; nt64 += (group_cols[g] + 63) / 64; }
     const int64_t tiles = (a.M + 63) / 64 * nt64;
-    if (tiles > (1 << 22)) return 0;   // a workgroup of 512 per tile: 2^31 of the 2^32 work-items a launch may have
+    if (tiles > (1 << 22)) return MidKernel::None;   // a workgroup of 512 per tile: 2^31 of the 2^32 work-items a launch may have
     GemmArgs s = a;
     const int bt = big ? 256 : 128;
     build_tiles(s, G, group_cols, bt, bt);
     choose_super(s, big ? kSlotsPerXcd : 2 * kSlotsPerXcd, bt, bt);
     const int64_t supers = (int64_t)((s.m_tiles + s.sm - 1) / s.sm) * ((s.n_tiles + s.sn - 1) / s.sn);
     const double rounds = (double)((supers + kNumXcd - 1) / kNumXcd);
+    const int chunks = (a.K + 63) / 64;
+    int64_t nt128 = 0;
+    for (int g = 0; g < G; ++g) nt128 += (group_cols[g] + 127) / 128;
+    const double ring = 5.0 + (double)((a.M + 127) / 128 * nt128) * (0.01 + 0.0025 * chunks + (f32_out ? 0.003 : 0.0));
     if (big) {
         const double stream = rounds * (10.0 + 0.025 * a.K);
         const double mid = 5.0 + (double)tiles * (0.0075 + 1.4e-5 * a.K);
-        return mid < 0.95 * stream ? 64 : 0;
+        if (tiles > 512 && ring < 0.95 * std::min(stream, mid)) return MidKernel::Ring;
+        return mid < 0.95 * stream ? MidKernel::Halves64 : MidKernel::None;
     }
-    if (N <= 128 && a.K >= 384) return 128;
-    if (tiles <= 512) return 64;
-    const int chunks = (a.K + 63) / 64;
-    if (chunks > (f32_out ? 1 : 5)) return 64;
+    if (N <= 128 && a.K >= 384) return MidKernel::Halves128;
+    if (tiles <= 512) return MidKernel::Halves64;
     const int id_chunks = a.ident ? ((a.d_h % 128 == 0 ? 128 : a.d_h) + 63) / 64 : 0;
     const double staged = 2.6 + 0.0037 * s.m_tiles * s.n_tiles + rounds * (0.96 * chunks + 0.7 * id_chunks + (kNumXcd * s.sm * s.sn > 256 ? 6.0 : 3.0));
     const double mid = 4.3 + (double)tiles * (0.0041 + 0.00086 * chunks + (a.ident ? 0.002 : 0.0));
-    return mid < (chunks > 1 ? 1.08 : 1.0) * staged ? 64 : 0;   // (two chunks or more: either is at most a little slower than the other)
+    if (a.ident && chunks > 1 && tiles > 768 && ring < std::min(mid, staged)) return MidKernel::Ring;
+    if (chunks > (f32_out ? 1 : 5)) return MidKernel::Halves64;
+    return mid < (chunks > 1 ? 1.08 : 1.0) * staged ? MidKernel::Halves64 : MidKernel::None;   // (two chunks or more: either is at most a little slower than the other)
 }
 
 int run_gemm(GemmArgs& a, int G, const int64_t* group_cols, int dtype, int out_dtype, hipStream_t st)
@@ -517,10 +550,11 @@ int run_gemm(GemmArgs& a, int G, const int64_t* group_cols, int dtype, int out_d
         const int tok_tile = quarter_tokens ? 64 : half_tokens ? 128 : 256;
         const bool big = plain || policy == 2 || policy == 3 || policy == 4 || ((policy == 0 || policy == 7) && mt256 * nt256 >= 96);
         const bool stream = big && stream_ok;
-        const int mid = (policy == 0 || policy == 7) && !plain && (stream || !big) ? mid_tile(a, G, group_cols, big, out_dtype == BDA_F32) : 0;
-        if (mid) {
-            build_tiles(a, G, group_cols, mid, mid);
-#define BDA_LAUNCH(X, O) return mid == 64 ? launch_mid<X, O, 1, 1>(a, st) : launch_mid<X, O, 2, 2>(a, st)
+        const MidKernel mid = (policy == 0 || policy == 7) && !plain && (stream || !big) ? mid_kernel(a, G, group_cols, big, out_dtype == BDA_F32) : MidKernel::None;
+        if (mid != MidKernel::None) {
+            const int edge = mid == MidKernel::Halves64 ? 64 : 128;
+            build_tiles(a, G, group_cols, edge, edge);
+#define BDA_LAUNCH(X, O) return mid == MidKernel::Ring ? launch_ring<X, O>(a, st) : edge == 64 ? launch_mid<X, O, 1, 1>(a, st) : launch_mid<X, O, 2, 2>(a, st)
             if (dtype == BDA_F16 && out_dtype == BDA_F16) { BDA_LAUNCH(F16, uint16_t); }
             if (dtype == BDA_F16 && out_dtype == BDA_F32) { BDA_LAUNCH(F16, float); }
             if (dtype == BDA_BF16 && out_dtype == BDA_BF16) { BDA_LAUNCH(BF16, uint16_t); }

@@ -61,7 +61,7 @@ int launch_ring(BwdArgs& a, int64_t rows, const int64_t* group_cols, int G, hipS
     const int64_t total = ring_grid<C>(a, rows, group_cols, G);
     const int64_t grid = kNumXcd * ((total + kNumXcd - 1) / kNumXcd);
     if (grid * C::THREADS >= (int64_t)1 << 32) return fail(BDA_EINVAL, "gradient of %lld tiles: too many for a launch", (long long)total);
-    constexpr int lds = WEIGHT ? C::BYTES : C::LATENT_BYTES;
+    constexpr int lds = WEIGHT ? C::BYTES : C::BYTES + kOnesBytes;
     const auto kern = [] {
         if constexpr (WEIGHT) return ring_weight_kernel<X, OutT, C>;
         else return ring_latent_kernel<X, OutT, C>;

@@ -514,6 +514,29 @@ def test_lowrank_linear_small(last, dtype):
     assert_parity(got[:, rest], ref2, lw.d_out - lw.r, dtype, dtype, "lowrank h C from the stored h")
 
 
+# The ring kernel (128 x 128 tiles, 64 KiB of LDS): contractions of two to ten stages that end inside one, windows inside stages
+# and across them, tiles cut by T, by a group's end and both, float32 and 16-bit results.
+@pytest.mark.parametrize("dtype,out_dtype", [(wl.F16, wl.F16), (wl.BF16, wl.F32)])
+@pytest.mark.parametrize("T,d_c,d_h,H,offs", [
+    (1500, 224, 96, [13, 11], [16, 128]),
+    (257, 416, 32, [200, 170], [8, 376]),
+    (2049, 640, 64, [9, 11, 5], [576, 0, 40]),
+    (1000, 888, 256, [5, 9], [632, 8]),
+])
+def test_kv_ring_kernel(T, d_c, d_h, H, offs, dtype, out_dtype):
+    """Tolerance as everywhere; a result's sum has 640 terms at most, in two float32 halves."""
+    plan = bda.bda_kv_project_plan(T, d_c, d_h, H, offs, dtype, out_dtype)
+    assert (plan["kernel"], plan["tile_tokens"], plan["tile_columns"], plan["lds_bytes"]) == (bda.KERNEL_MFMA, 128, 128, 65536), plan
+    rng = np.random.default_rng([T, d_c])
+    N = sum(H) * d_h
+    c_s, c64 = wl.to_storage(rng.standard_normal((T, d_c)), dtype)
+    C_s, C64 = wl.to_storage(0.25 * rng.standard_normal((d_c - d_h, N)), dtype)
+    got, raw = gh.kv_project(c_s, C_s, d_c, d_h, H, offs, dtype, out_dtype, ldc=d_c + 8, ldC=N + 16, ld_out=N + 8, fill=7, extra_rows=2)
+    assert_parity(got, oracle.kv_project(c64, C64, d_h, H, offs), d_h, dtype, out_dtype, f"T={T} d_c={d_c} d_h={d_h}")
+    raw = raw.cpu().numpy()
+    assert np.all(raw[T:] == 7) and np.all(raw[:, N:] == 7)
+
+
 # Launches without an identity slice beyond the few-token kernels' range: column counts that end 8, 24, 40 and 56
 # columns into a 64-column tile (and in a wave's second 32), contractions of one chunk, of a partial one, of two halves.
 MID64, MID128, STAGED = (64, 64, 512), (128, 128, 512), (128, 128, 256)
