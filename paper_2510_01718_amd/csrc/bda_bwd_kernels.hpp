@@ -115,6 +115,7 @@ __global__ __launch_bounds__(C::THREADS) void ring_latent_kernel(const BwdArgs p
         ld_rem -= CK;
         ld_soff += 2u * CK;
         if (ld_rem < CK) {
+            if (ld_rem <= 0 && ld_g + 1 >= n_groups) ld_soff = 0;    // (past the last group nothing is read: the range check sees no offset beyond the range)
             if (ld_rem <= 0 && ld_g + 1 < n_groups) {
                 ld_g = uniform(ld_g + 1);
                 // (waited for in here, not by every stage where the paths meet)
