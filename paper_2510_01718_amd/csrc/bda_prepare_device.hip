@@ -3,22 +3,26 @@
 // Search" for the candidate windows).  Float64 throughout:
 //   invert_kernel    C_h = W_h[Bbar,:] W_h[B,:]^{-1} for d_h <= 128, one workgroup per head (several when
 //                    there are few heads: each inverts for itself and takes a share of the rows): the
-//                    basis block is inverted in registers by Gauss-Jordan elimination with partial (row)
-//                    pivoting, then the d_c - d_h rows outside the window are multiplied by the inverse on
-//                    the matrix cores and stored rounded to the requested type;
+//                    basis block is inverted in LDS by Gauss-Jordan elimination with partial (row) pivoting
+//                    in panels of 16 columns, then the d_c - d_h rows outside the window are multiplied by
+//                    the inverse on the matrix cores and stored rounded to the requested type;
 //   prepare_wide_kernel   the same for d_h up to 256 with the block in the caller's workspace (the row
 //                    interchanges are undone as column interchanges at the end);
 //   strip_kernel     with a companion and d_c up to 512: the companion block, W_q^h W_h[B,:]^T or W_h[B,:] W_o^h,
 //                    rounded the same way, and the Frobenius reconstruction errors of the stored form of one
 //                    head for all candidate windows of the launch, as partial sums of squares (a fixed number
 //                    of parts per head, each summed in a fixed order);
+//   measure_kernel   the same for the shapes nearly every projection has (whole tiles, windows that start on
+//                    multiples of 16, aligned rows, 16-bit results), without per-lane decisions;
 //   side_kernel, residual_kernel   the same in two steps, one window per launch: wider latents, and errors
 //                    without a companion;
 //   select_kernel    per candidate window the mean over heads of the residuals, the smallest mean
 //                    (earlier candidate on ties, NaN as +inf), the chosen window start.
+//   copy_kernel      the chosen window's stored C from where the search kept it to C.
 // A search prepares and measures its candidate windows, as many per launch as the caller's outputs can hold
-// stored C's (see Slot), selects, and prepares the chosen window once more, whose start it reads from device
-// memory: nothing comes back to the host in between.
+// stored C's (see Slot), selects, and either copies the chosen window's C, where the companion output could hold
+// every candidate, or prepares that window once more, whose start it reads from device memory: nothing comes
+// back to the host in between.
 // The host routine bda_prepare solves with an orthogonal factorisation instead of forming the inverse;
 // the two agree to a small multiple of cond(W_h[B,:]) * 2^-53.
 #include <hip/hip_runtime.h>
