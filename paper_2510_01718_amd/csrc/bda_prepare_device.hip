@@ -1063,7 +1063,8 @@ __global__ __launch_bounds__(kStripThreads) void strip_kernel(const PrepArgs a)
 // of the MFMA's 64), so conversions come together, addresses are scalar and a lane's squares stay in LDS till the end.
 // Same sums as strip_kernel, in the same order but for a lane's squares over the strips.
 // Against strip_kernel: 25 windows of 16 heads for keys and values 7.05 -> 6.0 ms, two windows of 128 heads 2.15 -> 1.87 (with
-// the chosen window copied instead of prepared again; the matrix pipes busy 69 % of the time, 54 before).
+// the chosen window copied instead of prepared again; the matrix pipes busy 69 % of the time, 54 before); with the inversion
+// in panels 5.77 and 1.85.
 // ---------------------------------------------------------------------------------------------
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 constexpr uint32_t kNoOffset = 0x80000000u;   // beyond every range here
