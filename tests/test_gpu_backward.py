@@ -240,6 +240,24 @@ def test_backward_every_tile_edges(T, d_c, d_h, H, offs, dtype, grad_dtype, poli
     _check(T, d_c, d_h, H, offs, dtype, grad_dtype=grad_dtype, pad=8, policy=policy, seed=17)
 
 
+@pytest.mark.parametrize("dtype", [wl.F16, wl.BF16])
+@pytest.mark.parametrize("policy", [1, 2, 3, 4])
+def test_backward_weight_gradient_sums_are_in_two_parts_at_least(dtype, policy):
+    """Error of float32 weight gradients against 64 bits, for every tile.
+
+    A float32 sum of T independent products of unit size that is rounded after every n of them has a size of sqrt(n j) after
+    j roundings, so its error is d sqrt(T / 2n) of the result's sqrt(T); in two sums of T / 2 it is d sqrt(T / 4n).  d, the root
+    mean square of one rounding's relative error, is 2^-24 / sqrt(3) times the mean of 1 / m over mantissas m in [1, 2),
+    about 0.7: 2.4e-8.  With the two roundings of 8 products each that the errors of this card's MFMAs show, T = 8192 gives
+    3.8e-7 in two sums and 5.4e-7 in one (measured 4.0e-7 and 5.7e-7); the bound lies between."""
+    T, d_c, d_h, H, offs = 8192, 320, 128, [2], [64]
+    (c_s, c64), (g_s, g64), (C_s, C64) = _inputs(23, T, d_c, d_h, H, dtype)
+    _, ref = oracle.kv_project_backward(c64, g64, C64, d_h, H, offs)
+    _, got, _, _ = _backward(c_s, g_s, C_s, T, d_c, d_h, H, offs, dtype, wl.F32, want=(False, True), policy=policy)
+    error = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    assert error <= 4.7e-7, error
+
+
 def test_backward_gradients_aligned_to_eight_bytes():
     """16-bit gradients may start on any multiple of 8 bytes: a column view of a wider buffer."""
     T, d_c, d_h, H, offs, dtype = 200, 256, 64, [2, 3], [0, 128], wl.F16
