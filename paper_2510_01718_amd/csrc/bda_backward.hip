@@ -1,6 +1,8 @@
 // Device entry point for the gradients of the BD K/V projection: validation, tile grids, launches.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "bda_bwd_kernels.hpp"
 #include "bda_gemm_f32.hpp"
 #include "bda_internal.h"
@@ -33,6 +35,7 @@ int launched()
 typedef RingShape<128, 128, 1, 2, 4, 64, 4> LatentLarge;
 typedef RingShape<64, 128, 1, 2, 4, 64, 4> LatentMiddle;
 typedef RingShape<64, 64, 1, 1, 8, 128, 4> LatentSmall;
+typedef RingShape<64, 64, 1, 1, 4, 64, 3> LatentShort;
 typedef RingShape<192, 256, 2, 4, 1, 32, 5> WeightLarge;
 typedef RingShape<128, 256, 2, 4, 1, 32, 6> WeightMiddle;
 typedef RingShape<64, 128, 1, 2, 4, 64, 4> WeightSmall;
@@ -61,6 +64,10 @@ int launch_ring(BwdArgs& a, int64_t rows, const int64_t* group_cols, int G, hipS
     const int64_t total = ring_grid<C>(a, rows, group_cols, G);
     const int64_t grid = kNumXcd * ((total + kNumXcd - 1) / kNumXcd);
     if (grid * C::THREADS >= (int64_t)1 << 32) return fail(BDA_EINVAL, "gradient of %lld tiles: too many for a launch", (long long)total);
+    if constexpr (!WEIGHT) {
+        a.n_stages = 0;
+        for (int g = 0; g < a.n_groups; ++g) a.n_stages += (int)((a.col_start[g + 1] - a.col_start[g] + C::CK - 1) / C::CK);
+    }
     constexpr int lds = WEIGHT ? C::BYTES : C::BYTES + kOnesBytes;
     const auto kern = [] {
         if constexpr (WEIGHT) return ring_weight_kernel<X, OutT, C>;
@@ -71,12 +78,17 @@ int launch_ring(BwdArgs& a, int64_t rows, const int64_t* group_cols, int G, hipS
     return launched();
 }
 
-// The tile whose rounds over the 256 compute units (a workgroup each; two of the weight gradient's smallest) are estimated
-// to take the least.  The factors are times measured over the tiles, per 64 elements of the contraction and, for the weight
-// gradient, in us; over 60 drawn launches the rule's tile is within 7 % of the fastest one.  A wrong tile: 4096 tokens,
+// The tile whose rounds over the 256 compute units (a workgroup each; two of the weight gradient's smallest, three of the
+// latent gradient's shortest) are estimated to take the least.  The estimates are us measured over the tiles: per 64 elements of the
+// contraction, and what a round takes beside them (first requests, sum over the waves, stores; less where it is the only one).
+// Over 60 drawn launches the weight's rule is within 7 % of the fastest tile.  A wrong tile: 4096 tokens,
 // d_c = 512, N = 4096 latent 33 / 26 / 34 us with the large, middle, small one; 1024 tokens 31 / 22 / 17; 8192 tokens,
 // N = 32768 276 / 387 / 441; weight, 4096 tokens, K = 384, N = 4096 65 / 43 / 24 / 28 with the four, 301 tokens, N = 7424
 // 11 / 8.9 / 12.7 / 11.4, 5861 tokens, N = 2560 89 / 58 / 33 / 28.
+// Few output columns: 18 tokens, N = 64 6.9 / 5.4 / 5.6 / 5.1 with the four latent tiles, 912 tokens, N = 160 8.2 / 6.4 / 6.3 / 5.8, 20000
+// tokens, d_c = 160, N = 512 20.3 / 20.6 / 24.5 / 14.4; from N of about 600 on the eight waves are ahead (9 tokens, N = 2048 12.7 against 14.9).
+// Register-staged 64 x 64 tiles, which served N up to 512 before, took 5.3, 5.9 and 25.7 there; between N = 256 and 512 they
+// were up to 1 us ahead (1199 tokens, N = 512 6.9 against 7.2; 2 tokens, d_c = 600 6.9 and 7.8).
 template <typename X, typename OutT, bool WEIGHT>
 int launch_sized(BwdArgs& a, int64_t rows, const int64_t* group_cols, int G, hipStream_t st)
 {
@@ -101,18 +113,24 @@ int launch_sized(BwdArgs& a, int64_t rows, const int64_t* group_cols, int G, hip
         default: return launch_ring<X, OutT, WeightSmallest, true>(a, rows, group_cols, G, st);
         }
     } else {
-        if (pick < 0 || pick > 2) {
-            const double cost[3] = {rounds(ring_grid<LatentLarge>(a, rows, group_cols, G), 256) * 1.35,
-                                    rounds(ring_grid<LatentMiddle>(a, rows, group_cols, G), 256),
-                                    rounds(ring_grid<LatentSmall>(a, rows, group_cols, G), 256) * 0.76};
+        if (pick < 0 || pick > 3) {
+            double stages = 0.0;               // of 64 columns
+            for (int g = 0; g < a.n_groups; ++g) stages += (double)((a.col_start[g + 1] - a.col_start[g] + 63) / 64);
+            auto cost = [&](double r, double one, double each, double stage) { return r == 1.0 ? one + stage * stages : r * (each + stage * stages); };
+            const double n_short = (double)ring_grid<LatentShort>(a, rows, group_cols, G) / 256.0, one_short = 1.0 + 0.28 * stages;
+            const double tile_cost[4] = {cost(rounds(ring_grid<LatentLarge>(a, rows, group_cols, G), 256), 3.1, 4.5, 0.42),
+                                         cost(rounds(ring_grid<LatentMiddle>(a, rows, group_cols, G), 256), 1.4, 3.2, 0.31),
+                                         cost(rounds(ring_grid<LatentSmall>(a, rows, group_cols, G), 256), 1.8, 3.4, 0.21),
+                                         n_short <= 1.0 ? one_short : std::max(one_short, n_short * (1.2 + 0.2 * stages))};
             pick = 0;
-            for (int i = 1; i < 3; ++i)
-                if (cost[i] < cost[pick]) pick = i;
+            for (int i = 1; i < 4; ++i)
+                if (tile_cost[i] < tile_cost[pick]) pick = i;
         }
         switch (pick) {
         case 0: return launch_ring<X, OutT, LatentLarge, false>(a, rows, group_cols, G, st);
         case 1: return launch_ring<X, OutT, LatentMiddle, false>(a, rows, group_cols, G, st);
-        default: return launch_ring<X, OutT, LatentSmall, false>(a, rows, group_cols, G, st);
+        case 2: return launch_ring<X, OutT, LatentSmall, false>(a, rows, group_cols, G, st);
+        default: return launch_ring<X, OutT, LatentShort, false>(a, rows, group_cols, G, st);
         }
     }
 }

@@ -39,6 +39,7 @@ struct BwdArgs {
     int d_c, d_h, K;                     // K = d_c - d_h
     int n_groups;
     int m_tiles, n_tiles;                // tile grid: rows x columns of the output
+    int n_stages;                        // latent gradient: stages of all groups (none straddles two)
     int tile_start[kMaxGroups + 1];      // weight gradient: first column tile of each group
     int64_t col_start[kMaxGroups + 1];   // first output column of each group
     int a_off[kMaxGroups];               // basis window start of each group
@@ -51,7 +52,7 @@ template <typename X, typename OutT, typename C, typename Acc>
 __device__ __forceinline__ void ring_finish(unsigned char* smem, Acc& acc, __amdgpu_buffer_rsrc_t rD, int64_t ldo, int cols_left,
                                             int wave, int wt, int wn, int kg, int lane)
 {
-    wait_vmcnt<0>();                           // requests past the last stage still write zeros to the ring
+    wait_vmcnt<0>();                           // (requests past the last stage, of loops that are not unrolled, still write zeros to the ring)
     __syncthreads();
     ring_reduce<C>(smem, acc, kg, wt * C::WN + wn, lane);
     if (C::WK > 1 && kg >= 2) return;
@@ -98,8 +99,6 @@ __global__ __launch_bounds__(C::THREADS) void ring_latent_kernel(const BwdArgs p
     const u32x4 rC = make_rsrc_words(p.C, ((int64_t)(p.K - 1) * p.ldC + N) * 2);
     const uint32_t g_pitch = (uint32_t)(p.ldg * 2), c_pitch = (uint32_t)(p.ldC * 2);
     const int d_h = p.d_h, d_c = p.d_c, n_groups = p.n_groups;
-    int n_stages = 0;                          // stages never straddle groups
-    for (int g = 0; g < n_groups; ++g) n_stages += (int)((p.col_start[g + 1] - p.col_start[g] + CK - 1) / CK);
 
     // ---- requests: a wave's are 8 rows each of one block; a row's 16-byte piece p is stored at position p ^ tok_swz(row) ----
     const int lrow = lane >> 3, lpos = lane & 7;
@@ -115,8 +114,7 @@ __global__ __launch_bounds__(C::THREADS) void ring_latent_kernel(const BwdArgs p
         ld_rem -= CK;
         ld_soff += 2u * CK;
         if (ld_rem < CK) {
-            if (ld_rem <= 0 && ld_g + 1 >= n_groups) ld_soff = 0;    // (past the last group nothing is read: the range check sees no offset beyond the range)
-            if (ld_rem <= 0 && ld_g + 1 < n_groups) {
+            if (ld_rem <= 0) {                 // (nothing is requested past the last group)
                 ld_g = uniform(ld_g + 1);
                 // (waited for in here, not by every stage where the paths meet)
                 const int start = uniform((int)p.col_start[ld_g]), end = uniform((int)p.col_start[ld_g + 1]), off = uniform(p.a_off[ld_g]);
@@ -129,7 +127,7 @@ __global__ __launch_bounds__(C::THREADS) void ring_latent_kernel(const BwdArgs p
                     vw[j] = ok ? (uint32_t)(l < off ? l : l - d_h) * c_pitch + (uint32_t)(blk_n * 128 + piece(row) * 16) : kBadOffset;
                 }
             }
-            // (columns past the group's end, and everything past the last group, read as zero)
+            // (columns past the group's end read as zero)
 #pragma unroll
             for (int j = 0; j < PT; ++j) xt[j] = blk_t * 64 + piece(row_t + 8 * j) * 8 < ld_rem ? vt[j] : kBadOffset;
 #pragma unroll
@@ -229,7 +227,7 @@ __global__ __launch_bounds__(C::THREADS) void ring_latent_kernel(const BwdArgs p
             });
         });
     };
-    ring_loop<C>(n_stages, prepare, request, read, next, multiply);
+    ring_loop<C>(p.n_stages, prepare, request, read, next, multiply);
     const __amdgpu_buffer_rsrc_t rD = make_rsrc((char*)p.out + (t0 * p.ldo + l0) * (int64_t)sizeof(OutT),
                                                 ((rows_left - 1) * p.ldo + cols_left) * (int64_t)sizeof(OutT));
     ring_finish<X, OutT, C>(smem, acc, rD, p.ldo, cols_left, wave, wt, wn, kg, lane);

@@ -151,6 +151,15 @@ __device__ __forceinline__ void ring_store(unsigned char* stag, const f32x16& a0
     }
 }
 
+// Waits until at most the requests of the last `stages` stages are in flight; more than MAX of them cannot be.
+template <int P, int MAX>
+__device__ __forceinline__ void wait_stages(int stages)
+{
+    if constexpr (MAX <= 0) wait_vmcnt<0>();
+    else if (stages >= MAX) wait_vmcnt<P * MAX>();
+    else wait_stages<P, MAX - 1>(stages);
+}
+
 // The main loop.  Stage k lies in slot k % S; all of the ring is requested before the first stage.  One k-step of fragments
 // is read ahead of the MFMAs, across the stages' boundary: a wave passes the barrier that ends stage k with its last
 // k-step in registers, reads the first of stage k + 1 and puts its requests for stage k + S, which takes the slot just
@@ -160,6 +169,10 @@ __device__ __forceinline__ void ring_store(unsigned char* stag, const f32x16& a0
 // the same time, right behind the barrier, with nothing to multiply.  Stages of one k-step are unrolled over the slots, which makes
 // LDS addresses constants (latent gradient, 1024 tokens, N = 32768 104 -> 86 us); longer ones are not: with several ways out of the
 // loop the compiler moves the accumulators about, which those tiles have no registers for.
+// Unrolled, the last stages are a loop of their own that requests nothing past the end.  Such requests (zeros, which the
+// kernel waits for before its LDS takes the sums) cost S stages of LDS writes, 0.4 us of a launch of 6; with the question in
+// every stage a long loop took 12 % more.  (After the last stage a slot that was never filled may be read; nothing is
+// multiplied with it.)
 //   prepare()  sets up the requests of the next stage to be asked for      request(j, slot)  issues the j-th of them
 //   read(set, s, slot)  fetches k-step s of the stage being read           next()  goes on to the next stage to be read
 //   multiply(set, f)  the k-step's MFMAs, with f(i) after the i-th         (slot: its first byte)
@@ -167,16 +180,20 @@ template <typename C, typename Prepare, typename Request, typename Read, typenam
 __device__ __forceinline__ void ring_loop(int n_stages, Prepare&& prepare, Request&& request, Read&& read, Next&& next, Multiply&& multiply)
 {
     constexpr int P = C::PT + C::PN, M = C::TT * C::TN, PER = (P + M - 1) / M, S = C::S, KSW = C::KSW;
+    constexpr bool UNROLLED = KSW == 1;
     const std::integral_constant<int, 0> zero;
+    if (n_stages <= 0) return;
 #pragma unroll 1
-    for (uint32_t slot = 0; slot < (uint32_t)C::BYTES; slot += (uint32_t)C::STAGE) {
+    for (int k = 0; k < S && (!UNROLLED || k < n_stages); ++k) {
         prepare();
-        static_for<P>([&](auto j) { request(j, slot); });
+        static_for<P>([&](auto j) { request(j, (uint32_t)k * (uint32_t)C::STAGE); });
     }
-    wait_vmcnt<P * (S - 1)>();
+    wait_stages<P, S - 1>(UNROLLED ? n_stages - 1 : S - 1);
     __syncthreads();
     read(zero, zero, 0u);
-    auto stage = [&](auto first, uint32_t slot, uint32_t next_slot) {   // first: the set that holds the stage's first k-step
+    // first: the set that holds the stage's first k-step; last: whether the end may be within S stages; left: stages to go, if so
+    auto stage = [&](auto first, uint32_t slot, uint32_t next_slot, auto last, int left) {
+        constexpr bool LAST = decltype(last)::value;
         static_for<KSW>([&](auto sc) {
             constexpr int s = decltype(sc)::value, Q = (decltype(first)::value + s) % 2;
             const std::integral_constant<int, Q> now;
@@ -186,34 +203,41 @@ __device__ __forceinline__ void ring_loop(int n_stages, Prepare&& prepare, Reque
                 __builtin_amdgcn_sched_barrier(0);
                 multiply(now, [](auto) {});
             } else {
-                wait_vmcnt<P * (S - 2)>();
+                const bool more = !LAST || left > S;
+                wait_stages<P, S - 2>(LAST ? left - 2 : S - 2);
                 __syncthreads();
                 next();
                 read(other, zero, next_slot);
-                prepare();
+                if (more) prepare();
                 __builtin_amdgcn_sched_barrier(0);
                 multiply(now, [&](auto i) {
                     constexpr int I = decltype(i)::value;
                     __builtin_amdgcn_sched_barrier(0);
-                    static_for<PER>([&](auto jj) {
-                        constexpr int j = I * PER + decltype(jj)::value;
-                        if constexpr (j < P) request(std::integral_constant<int, j>{}, slot);
-                    });
+                    if (I * PER < P && more)
+                        static_for<PER>([&](auto jj) {
+                            constexpr int j = I * PER + decltype(jj)::value;
+                            if constexpr (j < P) request(std::integral_constant<int, j>{}, slot);
+                        });
                     __builtin_amdgcn_sched_barrier(0);
                 });
             }
             __builtin_amdgcn_sched_barrier(0);
         });
     };
-    if (n_stages <= 0) return;
-    if constexpr (KSW == 1) {
+    if constexpr (UNROLLED) {
         constexpr int U = S % 2 == 1 ? 2 * S : S;                    // stages until slot and set repeat
         static_assert(U <= 6);
-        for (int left = n_stages;;) {
-#define BDA_RING_STAGE(I)                                                                                              \
-    if constexpr (I < U) {                                                                                             \
-        stage(std::integral_constant<int, I % 2>{}, (uint32_t)(I % S * C::STAGE), (uint32_t)((I + 1) % S * C::STAGE)); \
-        if (--left == 0) break;                                                                                        \
+        auto turn = [&](auto ic, auto last, int left) {
+            constexpr int I = decltype(ic)::value;
+            stage(std::integral_constant<int, I % 2>{}, (uint32_t)(I % S * C::STAGE), (uint32_t)((I + 1) % S * C::STAGE), last, left);
+        };
+        int left = n_stages;
+        for (; left >= S + U; left -= U) static_for<U>([&](auto i) { turn(i, std::false_type{}, 0); });
+        for (;;) {
+#define BDA_RING_STAGE(I)                                                       \
+    if constexpr (I < U) {                                                      \
+        turn(std::integral_constant<int, I>{}, std::true_type{}, left);         \
+        if (--left == 0) break;                                                 \
     }
             BDA_RING_STAGE(0) BDA_RING_STAGE(1) BDA_RING_STAGE(2) BDA_RING_STAGE(3) BDA_RING_STAGE(4) BDA_RING_STAGE(5)
 #undef BDA_RING_STAGE
@@ -223,7 +247,7 @@ __device__ __forceinline__ void ring_loop(int n_stages, Prepare&& prepare, Reque
         uint32_t slot = 0;
         for (int left = n_stages; left > 0; --left) {
             const uint32_t next_slot = slot == (uint32_t)((S - 1) * C::STAGE) ? 0u : slot + (uint32_t)C::STAGE;
-            stage(zero, slot, next_slot);
+            stage(zero, slot, next_slot, std::false_type{}, 0);
             slot = next_slot;
         }
     }

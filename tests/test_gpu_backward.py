@@ -235,9 +235,18 @@ EDGES = [
 @pytest.mark.parametrize("T,d_c,d_h,H,offs", EDGES)
 @pytest.mark.parametrize("policy", [1, 2, 3, 4])
 def test_backward_every_tile_edges(T, d_c, d_h, H, offs, dtype, grad_dtype, policy):
-    """Tolerance as everywhere here; the longest contraction has 1056 terms, whose float32 sums are off by about
-    sqrt(1056) 2^-24 = 2e-6 of the result's size, far below a result's own rounding."""
+    """Tolerance as everywhere here; the longest contraction has 800 terms, whose float32 sums are off by about
+    sqrt(800) 2^-24 = 1.7e-6 of the result's size, far below a result's own rounding."""
     _check(T, d_c, d_h, H, offs, dtype, grad_dtype=grad_dtype, pad=8, policy=policy, seed=17)
+
+
+@pytest.mark.parametrize("policy", [0, 1, 2, 3, 4])
+def test_backward_short_contractions(policy):
+    """Contractions of 1 .. 12 stages of 64 for every tile: shorter than the ring, as long as it, whole turns of it and the
+    stages behind them; the last stage whole or in part, in one group or two.  Tolerance as everywhere here."""
+    for n in range(1, 13):
+        _check(70, 168, 32, [2 * n - 1] if n % 2 else [n, n - 1], [8, 136][: 1 if n % 2 else 2], wl.F16, pad=8, policy=policy, seed=n)
+        _check(64 * n - 24 * (n % 2), 168, 64, [n], [40], wl.BF16, grad_dtype=wl.F32, policy=policy, seed=n)
 
 
 @pytest.mark.parametrize("dtype", [wl.F16, wl.BF16])
