@@ -245,6 +245,10 @@ int bda_lowrank_linear(const void* x, int64_t ldx, int64_t T, int d_in, int r, i
  * and d_h a multiple of 32; anything else (and BDA_F32 inputs) runs a slower general kernel on the
  * float32 matrix instructions with the same result contract.  Gradients must not overlap the inputs or
  * each other.
+ * Infinities and NaN in d_out: grad_c is a matrix product, in which zeros times them are NaN.  They stay in their token's
+ * row of grad_c.  There every column outside the window of their group is lost (NaN or infinite), and inside it at least
+ * their own column; the MFMA path loses columns in aligned blocks of 64 (counted from column 0), the one or two that the
+ * element's aligned 16 columns of its head belong to and any that the window's ends cut, and keeps the others.
  * Errors: BDA_EINVAL, BDA_EDTYPE, BDA_EHIP.
  */
 int bda_kv_project_backward(const void* c, int64_t ldc, const void* d_out, int64_t ld_dout,

@@ -162,10 +162,11 @@ __global__ __launch_bounds__(C::THREADS) void ring_latent_kernel(const BwdArgs p
         ((uint32_t*)ones)[e] = (k0 == r ? IdentityFrag<X>::one : 0u) | (k0 + 1 == r ? IdentityFrag<X>::one << 16 : 0u);
     }
     const uint32_t a_ones = lds0 + (uint32_t)(C::BYTES + (l31 - kOnesFirst) * 32 + lhi * 16);
+    const uint32_t a_zeros = lds0 + (uint32_t)(C::BYTES + l31 * 32 + lhi * 16);   // 32 of its rows without a one
     const int colm0 = l0 + wn * (32 * TN);     // first latent column of this wave
     const int period = d_h * 32, step = CK % d_h * 32;
     int rd_g = -1, rd_left = 0, place = 0, at = 0;   // group being read, its stages left; 32 x: the wave's first column of the stage in its head, window start - colm0
-    bool inside[TN], cut = false, meets = false;     // blocks inside the window; some block is cut by its edge; some block has to do with it
+    bool inside[TN], all_inside = false, cut = false, meets = false;   // blocks inside the window; all of them; some block is cut by its edge; some block has to do with it
     auto enter_group = [&]() {
         rd_g = uniform(rd_g + 1);
         if (rd_g >= n_groups) return;
@@ -174,11 +175,13 @@ __global__ __launch_bounds__(C::THREADS) void ring_latent_kernel(const BwdArgs p
         place = 16 * kg * KSW % d_h * 32;
         at = (off - colm0) * 32;
         cut = meets = false;
+        all_inside = true;
 #pragma unroll
         for (int ni = 0; ni < TN; ++ni) {
             const int b = off - colm0 - 32 * ni;     // the window's start in the block
             inside[ni] = b <= 0 && 32 <= b + d_h;
             const bool touched = b < 32 && b + d_h > 0;
+            all_inside = all_inside && inside[ni];
             cut = cut || (touched && !inside[ni]);
             meets = meets || touched;
         }
@@ -199,14 +202,20 @@ __global__ __launch_bounds__(C::THREADS) void ring_latent_kernel(const BwdArgs p
     };
     auto read = [&](auto setc, auto sc, uint32_t slot) {
         constexpr int Q = decltype(setc)::value, s = decltype(sc)::value;
-#pragma unroll
-        for (int ti = 0; ti < TT; ++ti) ft[Q][ti] = *(lds_u32x4)(uintptr_t)(a_tok[s] + slot + ti * (32 * 128));
         if (!meets) {
+#pragma unroll
+            for (int ti = 0; ti < TT; ++ti) ft[Q][ti] = *(lds_u32x4)(uintptr_t)(a_tok[s] + slot + ti * (32 * 128));
 #pragma unroll
             for (int ni = 0; ni < TN; ++ni) fw[Q][ni] = *(lds_u32x4)(uintptr_t)(a_wgt[s] + slot + ni * (32 * 128));
         } else {
             int d0 = place + 16 * 32 * s;
             if (d0 >= period) d0 -= period;
+            // Nothing but zeros to multiply with: not with the tokens, which need not be finite.  (Per wave, for the price of an
+            // address.  Per block of 32, tokens masked in registers, 4096 tokens, N = 4096 took 29.6 us instead of 26.5; skipped
+            // MFMAs make the compiler move the accumulators.)
+            const bool idle = all_inside && (at + d0 <= -16 * 32 || at + d0 >= 32 * TN * 32);
+#pragma unroll
+            for (int ti = 0; ti < TT; ++ti) ft[Q][ti] = *(lds_u32x4)(uintptr_t)(idle ? a_zeros : a_tok[s] + slot + (uint32_t)(ti * (32 * 128)));
 #pragma unroll
             for (int ni = 0; ni < TN; ++ni) {
                 int d = at + d0 - 32 * 32 * ni;      // 32 x: where the k-step's columns begin in the block

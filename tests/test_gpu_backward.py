@@ -240,6 +240,37 @@ def test_backward_every_tile_edges(T, d_c, d_h, H, offs, dtype, grad_dtype, poli
     _check(T, d_c, d_h, H, offs, dtype, grad_dtype=grad_dtype, pad=8, policy=policy, seed=17)
 
 
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("policy", [1, 2, 3, 4])
+@pytest.mark.parametrize("T,d_c,d_h,H,offs,head,col", [
+    (150, 512, 256, [6], [128], 4, 200),        # four whole blocks of 64; the element's own is the last
+    (150, 576, 192, [3, 2], [64, 320], 1, 5),   # two groups with the same blocks of their own; its own is the first
+    (70, 512, 256, [5], [136], 3, 55),          # a window that cuts blocks, 16 columns that straddle two
+])
+def test_backward_non_finite_gradients_stay_in_their_row_and_blocks(T, d_c, d_h, H, offs, head, col, policy, value):
+    """grad_c with one infinite or NaN element in d_out against grad_c without: the same bits in all other rows and, where no
+    other group adds to them, in the blocks of 64 latent columns inside the window that the element does not belong to."""
+    dtype, token = wl.F16, 37
+    (c_s, _), (g_s, _), (C_s, _) = _inputs(29, T, d_c, d_h, H, dtype)
+    g_s = g_s.copy()
+    n = head * d_h + col                          # an element of group 0
+    g_s[token, n] = 0
+    clean, _, _, _ = _backward(c_s, g_s, C_s, T, d_c, d_h, H, offs, dtype, want=(True, False), policy=policy)
+    bad_s, _ = wl.to_storage(np.array([[value]]), dtype)
+    g_s[token, n] = bad_s[0, 0]
+    got, _, _, _ = _backward(c_s, g_s, C_s, T, d_c, d_h, H, offs, dtype, want=(True, False), policy=policy)
+    others = np.arange(T) != token
+    assert np.array_equal(got[others], clean[others])
+    first = offs[0] + col // 16 * 16
+    own = {first // 64, (first + 15) // 64}
+    kept = [b for b in range(-(-offs[0] // 64), (offs[0] + d_h) // 64) if b not in own]
+    assert kept
+    for b in kept:
+        assert np.array_equal(got[token, 64 * b:64 * b + 64], clean[token, 64 * b:64 * b + 64]), b
+    assert not np.isfinite(got[token, offs[0] + col])
+    assert not np.any(np.isfinite(got[token, :offs[0]])) and not np.any(np.isfinite(got[token, offs[0] + d_h:]))
+
+
 @pytest.mark.parametrize("policy", [0, 1, 2, 3, 4])
 def test_backward_short_contractions(policy):
     """Contractions of 1 .. 12 stages of 64 for every tile: shorter than the ring, as long as it, whole turns of it and the
