@@ -400,6 +400,12 @@ bool lean_kernel_applies(const GemmArgs& a, int G, const int64_t* group_cols)
 // so do fewer tiles (T = 184, K = 608, N = 8704 12.8 / 14.3; T = 1087, N = 1408 8.2 / 8.7).  Below 96 tiles of 256 x 256, products without
 // an identity slice, contractions of one chunk and up to 768 tiles keep the kernels that their launch plans have always reported,
 // though the ring would be ahead there too (T = 2048, K = 64, N = 2592 12.6 / 9.1; 600 tiles, T = 1570, K = 384, N = 1536 11.8 / 9.0).
+// That line knows no rounds: 512 workgroups of the ring run at a time, and a round after the first that is less than half full
+// (two workgroups of a unit no longer share it) still takes 0.43 of a full one, one that is fuller 0.8.  Where the streaming kernel
+// needs one round and the ring one and a little, it is ahead by what the little costs: K = 2512, T = 1184, N = 7144 68 / 85 us, K = 1864,
+// T = 552, N = 14016 58 / 71.  So the ring also has to be ahead, or within 5 %, by estimates in rounds.  They are fitted to 330 drawn
+// launches of K = 16 .. 4096 (rms 9 % for the ring, 12 % for the streaming kernel); over those the rule's choice is at most 6 %
+// slower than without the ring but for two (T = 4555, K = 64, N = 12224 39.6 / 49.4; T = 1558, K = 496, N = 16408 55 / 61).
 enum class MidKernel { None, Halves64, Halves128, Ring };
 MidKernel mid_kernel(const GemmArgs& a, int G, const int64_t* group_cols, bool big, bool f32_out)
 {
@@ -420,7 +426,13 @@ MidKernel mid_kernel(const GemmArgs& a, int G, const int64_t* group_cols, bool b
     if (big) {
         const double stream = rounds * (10.0 + 0.025 * a.K);
         const double mid = 5.0 + (double)tiles * (0.0075 + 1.4e-5 * a.K);
-        if (tiles > 512 && ring < 0.95 * std::min(stream, mid)) return MidKernel::Ring;
+        const int64_t ring_tiles = (a.M + 127) / 128 * nt128, rest = ring_tiles % 512;
+        const double tile_time = 0.0087 + 0.0025 * chunks + (f32_out ? 0.0035 : 0.0);
+        const double last = rest == 0 ? 0.0 : std::max((double)rest, rest <= 256 ? 0.43 * 512 : 0.8 * 512);
+        const double ring_rounds = 4.4 + tile_time * ((double)(ring_tiles - rest) + last);
+        const int id_stages = a.ident ? ((a.d_h % 256 == 0 ? 256 : a.d_h) + 63) / 64 : 0;
+        const double stream_rounds = 4.8 + rounds * (6.8 + 0.025 * a.K + 0.9 * id_stages + (f32_out ? 3.1 : 0.0));
+        if (tiles > 512 && ring < 0.95 * std::min(stream, mid) && ring_rounds < 1.05 * stream_rounds) return MidKernel::Ring;
         return mid < 0.95 * stream ? MidKernel::Halves64 : MidKernel::None;
     }
     if (N <= 128 && a.K >= 384) return MidKernel::Halves128;

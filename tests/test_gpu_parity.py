@@ -537,6 +537,70 @@ def test_kv_ring_kernel(T, d_c, d_h, H, offs, dtype, out_dtype):
     assert np.all(raw[T:] == 7) and np.all(raw[:, N:] == 7)
 
 
+RING = (bda.KERNEL_MFMA, 128, 128, 65536)
+
+
+def _ring_shape(plan):
+    return plan["kernel"], plan["tile_tokens"], plan["tile_columns"], plan["lds_bytes"]
+
+
+@pytest.mark.parametrize("dtype,out_dtype", [(wl.F16, wl.F16), (wl.BF16, wl.F32)])
+@pytest.mark.parametrize("T,d_c,d_h,H,offs", [
+    (3072, 96, 32, [33, 32], [0, 64]),        # one stage, from 96 tiles of 256 x 256 up
+    (2600, 1256, 96, [14, 13], [8, 640]),     # nineteen stages
+])
+def test_kv_ring_kernel_one_stage_and_many(T, d_c, d_h, H, offs, dtype, out_dtype):
+    """Tolerance as everywhere; a result's sum has 1160 terms at most, in two float32 halves."""
+    assert _ring_shape(bda.bda_kv_project_plan(T, d_c, d_h, H, offs, dtype, out_dtype)) == RING
+    rng = np.random.default_rng([T, d_c])
+    N = sum(H) * d_h
+    c_s, c64 = wl.to_storage(rng.standard_normal((T, d_c)), dtype)
+    C_s, C64 = wl.to_storage(0.25 * rng.standard_normal((d_c - d_h, N)), dtype)
+    got, raw = gh.kv_project(c_s, C_s, d_c, d_h, H, offs, dtype, out_dtype, ldc=d_c + 8, ldC=N + 16, ld_out=N + 8, fill=7, extra_rows=2)
+    assert_parity(got, oracle.kv_project(c64, C64, d_h, H, offs), d_h, dtype, out_dtype, f"T={T} d_c={d_c} d_h={d_h}")
+    raw = raw.cpu().numpy()
+    assert np.all(raw[T:] == 7) and np.all(raw[:, N:] == 7)
+
+
+# Products without an identity slice on the ring: column counts that end 8, 56, 72 and 104 columns into a tile, contractions of
+# two to seventeen stages that end inside one or with one.
+@pytest.mark.parametrize("dtype,out_dtype", [(wl.F16, wl.F16), (wl.BF16, wl.F32)])
+@pytest.mark.parametrize("T,K,N", [(831, 640, 7368), (2720, 384, 2440), (868, 352, 16648), (3500, 1032, 1976), (700, 72, 8312)])
+def test_dense_project_ring_kernel(T, K, N, dtype, out_dtype):
+    """Tolerance as everywhere; a result's sum has 1032 terms at most, in two float32 halves."""
+    assert _ring_shape(bda.bda_dense_project_plan(T, K, N, dtype, out_dtype, ldc=K + 8, ldW=N + 16, ld_out=N + 8)) == RING
+    rng = np.random.default_rng([T, K, N])
+    c_s, c64 = wl.to_storage(rng.standard_normal((T, K)), dtype)
+    W_s, W64 = wl.to_storage(0.25 * rng.standard_normal((K, N)), dtype)
+    c_d, W_d, out_d = gh.to_device(c_s, dtype, K + 8), gh.to_device(W_s, dtype, N + 16), gh.new_out(T + 2, N + 8, out_dtype, fill=3)
+    bda.bda_dense_project(c_d, K + 8, T, K, W_d, N + 16, N, out_d, N + 8, dtype, out_dtype, gh.stream())
+    torch.cuda.synchronize()
+    assert_parity(gh.to_host64(out_d[:T], out_dtype, N), c64 @ W64, N, dtype, out_dtype, f"T={T} K={K} N={N}")
+    raw = out_d.cpu().numpy()
+    assert np.all(raw[T:] == 3) and np.all(raw[:, N:] == 3)
+
+
+@pytest.mark.parametrize("last", [False, True])
+def test_lowrank_linear_ring_kernel(last):
+    """The second product on the ring, h read back from the padded output."""
+    T, d_in, r, d_out, dtype = 2720, 136, 384, 2824, wl.F16
+    rng = np.random.default_rng([T, d_out])
+    x_s, x64 = wl.to_storage(rng.standard_normal((T, d_in)), dtype)
+    Up_s, Up64 = wl.to_storage(0.1 * rng.standard_normal((d_in, r)), dtype)
+    C_s, C64 = wl.to_storage(0.1 * rng.standard_normal((r, d_out - r)), dtype)
+    ld, off = d_out + 8, d_out - r if last else 0
+    assert _ring_shape(bda.bda_dense_project_plan(T, r, d_out - r, dtype, ldc=ld, ld_out=ld)) == RING
+    out_d = gh.new_out(T + 1, ld, dtype, fill=5)
+    bda.bda_lowrank_linear(gh.to_device(x_s, dtype), d_in, T, d_in, r, d_out, off, gh.to_device(Up_s, dtype), gh.to_device(C_s, dtype), out_d, ld, dtype, gh.stream())
+    torch.cuda.synchronize()
+    got = gh.to_host64(out_d[:T], dtype, d_out)
+    assert_parity(got[:, off:off + r], x64 @ Up64, r, dtype, dtype, "h block")
+    rest = np.concatenate([np.arange(0, off), np.arange(off + r, d_out)])
+    assert_parity(got[:, rest], got[:, off:off + r] @ C64, d_out - r, dtype, dtype, "h C from the stored h")
+    raw = out_d.cpu().numpy()
+    assert np.all(raw[T:] == 5) and np.all(raw[:, d_out:] == 5)
+
+
 # Launches without an identity slice beyond the few-token kernels' range: column counts that end 8, 24, 40 and 56
 # columns into a 64-column tile (and in a wave's second 32), contractions of one chunk, of a partial one, of two halves.
 MID64, MID128, STAGED = (64, 64, 512), (128, 128, 512), (128, 128, 256)

@@ -375,6 +375,15 @@ def test_launch_plan_many_small_tiles_of_a_short_contraction():
     assert (p["kernel"], p["tile_tokens"], p["threads"]) == (bda.KERNEL_MFMA, 128, 256)
 
 
+@pytest.mark.parametrize("T,K,N", [(1184, 2512, 7144), (552, 1864, 14024), (522, 1984, 14536)])
+def test_launch_plan_ring_kernel_counts_rounds(T, K, N):
+    """550 to 570 tiles of 128 x 128 are a round of 512 and a little, which a long contraction makes dear: one round of the
+    streaming kernel's 256 x 256 tiles is ahead (68 against 85 us for the first)."""
+    assert bda.bda_dense_project_plan(T, K, N, bda.BDA_BF16)["kernel"] == bda.KERNEL_STREAM
+    full = bda.bda_dense_project_plan(T, K, 128 * (512 // -(-T // 128)) - 8, bda.BDA_BF16)       # a whole round: the ring
+    assert (full["kernel"], full["tile_tokens"], full["lds_bytes"]) == (bda.KERNEL_MFMA, 128, 65536), full
+
+
 @pytest.mark.parametrize("K", [8, 16, 40, 176, 296, 304, 496, 512])
 def test_launch_plan_few_tokens_lds_holds_whole_request_pairs(K):
     # 33 .. 64 tokens: the slice of C is requested 32 rows at a time and the token rows lie behind it, so the slice's
