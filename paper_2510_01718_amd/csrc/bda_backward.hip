@@ -88,7 +88,9 @@ int launch_ring(BwdArgs& a, int64_t rows, const int64_t* group_cols, int G, hipS
 // Few output columns: 18 tokens, N = 64 6.9 / 5.4 / 5.6 / 5.1 with the four latent tiles, 912 tokens, N = 160 8.2 / 6.4 / 6.3 / 5.8, 20000
 // tokens, d_c = 160, N = 512 20.3 / 20.6 / 24.5 / 14.4; from N of about 600 on the eight waves are ahead (9 tokens, N = 2048 12.7 against 14.9).
 // Register-staged 64 x 64 tiles, which served N up to 512 before, took 5.3, 5.9 and 25.7 there; between N = 256 and 512 they
-// were up to 1 us ahead (1199 tokens, N = 512 6.9 against 7.2; 2 tokens, d_c = 600 6.9 and 7.8).
+// were up to 1.2 us ahead (1199 tokens, N = 512 6.9 against 7.2; 2 tokens, d_c = 600 6.9 and 7.8; 19 tokens, N = 512 6.7 and 7.9).  Weight
+// gradients of 160 to 450 tokens are up to 0.5 us behind them as well (400 tokens, N = 256 5.2 and 5.7), all others level or ahead.
+// Neither gap is the ring's depth: with six slots, or one loop body in place of six, both took longer.
 template <typename X, typename OutT, bool WEIGHT>
 int launch_sized(BwdArgs& a, int64_t rows, const int64_t* group_cols, int G, hipStream_t st)
 {

@@ -171,8 +171,9 @@ __device__ __forceinline__ void wait_stages(int stages)
 // loop the compiler moves the accumulators about, which those tiles have no registers for.
 // Unrolled, the last stages are a loop of their own that requests nothing past the end.  Such requests (zeros, which the
 // kernel waits for before its LDS takes the sums) cost S stages of LDS writes, 0.4 us of a launch of 6; with the question in
-// every stage a long loop took 12 % more.  (After the last stage a slot that was never filled may be read; nothing is
-// multiplied with it.)
+// every stage a long loop took 12 % more.  It asks once a stage, behind the MFMAs: between them it split the stage into pieces that
+// the compiler does not schedule across (weight gradient, 425 tokens, N = 768 6.06 -> 5.81 us, 167 tokens, N = 160 5.10 -> 4.98).
+// (After the last stage a slot that was never filled may be read; nothing is multiplied with it.)
 //   prepare()  sets up the requests of the next stage to be asked for      request(j, slot)  issues the j-th of them
 //   read(set, s, slot)  fetches k-step s of the stage being read           next()  goes on to the next stage to be read
 //   multiply(set, f)  the k-step's MFMAs, with f(i) after the i-th         (slot: its first byte)
@@ -203,23 +204,27 @@ __device__ __forceinline__ void ring_loop(int n_stages, Prepare&& prepare, Reque
                 __builtin_amdgcn_sched_barrier(0);
                 multiply(now, [](auto) {});
             } else {
-                const bool more = !LAST || left > S;
                 wait_stages<P, S - 2>(LAST ? left - 2 : S - 2);
                 __syncthreads();
                 next();
                 read(other, zero, next_slot);
-                if (more) prepare();
+                if constexpr (!LAST) prepare();
                 __builtin_amdgcn_sched_barrier(0);
                 multiply(now, [&](auto i) {
                     constexpr int I = decltype(i)::value;
                     __builtin_amdgcn_sched_barrier(0);
-                    if (I * PER < P && more)
+                    if constexpr (!LAST && I * PER < P)
                         static_for<PER>([&](auto jj) {
                             constexpr int j = I * PER + decltype(jj)::value;
                             if constexpr (j < P) request(std::integral_constant<int, j>{}, slot);
                         });
                     __builtin_amdgcn_sched_barrier(0);
                 });
+                if constexpr (LAST)
+                    if (left > S) {
+                        prepare();
+                        static_for<P>([&](auto j) { request(j, slot); });
+                    }
             }
             __builtin_amdgcn_sched_barrier(0);
         });
