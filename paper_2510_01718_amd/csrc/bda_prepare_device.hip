@@ -105,7 +105,7 @@ struct PrepArgs {
     int cand, n_cand, n_parts;   // first candidate window of this launch and their number
     int w_type, c_type;          // element types of W / side and of C / side_out
     int search, c_slots;         // candidate windows in the outputs; how many of them in C (see Slot)
-    uint32_t width_magic;        // ceil(2^32 / d_h) (O)
+    uint32_t width_magic;        // see Slot (O)
     int write_side, measure;     // strip_kernel: store the companion block; sum the reconstruction errors
     int lane_sums;               // measure_kernel: one sum per lane in LDS
 };
@@ -127,7 +127,7 @@ struct Slot {
     void* p;
     int64_t ld;
     int first;                   // rows or pieces before this window's
-    uint32_t magic;              // ceil(2^32 / d_h); 0: rows of C's layout
+    uint32_t magic;              // ceil(2^32 / d_h), not read for heads of one column; 0: rows of C's layout
 };
 __device__ __forceinline__ Slot slot_of(const PrepArgs& a, int z)
 {
@@ -138,7 +138,7 @@ __device__ __forceinline__ int64_t slot_row(const Slot& s, int kk, int h, int n)
 {
     const int q = s.first + kk;
     if (!s.magic) return q * s.ld + (int64_t)h * n;
-    const int block = (int)__umulhi((uint32_t)q, s.magic);
+    const int block = n == 1 ? q : (int)__umulhi((uint32_t)q, s.magic);
     return ((int64_t)h * n + (q - block * n)) * s.ld + block * n;
 }
 
@@ -1637,8 +1637,8 @@ int run_prepare(const PrepCall& c, const Plan& p, unsigned char* ws, hipStream_t
         a.search = 1;
         int beside = c.d_side / K;
         if (c.side_kind == BDA_SIDE_O) {       // (one head width: a multiplication in place of the division; exact to 2^24 pieces)
-            a.width_magic = c.d_h > 1 ? (uint32_t)((((uint64_t)1 << 32) + c.d_h - 1) / c.d_h) : 0;
-            beside = c.d_h > 1 ? c.d_h * std::min(c.d_side / c.d_h, 1024) / K : 0;
+            a.width_magic = c.d_h > 1 ? (uint32_t)((((uint64_t)1 << 32) + c.d_h - 1) / c.d_h) : 1;
+            beside = c.d_h * std::min(c.d_side / c.d_h, 1024) / K;
         }
         a.c_slots = beside >= p.n_cand ? 0 : 1;
         slots = beside + a.c_slots;

@@ -204,7 +204,9 @@ def test_prepare_device_ex_head_widths_at_the_edges_of_the_register_tiles(d_c, H
     (512, 1, 128, 1000, oracle.SIDE_Q, wl.F32, oracle.RESIDUAL_MIN),   # largest strip, rows that end inside one
     (496, 3, 96, 405, oracle.SIDE_O, wl.F16, oracle.OFFSET_SEARCH),    # second window of a launch fills the companion output to its edge
     (513, 1, 96, 70, oracle.SIDE_Q, wl.F16, oracle.RESIDUAL_MIN),      # just past the strips
-    (64, 40, 16, 33, oracle.SIDE_Q, wl.BF16, oracle.RESIDUAL_MIN)])
+    (64, 40, 16, 33, oracle.SIDE_Q, wl.BF16, oracle.RESIDUAL_MIN),
+    (97, 3, 1, 300, oracle.SIDE_O, wl.F16, oracle.OFFSET_SEARCH),      # heads of one column: pieces of one element, four windows per launch
+    (97, 3, 1, 192, oracle.SIDE_O, wl.BF16, oracle.RESIDUAL_MIN)])     # the same, both in the companion output
 def test_prepare_device_ex_windows_prepared_together(d_c, H, d_h, d_side, side_kind, store, mode):
     """Several candidate windows in one launch, their stored C's in the companion output meanwhile: strips, column
     tiles and windows that end on and off the kernels' tile sizes."""
