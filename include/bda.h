@@ -300,7 +300,8 @@ int bda_kv_project_packed(const void* c, int64_t ldc, int64_t T, int d_c, int d_
  *   7 = 64 x 256 with the lean streaming kernel where it applies (else as 0 without the small-T
  *       kernels).
  * bda_kv_project_backward_ex takes 1 .. 4 as the tiles of its 16-bit kernels from the largest: grad_c 128 x 128,
- * 64 x 128 and 64 x 64 (eight waves, four), grad_C 192 x 256, 128 x 256, 64 x 128 and 64 x 64; the rest as automatic.
+ * 64 x 128 and 64 x 64 (eight waves, four), grad_C 192 x 256, 128 x 256, 64 x 128 and 64 x 64, and 5 as grad_C's 128 x 128; the rest as
+ * automatic.
  * Results do not depend on the policy beyond which kernel computes them.  Every kernel and tile shape
  * adds the products over k in a fixed order of its own (one sum, or partial sums of groups of waves that
  * are then added), so two of them agree to the rounding of float32 sums, and calls that differ in T

@@ -31,7 +31,7 @@ int launched()
     return err == hipSuccess ? BDA_OK : fail(BDA_EHIP, "kernel launch: %s", hipGetErrorString(err));
 }
 
-// The gradients' tiles, largest first.
+// The gradients' tiles, largest first but for the last.
 typedef RingShape<128, 128, 1, 2, 4, 64, 4> LatentLarge;
 typedef RingShape<64, 128, 1, 2, 4, 64, 4> LatentMiddle;
 typedef RingShape<64, 64, 1, 1, 8, 128, 4> LatentSmall;
@@ -40,6 +40,7 @@ typedef RingShape<192, 256, 2, 4, 1, 32, 5> WeightLarge;
 typedef RingShape<128, 256, 2, 4, 1, 32, 6> WeightMiddle;
 typedef RingShape<64, 128, 1, 2, 4, 64, 4> WeightSmall;
 typedef RingShape<64, 64, 1, 1, 4, 64, 4> WeightSmallest;
+typedef RingShape<128, 128, 1, 2, 4, 64, 4> WeightSquare;
 
 // Tile grid of shape C: its number of tiles; rows x group_cols = extent of the output.
 template <typename C>
@@ -81,10 +82,14 @@ int launch_ring(BwdArgs& a, int64_t rows, const int64_t* group_cols, int G, hipS
 // The tile whose rounds over the 256 compute units (a workgroup each; two of the weight gradient's smallest, three of the
 // latent gradient's shortest) are estimated to take the least.  The estimates are us measured over the tiles: per 64 elements of the
 // contraction, and what a round takes beside them (first requests, sum over the waves, stores; less where it is the only one).
-// Over 60 drawn launches the weight's rule is within 7 % of the fastest tile.  A wrong tile: 4096 tokens,
-// d_c = 512, N = 4096 latent 33 / 26 / 34 us with the large, middle, small one; 1024 tokens 31 / 22 / 17; 8192 tokens,
-// N = 32768 276 / 387 / 441; weight, 4096 tokens, K = 384, N = 4096 65 / 43 / 24 / 28 with the four, 301 tokens, N = 7424
-// 11 / 8.9 / 12.7 / 11.4, 5861 tokens, N = 2560 89 / 58 / 33 / 28.
+// The weight gradient's stages also take longer the more compute units work (requests wait for one another, and the clock falls), so
+// a round's stage has a part for its share of the units.  Fitted to 550 drawn launches (rms 8 to 12 %), over which the rule is 0.1 % behind the
+// fastest tile on average and at most 7 %.
+// A wrong tile: 4096 tokens, d_c = 512, N = 4096 latent 33 / 26 / 34 us with the large, middle, small one; 1024 tokens 31 / 22 / 17; 8192 tokens,
+// N = 32768 276 / 387 / 441; weight, 4096 tokens, K = 384, N = 4096 65 / 42 / 23 / 24 / 28.5 with the five, 300 tokens, K = 128, N = 32768
+// 11.6 / 9.3 / 12.4 / 12.4 / 10.3.  The square one is for few rows of C or few columns, where 256 columns leave half of the units empty: 8192
+// tokens, K = 128, N = 32768 131 / 130 / 147 / 172 / 101, K = 256, N = 16384 125 / 98 / 102 / 130 / 72, K = 384, N = 8192 123 / 80 / 74 / 83 / 53
+// (register-staged tiles of 128 x 128 took 108, 86 and 84).
 // Few output columns: 18 tokens, N = 64 6.9 / 5.4 / 5.6 / 5.1 with the four latent tiles, 912 tokens, N = 160 8.2 / 6.4 / 6.3 / 5.8, 20000
 // tokens, d_c = 160, N = 512 20.3 / 20.6 / 24.5 / 14.4; from N of about 600 on the eight waves are ahead (9 tokens, N = 2048 12.7 against 14.9).
 // Register-staged 64 x 64 tiles, which served N up to 512 before, took 5.3, 5.9 and 25.7 there; between N = 256 and 512 they
@@ -97,22 +102,29 @@ int launch_sized(BwdArgs& a, int64_t rows, const int64_t* group_cols, int G, hip
     auto rounds = [](int64_t tiles, int64_t slots) { return (double)((tiles + slots - 1) / slots); };
     int pick = tile_policy() - 1;              // 1, 2, ...: that tile, from the largest (testing hook)
     if constexpr (WEIGHT) {
-        if (pick < 0 || pick > 3) {
-            const double chunks = (double)((a.T + 63) / 64), start = 2.0;   // a round's first requests and stores: about 2 us
-            const int64_t smallest = ring_grid<WeightSmallest>(a, rows, group_cols, G);
-            const double cost[4] = {rounds(ring_grid<WeightLarge>(a, rows, group_cols, G), 256) * (1.25 * chunks + start),
-                                    rounds(ring_grid<WeightMiddle>(a, rows, group_cols, G), 256) * (0.8 * chunks + start),
-                                    rounds(ring_grid<WeightSmall>(a, rows, group_cols, G), 256) * (0.4 * chunks + start),
-                                    smallest <= 256 ? 0.24 * chunks + start : rounds(smallest, 512) * (0.45 * chunks + start)};
+        if (pick < 0 || pick > 4) {
+            const double chunks = (double)((a.T + 63) / 64);
+            auto cost = [&](int64_t tiles, double start, double stage, double crowd) {   // stage + crowd: of a round that all units work in
+                const int64_t rest = tiles % 256;
+                return (double)(tiles / 256) * (start + chunks * (stage + crowd)) + (rest ? start + chunks * (stage + crowd * (double)rest / 256.0) : 0.0);
+            };
+            const int64_t smallest = ring_grid<WeightSmallest>(a, rows, group_cols, G), rest = smallest % 512;
+            const double two = 5.0 + 0.42 * chunks;   // a round with two workgroups on some unit
+            const double tile_cost[5] = {cost(ring_grid<WeightLarge>(a, rows, group_cols, G), 5.7, 0.88, 0.35),
+                                         cost(ring_grid<WeightMiddle>(a, rows, group_cols, G), 4.8, 0.55, 0.345),
+                                         cost(ring_grid<WeightSmall>(a, rows, group_cols, G), 4.8, 0.22, 0.175),
+                                         (double)(smallest / 512) * two + (rest > 256 ? two : cost(rest, 4.4, 0.156, 0.09)),
+                                         cost(ring_grid<WeightSquare>(a, rows, group_cols, G), 6.6, 0.305, 0.205)};
             pick = 0;
-            for (int i = 1; i < 4; ++i)
-                if (cost[i] < cost[pick]) pick = i;
+            for (int i = 1; i < 5; ++i)
+                if (tile_cost[i] < tile_cost[pick]) pick = i;
         }
         switch (pick) {
         case 0: return launch_ring<X, OutT, WeightLarge, true>(a, rows, group_cols, G, st);
         case 1: return launch_ring<X, OutT, WeightMiddle, true>(a, rows, group_cols, G, st);
         case 2: return launch_ring<X, OutT, WeightSmall, true>(a, rows, group_cols, G, st);
-        default: return launch_ring<X, OutT, WeightSmallest, true>(a, rows, group_cols, G, st);
+        case 3: return launch_ring<X, OutT, WeightSmallest, true>(a, rows, group_cols, G, st);
+        default: return launch_ring<X, OutT, WeightSquare, true>(a, rows, group_cols, G, st);
         }
     } else {
         if (pick < 0 || pick > 3) {

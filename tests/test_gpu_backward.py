@@ -233,7 +233,7 @@ EDGES = [
 
 @pytest.mark.parametrize("dtype,grad_dtype", [(wl.F16, wl.F32), (wl.BF16, wl.BF16)])
 @pytest.mark.parametrize("T,d_c,d_h,H,offs", EDGES)
-@pytest.mark.parametrize("policy", [1, 2, 3, 4])
+@pytest.mark.parametrize("policy", [1, 2, 3, 4, 5])
 def test_backward_every_tile_edges(T, d_c, d_h, H, offs, dtype, grad_dtype, policy):
     """Tolerance as everywhere here; the longest contraction has 800 terms, whose float32 sums are off by about
     sqrt(800) 2^-24 = 1.7e-6 of the result's size, far below a result's own rounding."""
@@ -271,7 +271,7 @@ def test_backward_non_finite_gradients_stay_in_their_row_and_blocks(T, d_c, d_h,
     assert not np.any(np.isfinite(got[token, :offs[0]])) and not np.any(np.isfinite(got[token, offs[0] + d_h:]))
 
 
-@pytest.mark.parametrize("policy", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("policy", [0, 1, 2, 3, 4, 5])
 def test_backward_short_contractions(policy):
     """Contractions of 1 .. 12 stages of 64 for every tile: shorter than the ring, as long as it, whole turns of it and the
     stages behind them; the last stage whole or in part, in one group or two.  Tolerance as everywhere here."""
@@ -281,7 +281,7 @@ def test_backward_short_contractions(policy):
 
 
 @pytest.mark.parametrize("dtype", [wl.F16, wl.BF16])
-@pytest.mark.parametrize("policy", [1, 2, 3, 4])
+@pytest.mark.parametrize("policy", [1, 2, 3, 4, 5])
 def test_backward_weight_gradient_sums_are_in_two_parts_at_least(dtype, policy):
     """Error of float32 weight gradients against 64 bits, for every tile.
 
