@@ -108,9 +108,9 @@ int bda_prepare_lowrank(const double* U, const double* V, int d_in, int r, int d
  * per head and window, or several that share its rows.  A search prepares candidate windows into the
  * outputs - one at a time into C, and with a companion, d_h <= 128 and d_c <= 512 as many more per
  * launch as side_out has room for (its rows and columns serve as scratch until the chosen window is
- * written) - measures the reconstruction error of what was stored, selects on the device, and
- * prepares the chosen window once more.  Asynchronous on `stream`; nothing comes back to the host and
- * nothing is allocated.
+ * written) - measures the reconstruction error of what was stored and selects on the device.  The
+ * chosen window's C is copied from side_out, where that held every candidate, and prepared once more
+ * otherwise.  Asynchronous on `stream`; nothing comes back to the host and nothing is allocated.
  *   W        device, d_c x (H d_h), ld = ldw, element type w_dtype (any bda_dtype).
  *   side     device or NULL: companion weight as in bda_prepare (W_q: d_side x H d_h; W_o: H d_h x
  *            d_side), ld = ld_side, element type w_dtype.
@@ -303,8 +303,8 @@ int bda_kv_project_packed(const void* c, int64_t ldc, int64_t T, int d_c, int d_
  * 64 x 128 and 64 x 64 (eight waves, four), grad_C 192 x 256, 128 x 256, 64 x 128 and 64 x 64, and 5 as grad_C's 128 x 128; the rest as
  * automatic.
  * Results do not depend on the policy beyond which kernel computes them.  Every kernel and tile shape
- * adds the products over k in a fixed order of its own (one sum, or partial sums of groups of waves that
- * are then added), so two of them agree to the rounding of float32 sums, and calls that differ in T
+ * adds the products over k in a fixed order of its own (one sum, or partial sums of groups of waves or of
+ * alternate k-steps that are then added), so two of them agree to the rounding of float32 sums, and calls that differ in T
  * alone may differ by as much.  Errors: as the plain call, plus BDA_EINVAL for a policy outside 0 .. 7.
  */
 int bda_kv_project_ex(const void* c, int64_t ldc, int64_t T, int d_c, int d_h,

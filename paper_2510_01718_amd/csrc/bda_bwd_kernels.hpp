@@ -18,7 +18,7 @@
 // the LDS read.
 // Bound: a stage's requests at 64 bytes a clock and compute unit beside its MFMAs, plus some 300 cycles of barrier and
 // bookkeeping a stage that both waves of a SIMD spend at the same time.  Against the kernels before (register-staged copies,
-// two halves of 2 x 2 waves): 8192 tokens, N = 32768, bf16: latent 381 -> 276 us, weight 282 -> 190; 4096 tokens, N = 4096,
+// two halves of 2 x 2 waves): 8192 tokens, N = 32768, bf16: latent 381 -> 278 us, weight 282 -> 193; 4096 tokens, N = 4096,
 // f16, float32 gradients: 41 -> 26 and 32 -> 24; 202 tokens, N = 30464: 193 -> 86 and 34 -> 13.
 // Whichever operand is contiguous in the OUTPUT is the MFMA's row operand, so that each lane holds four consecutive
 // elements of a row.

@@ -1062,6 +1062,8 @@ __global__ __launch_bounds__(kStripThreads) void strip_kernel(const PrepArgs a)
 // Vector instructions do not run beside the float64 MFMAs (one between every two MFMAs of a loop costs 12 cycles, four 19,
 // of the MFMA's 64), so conversions come together, addresses are scalar and a lane's squares stay in LDS till the end.
 // Same sums as strip_kernel, in the same order but for a lane's squares over the strips.
+// The form for 257 .. 512 columns spills 28 to 75 of its 256 registers (offsets of the strip's rows and tiles, which all strips share: stored once,
+// fetched once a strip); the loop over the windows has no scratch access.  The form up to 256 columns spills none.
 // Against strip_kernel: 25 windows of 16 heads for keys and values 7.05 -> 6.0 ms, two windows of 128 heads 2.15 -> 1.87 (with
 // the chosen window copied instead of prepared again; the matrix pipes busy 69 % of the time, 54 before); with the inversion
 // in panels 5.77 and 1.85.
