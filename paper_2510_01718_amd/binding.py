@@ -145,7 +145,7 @@ def _dp(a: Optional[np.ndarray]):
 
 
 # (These two run two to five times a call: one lookup each, and array types that are made once.  Calls of one token follow one another as
-# fast as the host issues them, 5.7 -> 5.3 us with these; the same launches in a graph take 2.8, 4.2 with weights that are not in a cache.)
+# fast as the host issues them, 5.7 -> 5.3 us with these; the same launches in a graph take 2.8, 4.3 with weights that are not in a cache.)
 def _ptr(x) -> Optional[int]:
     if x is None:
         return None
